@@ -30,7 +30,7 @@ GAMMAS = (1e-6, 1e-4, 1e-2, 1.0)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_daughters_config2_traffic.json")
 VALU_FILE = os.path.join(ROOT, "profiles", "k_daughters_config2_valu.json")
 KERNEL_SRC = os.path.join(ROOT, "paper_2312_02990_amd", "csrc", "ttcf_pairs.hip")
-PEF_SRC = os.path.join(ROOT, "paper_2312_02990_amd", "csrc", "ttcf_elongation.hip")
+PEF_SRC = os.path.join(ROOT, "paper_2312_02990_amd", "csrc", "ttcf_flow64.hip")
 PEF_VALU_FILE = os.path.join(ROOT, "profiles", "k_daughters_pef_n2048_valu.json")
 MIX_VALU_FILE = os.path.join(ROOT, "profiles", "k_daughters_mix_n2048_valu.json")
 CH_SRC = os.path.join(ROOT, "paper_2312_02990_amd", "csrc", "ttcf_channel.hip")

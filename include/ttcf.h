@@ -408,7 +408,9 @@ int32_t ttcf_pair_forces_static(const ttcf_system* sys, double gamma_dot, int64_
                                 double* out, void* stream);
 enum { TTCF_STATIC_SCRATCH_BYTES = 1 << 20 };
 
-/* Shape of the daughter step kernel (the knobs a tuner searches). variant: 0 automatic,
+/* Shape of the daughter step kernel (the knobs a tuner searches). variant: 0 automatic (FP32
+ * forces: 2 where it fits, else 1; FP64 forces: neighbour lists kept in LDS over several steps
+ * for systems of up to 2048 atoms without a block_threads of their own, else 1),
  * 1 cell list rebuilt every step (FP64 or FP32 forces), 2 pair list of radius r_cut + skin
  * rebuilt when needed (FP32 forces, at most 4096 atoms: every pair within the radius stored
  * once in per-workgroup global scratch, four atoms per thread, pair forces summed in 32-bit
@@ -439,7 +441,9 @@ int32_t ttcf_set_step_shape(ttcf_ctx* ctx, int32_t variant, int32_t threads, dou
  * architecture, N, round(1000 N/V), round(10000 r_cut), precision), replacing an older entry,
  * and written to *out (may be NULL). While no explicit shape is set (ttcf_set_step_shape(ctx,
  * 0, 0, 0, 0), the default), ttcf_step uses the cached shape of each daughter's system, the
- * list grid of its skin and, per launch, the workgroup size of the largest system. Synchronises
+ * list grid of its skin and, per launch, the workgroup size of the largest system; with FP64
+ * forces a cached shape holds where the system runs in the cell form (see
+ * ttcf_set_step_shape). Synchronises
  * the context's stream. Errors: TTCF_EINVAL (no stored states, bad arguments, no shape fits),
  * TTCF_EDEVICE (probe daughters unhealthy other than by list overflow, or a HIP error). */
 typedef struct ttcf_shape {

@@ -11,7 +11,7 @@ LIB = os.path.join(HERE, "libttcf.so")
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = [os.path.join(CSRC, f) for f in (
     "ttcf_kernels.hip", "ttcf_pairs.hip", "ttcf_mlp.hip", "ttcf_capi.hip", "ttcf_channel.hip",
-    "ttcf_channel_capi.hip", "ttcf_estimators.hip", "ttcf_elongation.hip")]
+    "ttcf_channel_capi.hip", "ttcf_estimators.hip", "ttcf_flow64.hip")]
 HEADERS = [os.path.join(CSRC, "ttcf_internal.h"), os.path.join(CSRC, "ttcf_device.h"),
            os.path.join(CSRC, "ttcf_channel.h"),
            os.path.join(os.path.dirname(HERE), "include", "ttcf.h")]

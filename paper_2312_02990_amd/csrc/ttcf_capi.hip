@@ -1074,8 +1074,9 @@ int32_t spawn_impl(ttcf_ctx* c, int32_t mother, int32_t n_states, int64_t steps_
 
 // Launch shape of one group of daughters in one kernel form. threads_req > 0 fixes the
 // workgroup size; kmax is the list capacity of the neighbour-list form.
-// block_explicit: some member's system fixes its workgroup size (block_threads > 0).
-int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, bool block_explicit,
+// list64: FP64 forces may run over neighbour lists (no step shape was set and no member's system
+// fixes its workgroup size, which ask for the cell form).
+int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, bool list64,
                    int variant, int precision, int32_t n_steps, int threads_req, BatchLaunch* L) {
     int nmax = 0, cmax = 0, lcmax = 0, threads = 0, kmax = 0;
     size_t nl_lds = 0;
@@ -1097,7 +1098,6 @@ int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, b
     // the pair-list form: four atoms per thread of each job, the workgroup as large as the
     // largest job needs (the thread count of a job does not depend on the launch)
     if (!nlf && threads_req > 0) threads = threads_req;
-    (void)block_explicit;
     const int apt = nlf ? pair_job_apt(nmax) : pick_apt(nmax, threads);
     if (apt < 0) return fail(c, TTCF_EINVAL, "batch needs more than 4 atoms per thread");
     // pair words in LDS when every job's fit beside its layout (four atoms per thread only),
@@ -1132,6 +1132,28 @@ int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, b
                                     "daughters recording the extra observables");
     L->pair_stride = pair_stride;
     L->pairs_lds = pairs_lds ? 1 : 0;
+    if (!nlf && list64 && precision == TTCF_PREC_FP64 && !L->obs && !L->field &&
+        nmax <= kPefMaxAtoms) {
+        // FP64 forces over neighbour lists wherever a workgroup holds them (the cell form
+        // rebuilds its grid and scans 27 cells in FP64 every step) and a list has room for half
+        // as many neighbours again as its radius holds on average (atoms with more are tried
+        // against every other atom)
+        int cells = 0;
+        double most = 0.0;
+        for (const DaughterDesc* dp : group) {
+            cells = std::max(cells, pef_max_cells(dp->sys.volume, dp->sys.rc) + 8);
+            most = std::max(most, flow64_neighbours(dp->sys.n / dp->sys.volume, dp->sys.rc));
+        }
+        Flow64Shape f{};
+        if (1.5 * most <= flow64_list_cap() && flow64_shape(nmax, cells, L->n_jobs, c->num_cu, c->max_lds, &f)) {
+            L->flow64 = 1;
+            L->apt = f.apt;
+            L->threads = f.threads;
+            L->cmax = f.cmax;
+            L->grid = f.grid;
+            return TTCF_OK;
+        }
+    }
     L->lds_bytes = nlf ? (pairs_lds ? nl_lds_pl : nl_lds) : lds_bytes_for(nmax, cmax, threads, precision);
     if (L->lds_bytes > c->max_lds) return fail(c, TTCF_EINVAL, "batch exceeds the LDS of one workgroup");
     const int per_cu_lds = (int)(c->max_lds / L->lds_bytes);
@@ -1287,7 +1309,7 @@ int32_t step_impl(ttcf_ctx* c, int32_t n_steps, const std::vector<char>* only,
                              c->mothers[c->batches[c->live[i].batch].mother].sys.block_threads > 0;
         }
         BatchLaunch L{};
-        rc = plan_group(c, ds, block_explicit, form == 1 ? kVariantCells : kVariantNeighbourList,
+        rc = plan_group(c, ds, !force && !c->shape_explicit && !block_explicit, form == 1 ? kVariantCells : kVariantNeighbourList,
                         precision, n_steps, eff[group[0]].threads, &L);
         if (rc != TTCF_OK) return rc;
         if (form != 1 && !L.pairs_lds) {
@@ -1318,24 +1340,30 @@ int32_t step_impl(ttcf_ctx* c, int32_t n_steps, const std::vector<char>* only,
         P.n_jobs = (int32_t)pef[th].size();
         P.max_steps = n_steps;
         P.thermo = th & 1;
-        P.mix = th >> 1;
+        P.flow = 1 + (th >> 1);
+        int cells = 0;
         for (int32_t i : pef[th]) {
             const SysDev& sd = c->descs[i].sys;
             P.nmax = std::max(P.nmax, sd.n);
             // no cell grid of a box of this volume exceeds volume / r_c^3 cells
-            P.cmax = std::max(P.cmax, pef_max_cells(sd.volume, sd.rc) + 8);
+            cells = std::max(cells, pef_max_cells(sd.volume, sd.rc) + 8);
         }
-        P.threads = pef_threads(P.nmax);
-        P.lds_bytes = lds_bytes_pef(P.nmax, P.cmax);
-        if (P.lds_bytes > c->max_lds)
+        Flow64Shape f{};
+        if (pef_grid_bytes(P.nmax, cells) > c->max_lds ||
+            !flow64_shape(P.nmax, cells, P.n_jobs, c->num_cu, c->max_lds, &f))
             return fail(c, TTCF_EINVAL, "planar-elongation batch exceeds the LDS of one workgroup");
+        P.threads = f.threads;
+        P.apt = f.apt;
+        P.grid = f.grid;
+        P.cmax = f.cmax;
+        P.queue = c->d_queue;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (timing) {
             HIPCHECK(c, hipEventCreate(&e0));
             HIPCHECK(c, hipEventCreate(&e1));
             HIPCHECK(c, hipEventRecord(e0, c->stream));
         }
-        HIPCHECK(c, launch_pef(P, c->stream));
+        HIPCHECK(c, launch_flow64(P, c->stream));
         if (timing) {
             HIPCHECK(c, hipEventRecord(e1, c->stream));
             c->pending_events.emplace_back(e0, e1);
@@ -2179,11 +2207,9 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
     std::vector<double*> hdst(nd);
     std::vector<int32_t> hints(3 * (size_t)nd + n_states + 1);
     std::vector<char> nl_of(nd, 0);
-    bool block_explicit = false;
     for (GraphPart& P : parts) {
         const ttcf_graph_desc* gd = P.gd;
         const Mother& m = c->mothers[gd->mother];
-        block_explicit = block_explicit || m.sys.block_threads > 0;
         P.shape = resolve_shape(c, m.dev, precision, nullptr);
         const double nf = 3.0 * P.n - 3.0;
         for (int32_t st = 0; st < P.n_states; ++st) {
@@ -2240,10 +2266,15 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
         const int form = gi / 2;
         const StepShape& sh = parts[0].shape;
         int threads_req = sh.threads;
-        for (const GraphPart& P : parts)
+        bool block_explicit = false;
+        for (const GraphPart& P : parts) {
             if (grp[0] >= P.d0 && grp[0] < P.d0 + P.nd) threads_req = P.shape.threads;
+            for (int32_t d : grp)
+                if (d >= P.d0 && d < P.d0 + P.nd)
+                    block_explicit = block_explicit || c->mothers[P.gd->mother].sys.block_threads > 0;
+        }
         BatchLaunch B{};
-        rc = plan_group(c, hp, block_explicit, form == 1 ? kVariantCells : kVariantNeighbourList,
+        rc = plan_group(c, hp, !c->shape_explicit && !block_explicit, form == 1 ? kVariantCells : kVariantNeighbourList,
                         precision, n_steps, threads_req, &B);
         if (rc != TTCF_OK) return bail(rc, c->err);
         if (form != 1 && !B.pairs_lds) {

@@ -1,0 +1,1230 @@
+// ttcf_flow64.hip -- daughters with FP64 pair forces on gfx950: shear (Lees-Edwards), planar
+// elongation, and mixed flow, isokinetic or Nose-Hoover.
+//
+// The Introduction names elongational and mixed flows among the fields TTCF extends to, and
+// Section Mathematical Framework notes that a field other than shear needs mappings of its
+// own. The paper prints no equations for them; the dynamics is SLLOD (Eq. system1 with the
+// velocity gradient u_x = e x + s y, u_y = -e y in place of the shear; e = 0 is Eq. system1
+// itself), dr/dt = p + A r, dp/dt = F - A p - alpha p, A = [[e, s, 0], [0, -e, 0], [0, 0, 0]],
+// in the cell the flow carries:
+//   elongation  diag(L_x e^{et}, L_y e^{-et}, L_z);
+//   mixed       H(t) = exp(A t) diag(L): H_xx = L e^{et}, H_xy = L s t sinhc(e t), H_yy = L e^{-et};
+//   shear       the sliding brick, offset fmod(s L_y t, L_x).
+// Daughters are short transients, so the carried cells need no reproducible lattice (the host
+// refuses a daughter whose cell would become narrower than 3 r_c).
+//
+// One step of h = dt, tau = h/2, is E(tau) K(tau) D(h) [forces] K(tau) E(tau): E the flow part
+// p -> exp(-A tau) p scaled back to the old p.p, K the exact constrained kick under fixed
+// forces (Zhang, J. Chem. Phys. 106, 6102 (1997)), D the exact streaming r -> exp(A h)(r + N p),
+// N = int_0^h exp(-A u) du; Nose-Hoover daughters run Z T E K D K E T Z without the scalings.
+// Every scalar of both halves follows in closed form from moments of (p, F) summed once after
+// the force pass, so a step needs one workgroup reduction and two barriers.
+//
+// Layout: one workgroup per daughter at a time, one, two or four atoms per thread, momenta and
+// forces in registers, FP64 positions in LDS (fractions of the carried cell, or the brick's
+// coordinates). The atoms go to the threads in the cell order of the call's start, which atoms
+// leave slowly, so a wave's lanes work on neighbours: their list builds read the same cells.
+// Each atom has the list of every atom within r_c + skin of it, built from a cell grid and kept
+// until the atoms may have moved too far (f64_fresh). A list holds both sides of a pair, so each
+// force is one thread's sum in list order: results are deterministic (they follow the rebuilds,
+// so splitting a run over calls changes roundings).
+//
+// What bounds it: FP64 issue. Rebuilding the grid and scanning the 27-cell stencil in FP64 every
+// step spends most of its lanes on candidates out of range; a list of about 8 entries per atom of
+// which 5 are in range leaves the pair arithmetic (32 FP64 instructions a pair). Measured on one
+// MI355X against the kernels that scanned the stencil every step: 1024 daughters of N = 2048 over
+// 50 steps, shear 14.97 ms -> 4.14 (2.5e10 atom-steps/s), elongation 15.09 -> 4.02; 256 mixed-flow
+// Nose-Hoover daughters of N = 864 over 100 steps 4.91 -> 1.12. Of a step's time about half is
+// the force pass, a fifth the list builds, the rest the step's scalars and the two barriers.
+
+#include <math.h>
+
+#include "ttcf_device.h"
+
+namespace ttcf {
+namespace {
+
+constexpr int kF64Cap = 24;        // list entries per atom
+constexpr double kF64Skin = 0.15;   // list skin, in units of r_c (0.12: +5%, 0.2: +1%)
+constexpr int kF64Red = 16;        // doubles per wave in the reduction scratch
+constexpr int kF64Side = 4;        // atoms of a thread whose pairs are evaluated side by side
+constexpr int kScan = 3;           // candidates per lane per trip of the list build
+
+enum Flow64 { kFlowShear = 0, kFlowElong = 1, kFlowMixed = 2 };
+
+__host__ __device__ inline size_t f64_align(size_t v) { return (v + 15) & ~(size_t)15; }
+
+struct F64Plan {
+    size_t xy, z, start, cnt, sid, list, red, wmax, scan, misc, total;
+};
+
+__host__ __device__ inline F64Plan f64_plan(int nmax, int cmax, int threads, int apt) {
+    F64Plan p;
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o = f64_align(o + bytes);
+        return at;
+    };
+    p.xy = take(2 * sizeof(double) * (size_t)nmax);
+    p.z = take(sizeof(double) * (size_t)nmax);
+    p.start = take(sizeof(int32_t) * (size_t)(cmax + 1));
+    // the build's counts and ids live in the list's bytes until the list is written
+    const size_t cnt = f64_align(sizeof(int32_t) * (size_t)cmax);
+    const size_t build = cnt + sizeof(uint16_t) * (size_t)nmax;
+    const size_t list = sizeof(uint16_t) * (size_t)kF64Cap * threads * apt;
+    p.list = take(list > build ? list : build);
+    p.cnt = p.list;
+    p.sid = p.list + cnt;
+    p.red = take(sizeof(double) * kF64Red * kMaxWaves);
+    p.wmax = take(sizeof(float) * kMaxWaves);
+    p.scan = take(sizeof(int32_t) * kMaxWaves);
+    p.misc = take(sizeof(int32_t) * 4);
+    p.total = o;
+    return p;
+}
+
+typedef __attribute__((address_space(1))) double GlobalF64;
+
+struct F64Lds {
+    double2* xy;       // [nmax] positions; during a build the same bytes hold
+    double* z;         //        float4 sorted[nmax]
+    int32_t* start;    // [cells + 1] first sorted slot of each cell
+    int32_t* cnt;      // [cells] counts, then cursors (build only)
+    uint16_t* sid;     // [nmax] atoms by cell (build only)
+    uint16_t* list;    // [kF64Cap][threads][APT]
+    double* red;       // [waves][kF64Red]
+    float* wmax;       // [waves]
+    int32_t* scan;     // [waves]
+    int32_t* misc;     // [0]: an atom's list outgrew its capacity; [1]: the job
+};
+
+__device__ __forceinline__ F64Lds f64_carve(char* base, int nmax, int cmax, int threads, int apt) {
+    const F64Plan p = f64_plan(nmax, cmax, threads, apt);
+    F64Lds S;
+    S.xy = (double2*)(base + p.xy);
+    S.z = (double*)(base + p.z);
+    S.start = (int32_t*)(base + p.start);
+    S.cnt = (int32_t*)(base + p.cnt);
+    S.sid = (uint16_t*)(base + p.sid);
+    S.list = (uint16_t*)(base + p.list);
+    S.red = (double*)(base + p.red);
+    S.wmax = (float*)(base + p.wmax);
+    S.scan = (int32_t*)(base + p.scan);
+    S.misc = (int32_t*)(base + p.misc);
+    return S;
+}
+
+// A value that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Sum of K <= P doubles over the workgroup (P = 4, 8 or 16), the same total in every thread.
+// Inside a wave a transposed reduction splits the P values over the lane bits (P - 1 exchanges
+// and adds in place of P log2 64), the remaining lane bits add in place; then the waves in
+// sequence. Fixed order; one barrier, and `red` may be written again only after a later one.
+template <int K, int P>
+__device__ __forceinline__ void f64_sum(double (&v)[K], double* red) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    double a[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) a[k] = k < K ? v[k] : 0.0;
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
+    int idx = 0;
+    xstage<P / 2, 0xB1>(a, b0);  // quad_perm [1, 0, 3, 2]
+    xstage<P / 4, 0x4E>(a, b1);  // quad_perm [2, 3, 0, 1]
+    if constexpr (P >= 8)
+        xstage<P / 8, 0x124>(a, b2);  // row_ror:4
+    else
+        a[0] += dpp_move<0x124>(a[0]);
+    if constexpr (P >= 16)
+        xstage<P / 16, 0x128>(a, b3);  // row_ror:8
+    else
+        a[0] += dpp_move<0x128>(a[0]);
+    a[0] += swap_partner<16>(a[0]);
+    a[0] += swap_partner<32>(a[0]);
+    idx = (P / 2) * (int)b0 + (P / 4) * (int)b1 + (P >= 8 ? (P / 8) * (int)b2 : 0) +
+          (P >= 16 ? (int)b3 : 0);
+    if (lane < 16 && (P >= 8 || !b2) && (P >= 16 || !b3)) red[wave * kF64Red + idx] = a[0];
+    __syncthreads();
+    double s = 0.0;
+    if (lane < K)
+        for (int w = 0; w < nw; ++w) s += red[w * kF64Red + lane];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = lane_value(s, k);
+}
+
+// The cell of one moment: how a separation is formed from two stored positions.
+struct Cell64 {
+    double hxx, hxy, hyy, hzz;  // carried cell; shear: the brick's edges, hxy the offset
+    double ixx, iyy, izz;       // shear: reciprocal edges
+};
+
+// 1/x: the hardware estimate (relative error e below 2^-22) and one third-order step, which leaves
+// e^3.
+__device__ __forceinline__ double f64_recip(double x) {
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, __builtin_fma(e, e, e), r);
+}
+
+// Separation of positions (dx, dy, dz apart, as stored), through the image that holds every pair
+// within r_c: the cell's perpendicular widths are 3 r_c or more, so that pair's fractional
+// separations stay below 1/3 and rounding finds its image.
+template <int F>
+__device__ __forceinline__ void f64_sep(const Cell64& H, double dx, double dy, double dz,
+                                        double (&d)[3]) {
+    if constexpr (F == kFlowShear) {
+        const double ny = rint(dy * H.iyy);
+        dx = __builtin_fma(-ny, H.hxy, dx);
+        d[1] = __builtin_fma(-ny, H.hyy, dy);
+        d[0] = __builtin_fma(-rint(dx * H.ixx), H.hxx, dx);
+        d[2] = __builtin_fma(-rint(dz * H.izz), H.hzz, dz);
+    } else {
+        dx -= rint(dx);
+        dy -= rint(dy);
+        dz -= rint(dz);
+        d[0] = dx * H.hxx;
+        if constexpr (F == kFlowMixed) d[0] = __builtin_fma(dy, H.hxy, d[0]);
+        d[1] = dy * H.hyy;
+        d[2] = dz * H.hzz;
+    }
+}
+
+__device__ __forceinline__ double f64_frac(double s) {
+    s -= floor(s);
+    return s >= 1.0 ? 0.0 : s;
+}
+
+__device__ __forceinline__ int f64_cell(double s, int nc) {
+    const int c = (int)(s * (double)nc);
+    return c < 0 ? 0 : (c > nc - 1 ? nc - 1 : c);
+}
+
+// What a list was built for.
+struct List64 {
+    double rl;        // list radius: every pair closer than this at the build is listed
+    int64_t k;        // strain counter at the build
+    bool no_skin;     // a list with a skin outgrew its capacity: build at r_c every step
+};
+
+// Grid of a build: the tilted cell (shear: the offset reduced to half an edge) and cells at least
+// the list radius wide in its perpendicular widths, 3 or more a side, split in half along x (a
+// row's members lie consecutively, so the scan takes 5 half cells of it in place of 3 cells: a
+// sixth fewer candidates), at most cmax half cells in all.
+struct Grid64 {
+    double hxy;
+    int nx, ny, nz;  // nx counts half cells: twice as many along x
+};
+
+template <int F>
+__device__ __forceinline__ double f64_tilt(const Cell64& H) {
+    if constexpr (F == kFlowShear) return H.hxy - H.hxx * rint(H.hxy * H.ixx);
+    return F == kFlowMixed ? H.hxy : 0.0;
+}
+
+__device__ __forceinline__ Grid64 f64_grid(const Cell64& H, double hxy, double wx, double reach,
+                                           int cmax) {
+    Grid64 g;
+    g.hxy = hxy;
+    int nx = max(3, (int)fmin(wx / reach, 1000.0)), ny = max(3, (int)fmin(H.hyy / reach, 1000.0)),
+        nz = max(3, (int)fmin(H.hzz / reach, 1000.0));
+    while (2 * nx * ny * nz > cmax) {  // coarser cells, widest direction first (cmax >= 54)
+        if (nx >= ny && nx >= nz)
+            --nx;
+        else if (ny >= nz)
+            --ny;
+        else
+            --nz;
+    }
+    g.nx = __builtin_amdgcn_readfirstlane(2 * nx);
+    g.ny = __builtin_amdgcn_readfirstlane(ny);
+    g.nz = __builtin_amdgcn_readfirstlane(nz);
+    return g;
+}
+
+// Counting sort of the atoms into the grid's cells, members of a cell in index order (an atom's
+// place is the number of smaller indexes in its cell, so the order does not depend on the
+// placement atomics). place[j]: the sorted slot of atom t + j T; cell[j] its cell (-1: no atom);
+// cart: its position in the tilted cell. Begins with nothing of the previous list in use; ends without a barrier
+// (S.start and S.sid are complete).
+template <int F, int APT>
+__device__ __forceinline__ void f64_sort(const F64Lds& S, const Cell64& H, const Grid64& g, int n,
+                                         const double (&x)[APT], const double (&y)[APT],
+                                         const double (&z)[APT], int (&place)[APT],
+                                         int (&cell)[APT], float (&cart)[APT][3]) {
+    const int T = blockDim.x, t = threadIdx.x;
+    const int C = g.nx * g.ny * g.nz;
+    for (int c = t; c < C; c += T) S.cnt[c] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        const int a = t + j * T;
+        cell[j] = -1;
+        place[j] = 0;
+        double fx = x[j], fy = y[j], fz = z[j];
+        if constexpr (F == kFlowShear) {
+            fy = f64_frac(y[j] * H.iyy);
+            fx = f64_frac((x[j] - g.hxy * fy) * H.ixx);
+            fz = f64_frac(z[j] * H.izz);
+        }
+        cart[j][0] = (float)(fx * H.hxx + fy * g.hxy);
+        cart[j][1] = (float)(fy * H.hyy);
+        cart[j][2] = (float)(fz * H.hzz);
+        if (a < n) {
+            cell[j] = f64_cell(fx, g.nx) + g.nx * (f64_cell(fy, g.ny) + g.ny * f64_cell(fz, g.nz));
+            place[j] = atomicAdd(&S.cnt[cell[j]], 1);
+        }
+    }
+    __syncthreads();
+    scan_cells(S.cnt, S.start, C, S.scan);
+    if (t == 0) S.start[C] = n;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < APT; ++j)
+        if (cell[j] >= 0) S.sid[S.start[cell[j]] + place[j]] = (uint16_t)(t + j * T);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        if (cell[j] >= 0) {
+            const int a = t + j * T;
+            const int b = S.start[cell[j]], e = S.start[cell[j] + 1];
+            int q = b;
+            for (int i = b; i < e; ++i) q += S.sid[i] < a ? 1 : 0;
+            place[j] = q;
+        }
+    }
+}
+
+// Builds the lists of the positions x, y, z (wrapped into the cell here) and publishes them in
+// S.xy, S.z. nh: the own atoms' list lengths; returns the wave's longest. The scan runs in FP32 over nine rows of five half cells (two ranges where a row
+// wraps in x), kScan candidates per lane per trip; the FP32 test has a margin for its own
+// rounding, so a list misses no pair of its radius.
+template <int F, int APT>
+__device__ int f64_build(const F64Lds& S, const Cell64& H, int n, int cmax, double rc,
+                         double (&x)[APT], double (&y)[APT], double (&z)[APT], List64& L,
+                         int (&nh)[APT]) {
+    const int T = blockDim.x, t = threadIdx.x;
+    float4* sorted = (float4*)S.xy;
+    const double hxy = f64_tilt<F>(H);
+    const double wx = H.hxx * H.hyy / sqrt(hxy * hxy + H.hyy * H.hyy);
+    const double wmin = fmin(wx, fmin(H.hyy, H.hzz));
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        if constexpr (F == kFlowShear) {
+            const double ny = floor(y[j] * H.iyy);
+            y[j] = __builtin_fma(-ny, H.hyy, y[j]);
+            x[j] = __builtin_fma(-ny, H.hxy, x[j]);
+            if (y[j] < 0.0 || y[j] >= H.hyy) y[j] = 0.0;  // a quotient rounded to a whole edge
+            x[j] = wrap1(x[j], H.hxx);
+            z[j] = wrap1(z[j], H.hzz);
+        } else {
+            x[j] = f64_frac(x[j]);
+            y[j] = f64_frac(y[j]);
+            z[j] = f64_frac(z[j]);
+        }
+    }
+    for (;;) {
+        double skin = L.no_skin ? 0.0 : fmin(kF64Skin * rc, wmin * (1.0 / 3.0) - rc);
+        if (skin < 0.05 * rc) skin = 0.0;
+        L.rl = rc + skin;
+        // FP32 positions and images are off by less than 2^-23 edges, separations by 2^-21
+        const double pad = L.rl + 5e-7 * (H.hxx + fabs(hxy) + H.hyy + H.hzz);
+        const Grid64 g = f64_grid(H, hxy, wx, pad, cmax);
+        if (t == 0) S.misc[0] = 0;
+        int place[APT], cell[APT];
+        float cart[APT][3];
+        f64_sort<F, APT>(S, H, g, n, x, y, z, place, cell, cart);
+#pragma unroll
+        for (int j = 0; j < APT; ++j)
+            if (cell[j] >= 0)
+                sorted[place[j]] =
+                    make_float4(cart[j][0], cart[j][1], cart[j][2], __int_as_float(t + j * T));
+        __syncthreads();
+        const float fxx = (float)H.hxx, fxy = (float)hxy, fyy = (float)H.hyy, fzz = (float)H.hzz;
+        const float rl2 = (float)(pad * pad) * (1.0f + 1e-6f);
+        bool over = false;
+#pragma unroll
+        for (int j = 0; j < APT; ++j) {
+            const int self = t + j * T;
+            const bool own = cell[j] >= 0;
+            const int c0 = own ? cell[j] : 0;
+            const int cx = c0 % g.nx, cy = (c0 / g.nx) % g.ny, cz = c0 / (g.nx * g.ny);
+            // half cells m0..m1-1 of a row, and w0..w1-1 across the x edge (nx is 6 or more)
+            const int m0 = max(cx - 2, 0), m1 = min(cx + 3, g.nx);
+            const int w0 = cx < 2 ? g.nx + cx - 2 : 0, w1 = cx < 2 ? g.nx : max(cx + 3 - g.nx, 0);
+            const float wrap = cx < 2 ? fxx : -fxx;
+            uint16_t* list = S.list + (t * APT + j);
+            int got = 0;
+#pragma unroll 1
+            for (int r = 0; r < 9; ++r) {
+                const int dz = r / 3 - 1, dy = r % 3 - 1;
+                int zz = cz + dz, yy = cy + dy;
+                const float uz = cart[j][2] + (zz < 0 ? fzz : (zz >= g.nz ? -fzz : 0.0f));
+                zz += zz < 0 ? g.nz : (zz >= g.nz ? -g.nz : 0);
+                const float uy = cart[j][1] + (yy < 0 ? fyy : (yy >= g.ny ? -fyy : 0.0f));
+                float ux = cart[j][0];
+                if constexpr (F != kFlowElong) ux += yy < 0 ? fxy : (yy >= g.ny ? -fxy : 0.0f);
+                const float uw = ux + wrap;
+                yy += yy < 0 ? g.ny : (yy >= g.ny ? -g.ny : 0);
+                const int rowb = g.nx * (yy + g.ny * zz);
+                const int lo0 = S.start[rowb + m0];
+                const int len0 = own ? S.start[rowb + m1] - lo0 : 0;
+                const int lo1 = S.start[rowb + w0];
+                const int len = len0 + (own ? S.start[rowb + w1] - lo1 : 0);
+                const int off1 = lo1 - len0;
+                for (int v = 0; __builtin_amdgcn_ballot_w64(v < len) != 0; v += kScan) {
+                    float4 m[kScan];
+#pragma unroll
+                    for (int i = 0; i < kScan; ++i) {
+                        const int vv = v + i;
+                        m[i] = sorted[vv < len ? vv + (vv < len0 ? lo0 : off1) : 0];
+                    }
+#pragma unroll
+                    for (int i = 0; i < kScan; ++i) {
+                        const int vv = v + i;
+                        const float d0 = (vv < len0 ? ux : uw) - m[i].x;
+                        const float d1 = uy - m[i].y, d2 = uz - m[i].z;
+                        const float r2 = d0 * d0 + d1 * d1 + d2 * d2;
+                        const int id = __float_as_int(m[i].w);
+                        if ((vv < len) & (id != self) & (r2 < rl2)) {
+                            if (got < kF64Cap) list[got * (T * APT)] = (uint16_t)id;
+                            ++got;
+                        }
+                    }
+                }
+            }
+            nh[j] = got;
+            over = over || got > kF64Cap;
+        }
+        if (over) S.misc[0] = 1;
+        __syncthreads();
+        if (S.misc[0] == 0 || skin == 0.0) break;
+        L.no_skin = true;  // again at r_c (uniform: every thread read the same flag)
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        const int a = t + j * T;
+        if (a < n) {
+            S.xy[a] = make_double2(x[j], y[j]);
+            S.z[a] = z[j];
+        }
+    }
+    int most = 0;
+#pragma unroll
+    for (int j = 0; j < APT; ++j) most = max(most, min(nh[j], kF64Cap));
+    most = __builtin_amdgcn_readlane((int)wave_max_dpp((float)most), 63);
+    __syncthreads();
+    return most;
+}
+
+// Forces of the own atoms over their lists, and the thread's share of the pair virials: shear
+// w0 = W_xy; elongation w0 = W_xx - W_yy; mixed both (w0 = W_xx - W_yy, w1 = W_xy). Every pair is
+// seen from both sides, so each side adds half. The thread's atoms run side by side (two
+// independent chains), the next list word and positions loaded a trip ahead.
+template <int F, int APT>
+__device__ __forceinline__ void f64_forces(const F64Lds& S, const Cell64& H, int n, double rc2,
+                                           double ca, const int (&nh)[APT], int longest,
+                                           double (&fx)[APT], double (&fy)[APT],
+                                           double (&fz)[APT], double& w0, double& w1) {
+    const int T = blockDim.x, t = threadIdx.x;
+    double a0 = 0.0, a1 = 0.0;
+    constexpr int P = APT < kF64Side ? APT : kF64Side;  // atoms side by side
+#pragma unroll
+    for (int q = 0; q < APT; q += P) {
+        double xi[P], yi[P], zi[P], gx[P], gy[P], gz[P];
+        int own[P];
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            const int a = t + (q + j) * T;
+            own[j] = a < n ? a : 0;
+            const double2 p = S.xy[own[j]];
+            xi[j] = p.x;
+            yi[j] = p.y;
+            zi[j] = S.z[own[j]];
+            gx[j] = gy[j] = gz[j] = 0.0;
+        }
+        int len[P];
+        bool over = false;  // an atom has no complete list (only ever at r_c)
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            const bool o = nh[q + j] > kF64Cap;
+            len[j] = o ? 0 : nh[q + j];
+            over = over || o;
+        }
+        // entries k of the P atoms (clamped: nothing past the longest list is read)
+        struct Word {
+            uint16_t id[P];
+        };
+        auto word = [&](int k) -> Word {
+            k = k < longest ? k : longest - 1;
+            Word w;
+            __builtin_memcpy(&w, __builtin_assume_aligned(S.list + (k * T + t) * APT + q, 2 * P), 2 * P);
+            return w;
+        };
+        double2 pj[P];
+        double zj[P];
+        auto load = [&](const Word& w, int k) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const int m = k < len[j] ? (int)w.id[j] : own[j];
+                pj[j] = S.xy[m];
+                zj[j] = S.z[m];
+            }
+        };
+        auto pair = [&](int j, const double2& p, double z, bool listed) {
+            double d[3];
+            f64_sep<F>(H, xi[j] - p.x, yi[j] - p.y, zi[j] - z, d);
+            const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+            const double inv = f64_recip(r2);
+            const double s3 = inv * inv * inv;
+            double fs = s3 * (48.0 * s3 - 24.0 * ca) * inv;
+            fs = (listed && r2 < rc2) ? fs : 0.0;
+            gx[j] += fs * d[0];
+            gy[j] += fs * d[1];
+            gz[j] += fs * d[2];
+            if constexpr (F == kFlowShear) {
+                a0 += d[0] * (fs * d[1]);
+            } else {
+                a0 += fs * (d[0] * d[0] - d[1] * d[1]);
+                if constexpr (F == kFlowMixed) a1 += fs * (d[0] * d[1]);
+            }
+        };
+        Word next{};
+        if (longest > 0) {
+            load(word(0), 0);
+            next = word(1);
+        }
+#pragma unroll 1
+        for (int k = 0; k < longest; ++k) {
+            double2 pc[P];
+            double zc[P];
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                pc[j] = pj[j];
+                zc[j] = zj[j];
+            }
+            load(next, k + 1);
+            next = word(k + 2);
+#pragma unroll
+            for (int j = 0; j < P; ++j)
+                pair(j, pc[j], zc[j], k < len[j]);
+        }
+        if constexpr (F == kFlowShear) {
+            // an atom with more neighbours than a list holds: every other atom is tried
+            if (__builtin_amdgcn_ballot_w64(over) != 0) {
+#pragma unroll 1
+                for (int m = 0; m < n; ++m) {
+                    const double2 pm = S.xy[m];
+                    const double zm = S.z[m];
+#pragma unroll
+                    for (int j = 0; j < P; ++j)
+                        pair(j, pm, zm, nh[q + j] > kF64Cap && m != own[j]);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            // a carried-flow daughter this dense fails its health check
+            fx[q + j] = F != kFlowShear && nh[q + j] > kF64Cap ? __builtin_nan("") : gx[j];
+            fy[q + j] = gy[j];
+            fz[q + j] = gz[j];
+        }
+    }
+    w0 = 0.5 * a0;
+    w1 = 0.5 * a1;
+}
+
+// Moments of (p, F) from which both half steps follow.
+struct Mom64 {
+    double pp, xx, yy, xy;        // sum p.p, p_x^2, p_y^2, p_x p_y
+    double fp, gxx, gyy, gxy, gyx;  // sum F.p, F_x p_x, F_y p_y, F_x p_y, F_y p_x
+    double ff, qxx, qyy, qxy;     // sum F.F, F_x^2, F_y^2, F_x F_y
+};
+
+// Moments summed over the workgroup, with the pair virials and (shear) the positions' sum, which
+// carries a non-finite coordinate to the health check.
+template <int F, int APT>
+__device__ __forceinline__ Mom64 f64_moments(const double (&px)[APT], const double (&py)[APT],
+                                             const double (&pz)[APT], const double (&fx)[APT],
+                                             const double (&fy)[APT], const double (&fz)[APT],
+                                             double& w0, double& w1, double& pos, double* red) {
+    Mom64 m{};
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        m.pp += px[j] * px[j] + py[j] * py[j] + pz[j] * pz[j];
+        m.xx += px[j] * px[j];
+        m.yy += py[j] * py[j];
+        m.xy += px[j] * py[j];
+        m.fp += fx[j] * px[j] + fy[j] * py[j] + fz[j] * pz[j];
+        m.gxx += fx[j] * px[j];
+        m.gyy += fy[j] * py[j];
+        m.gxy += fx[j] * py[j];
+        m.gyx += fy[j] * px[j];
+        m.ff += fx[j] * fx[j] + fy[j] * fy[j] + fz[j] * fz[j];
+        m.qxx += fx[j] * fx[j];
+        m.qyy += fy[j] * fy[j];
+        m.qxy += fx[j] * fy[j];
+    }
+    if constexpr (F == kFlowShear) {
+        double v[12] = {m.pp, m.xy, m.yy, m.fp, m.gxy, m.gyx, m.qxy, m.gyy, m.qyy, m.ff, w0, pos};
+        f64_sum<12, 16>(v, red);
+        m = Mom64{v[0], 0, v[2], v[1], v[3], 0, v[7], v[4], v[5], v[9], 0, v[8], v[6]};
+        w0 = v[10];
+        pos = v[11];
+    } else if constexpr (F == kFlowElong) {
+        double v[10] = {m.pp, m.xx, m.yy, m.fp, m.gxx, m.gyy, m.ff, m.qxx, m.qyy, w0};
+        f64_sum<10, 16>(v, red);
+        m = Mom64{v[0], v[1], v[2], 0, v[3], v[4], v[5], 0, 0, v[6], v[7], v[8], 0};
+        w0 = v[9];
+    } else {
+        double v[15] = {m.pp,  m.xx, m.yy,  m.xy,  m.fp,  m.gxx, m.gyy, m.gxy,
+                        m.gyx, m.ff, m.qxx, m.qyy, m.qxy, w0,    w1};
+        f64_sum<15, 16>(v, red);
+        m = Mom64{v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10], v[11], v[12]};
+        w0 = v[13];
+        w1 = v[14];
+    }
+    return m;
+}
+
+// The flow part E, p -> (fa p_x + fc p_y, fd p_y, p_z), on the moments (not rescaled).
+template <int F>
+__device__ __forceinline__ void f64_flow(Mom64& m, double fa, double fc, double fd) {
+    if constexpr (F == kFlowShear) {
+        m.pp += 2.0 * fc * m.xy + fc * fc * m.yy;
+        m.fp += fc * m.gxy;
+        m.xy += fc * m.yy;
+    } else {
+        const double zz = m.pp - m.xx - m.yy, gzz = m.fp - m.gxx - m.gyy;
+        m.xx = fa * fa * m.xx;
+        m.gxx = fa * m.gxx;
+        if constexpr (F == kFlowMixed) {
+            m.xx += 2.0 * fa * fc * m.xy + fc * fc * m.yy;
+            m.gxx += fc * m.gxy;
+            m.xy = fd * (fa * m.xy + fc * m.yy);
+            m.gxy = fd * m.gxy;
+            m.gyx = fa * m.gyx + fc * m.gyy;
+        }
+        m.yy = fd * fd * m.yy;
+        m.gyy = fd * m.gyy;
+        m.pp = m.xx + m.yy + zz;
+        m.fp = m.gxx + m.gyy + gzz;
+    }
+}
+
+// The kick K, p -> (p + F s) / sd, on the moments.
+__device__ __forceinline__ void f64_kick(Mom64& m, double s, double isd) {
+    const double i2 = isd * isd;
+    m.pp = (m.pp + 2.0 * s * m.fp + s * s * m.ff) * i2;
+    m.xx = (m.xx + 2.0 * s * m.gxx + s * s * m.qxx) * i2;
+    m.yy = (m.yy + 2.0 * s * m.gyy + s * s * m.qyy) * i2;
+    m.xy = (m.xy + s * (m.gxy + m.gyx) + s * s * m.qxy) * i2;
+    m.fp = (m.fp + s * m.ff) * isd;
+    m.gxx = (m.gxx + s * m.qxx) * isd;
+    m.gyy = (m.gyy + s * m.qyy) * isd;
+    m.gxy = (m.gxy + s * m.qxy) * isd;
+    m.gyx = (m.gyx + s * m.qxy) * isd;
+}
+
+__device__ __forceinline__ void f64_scale(Mom64& m, double c) {
+    const double c2 = c * c;
+    m.pp *= c2;
+    m.xx *= c2;
+    m.yy *= c2;
+    m.xy *= c2;
+    m.fp *= c;
+    m.gxx *= c;
+    m.gyy *= c;
+    m.gxy *= c;
+    m.gyx *= c;
+}
+
+__device__ __forceinline__ double f64_phi(double u) { return u == 0.0 ? 1.0 : -expm1(-u) / u; }
+
+// sinh(x) / x from e^x and e^-x; the power series where their difference would cancel (the first
+// omitted term is below 1e-16 for |x| < 0.5)
+__device__ __forceinline__ double f64_sinhc(double x, double ep, double em) {
+    const double u = x * x;
+    double c = 1.0 + u * (1.0 / 156.0);
+    c = 1.0 + u * (1.0 / 110.0) * c;
+    c = 1.0 + u * (1.0 / 72.0) * c;
+    c = 1.0 + u * (1.0 / 42.0) * c;
+    c = 1.0 + u * (1.0 / 20.0) * c;
+    c = 1.0 + u * (1.0 / 6.0) * c;
+    return u < 0.25 ? c : 0.5 * (ep - em) / x;
+}
+
+// What a step reads besides the moments; LDS keeps it out of the force loop's registers.
+struct Const64 {
+    double l0x, l0y, lz, il0x, il0y, ilz;  // edges at strain 0 and their reciprocals
+    double er, sr, irn;      // flow rates (shear: sr; elongation: er), 1 / the response's divisor
+    double fa, fc, fd;       // exp(-A tau)
+    double nxx, nxy, nyy;    // N = int_0^h exp(-A u) du
+    double h, k0, root2k0, nh_iq, nh_target, inv_v, rc, rc2, ca;
+    double mu, drift;        // growth rate bound of separations; |N p| <= drift h |p|
+};
+
+// The carried cell at strain counter k, and e^{-zeta tau} (Nose-Hoover): one exp evaluation for
+// all three values, a lane each.
+template <int F, bool NH>
+__device__ __forceinline__ void f64_cell_at(const Const64& Q, const SysDev& sys, int64_t k,
+                                            double zeta, Cell64& H, double& damp) {
+    const int lane = threadIdx.x & 63;
+    const double tau = 0.5 * Q.h;
+    damp = 1.0;
+    if constexpr (F == kFlowShear) {
+        H.hxy = uniform(le_offset_nb(sys, Q.sr, k, Q.il0x));
+        if constexpr (NH) damp = uniform(exp(-zeta * tau));
+    } else {
+        const double x = Q.er * ((double)k * Q.h);
+        const double v = exp(lane == 0 ? x : (lane == 1 ? -x : (NH ? -zeta * tau : 0.0)));
+        const double ep = lane_value(v, 0), em = lane_value(v, 1);
+        H.hxx = uniform(Q.l0x * ep);
+        H.hyy = uniform(Q.l0y * em);
+        H.ixx = uniform(Q.il0x * em);
+        H.iyy = uniform(Q.il0y * ep);
+        if constexpr (F == kFlowMixed)
+            H.hxy = uniform(Q.l0y * Q.sr * ((double)k * Q.h) * f64_sinhc(x, ep, em));
+        if constexpr (NH) damp = lane_value(v, 2);
+    }
+}
+
+// Whether lists built at strain counter L.k still hold every pair within r_c: a pair now closer
+// than r_c was closer than sigma (r_c + 2 path) at the build, sigma >= |exp(-A t)| over the time
+// since (exp(mu t), mu the largest eigenvalue of the symmetric part of -A) and path the longest
+// |N p| path of an atom. e^v <= 1 + v + v^2 for v <= 1.
+__device__ __forceinline__ bool f64_fresh(const Const64& Q, const List64& L, int64_t k, float path) {
+    const double v = Q.mu * ((double)(k - L.k) * Q.h);
+    const double sigma = 1.0 + v + v * v;
+    return v <= 1.0 && sigma * (Q.rc + 2.0 * Q.drift * (double)path) <= L.rl;
+}
+
+template <int F, bool NH, int APT>
+__device__ __forceinline__ void flow64_job(DaughterDesc* dp, const PefLaunch& B, const F64Lds& S,
+                                           Const64& Q, SysDev& sys) {
+    const int T = blockDim.x, t = threadIdx.x;
+    const int n = dp->sys.n;
+    const int32_t done0 = dp->done;
+    int health = dp->health;
+    int todo = min(B.max_steps, dp->n_steps - done0);
+    if (health != 0) todo = 0;
+    if (todo <= 0) return;  // uniform over the workgroup
+    if (t == 0) {
+        sys = dp->sys;
+        Q.h = dp->sys.dt;
+        Q.er = F == kFlowShear ? 0.0 : (F == kFlowElong ? dp->gamma_dot : dp->erate);
+        Q.sr = F == kFlowShear ? dp->gamma_dot : (F == kFlowElong ? 0.0 : dp->srate);
+        Q.irn = 1.0 / dp->gamma_dot;
+        const double h = Q.h, tau = 0.5 * h, x = Q.er * tau, hh = Q.er * h;
+        Q.fa = exp(-x);
+        Q.fd = exp(x);
+        const double hs = f64_sinhc(x, Q.fd, Q.fa);
+        Q.fc = -Q.sr * tau * hs;
+        Q.nxx = h * f64_phi(hh);
+        Q.nyy = h * f64_phi(-hh);
+        Q.nxy = -0.5 * Q.sr * h * h * hs * hs;
+        Q.l0x = dp->sys.box[0];
+        Q.l0y = dp->sys.box[1];
+        Q.lz = dp->sys.box[2];
+        Q.il0x = 1.0 / Q.l0x;
+        Q.il0y = 1.0 / Q.l0y;
+        Q.ilz = 1.0 / Q.lz;
+        Q.k0 = dp->k0;
+        Q.root2k0 = sqrt(2.0 * dp->k0);
+        Q.nh_iq = NH ? 1.0 / dp->nh_q : 0.0;
+        Q.nh_target = dp->nh_target;
+        Q.inv_v = 1.0 / dp->sys.volume;
+        Q.rc = dp->sys.rc;
+        Q.rc2 = dp->sys.rc2;
+        Q.ca = dp->sys.c_attr;
+        Q.mu = sqrt(Q.er * Q.er + 0.25 * Q.sr * Q.sr);
+        const double a = fabs(hh) + fabs(Q.sr * h);
+        Q.drift = (1.0 + a + a * a) * (1.0 + 1e-5);  // |N p| <= h |p| e^{|A| h}; FP32 paths
+    }
+    __syncthreads();
+    if (n > T * APT || n > B.nmax || (F == kFlowMixed && !(dp->gamma_dot > 0.0)))
+        health = kHealthNonFinite;
+    int64_t k = dp->k;
+    double zeta = dp->zeta, damp;
+    Cell64 H;
+    H.hxx = uniform(Q.l0x);
+    H.hyy = uniform(Q.l0y);
+    H.hzz = uniform(Q.lz);
+    H.hxy = 0.0;
+    H.ixx = uniform(Q.il0x);
+    H.iyy = uniform(Q.il0y);
+    H.izz = uniform(Q.ilz);
+    f64_cell_at<F, false>(Q, sys, k, 0.0, H, damp);
+    auto narrow = [&]() {  // the host refuses such runs; every lane agrees
+        if constexpr (F == kFlowShear) {
+            return false;
+        } else {
+            const double w3 = 3.0 * Q.rc * (1.0 - 1e-12);
+            const double wx = F == kFlowMixed ? H.hxx * H.hyy * rsq_nr(H.hxy * H.hxy + H.hyy * H.hyy)
+                                              : H.hxx;
+            return !(wx >= w3) || !(H.hyy >= w3) || !(H.hzz >= w3);
+        }
+    };
+    if (narrow()) health = kHealthNonFinite;
+    if (health) {
+        if (t == 0) dp->health = health;
+        return;
+    }
+    double* st = dp->state;
+    GlobalF64* series = (GlobalF64*)dp->series;
+    GlobalF64* xs = F == kFlowMixed ? (GlobalF64*)dp->xseries : nullptr;
+    const bool components = F == kFlowMixed && dp->xseries != nullptr;
+
+    double px[APT], py[APT], pz[APT], fx[APT], fy[APT], fz[APT];
+    float path[APT];
+    int nh[APT], longest = 0;
+    uint16_t atom[APT];  // the state's atom behind the thread's atom j
+    List64 L;
+    L.no_skin = false;
+    double w0, w1 = 0.0;
+    // a coordinate of the state as the kernel holds it
+    auto stored = [&](double& x, double& y, double& z) {
+        if constexpr (F == kFlowElong) {
+            x /= H.hxx;
+            y /= H.hyy;
+            z /= H.hzz;
+        } else if constexpr (F == kFlowMixed) {
+            y /= H.hyy;
+            x = (x - H.hxy * y) / H.hxx;
+            z /= H.hzz;
+        }
+    };
+    {
+        // deal the atoms to the threads in cell order
+        double x[APT], y[APT], z[APT];
+#pragma unroll
+        for (int j = 0; j < APT; ++j) {
+            const int a = t + j * T;
+            const bool v = a < n;
+            x[j] = v ? st[a] : 0.0;
+            y[j] = v ? st[n + a] : 0.0;
+            z[j] = v ? st[2 * n + a] : 0.0;
+            stored(x[j], y[j], z[j]);
+            if constexpr (F != kFlowShear) {
+                x[j] = f64_frac(x[j]);
+                y[j] = f64_frac(y[j]);
+                z[j] = f64_frac(z[j]);
+            }
+        }
+        const double hxy = f64_tilt<F>(H);
+        const double wx = H.hxx * H.hyy / sqrt(hxy * hxy + H.hyy * H.hyy);
+        const Grid64 g = f64_grid(H, hxy, wx, Q.rc, B.cmax);
+        int place[APT], cell[APT];
+        float cart[APT][3];
+        f64_sort<F, APT>(S, H, g, n, x, y, z, place, cell, cart);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < APT; ++j)
+            if (cell[j] >= 0) S.sid[place[j]] = (uint16_t)(t + j * T);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < APT; ++j) {
+            const int a = t + j * T;
+            atom[j] = a < n ? S.sid[a] : 0;
+        }
+        __syncthreads();  // the build reuses these bytes
+    }
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        const int a = t + j * T;
+        const bool v = a < n;
+        const double* q = st + atom[j];
+        px[j] = v ? q[3 * (size_t)n] : 0.0;
+        py[j] = v ? q[4 * (size_t)n] : 0.0;
+        pz[j] = v ? q[5 * (size_t)n] : 0.0;
+        path[j] = 0.0f;
+        if (v) {
+            double x = q[0], y = q[n], z = q[2 * (size_t)n];
+            stored(x, y, z);
+            S.xy[a] = make_double2(x, y);
+            S.z[a] = z;
+        }
+    }
+    // the recorded series, and for mixed flow its components
+    auto record = [&](int at, const Mom64& q) {
+        double b;
+        if constexpr (F == kFlowShear) {
+            b = q.xy + w0;
+        } else if constexpr (F == kFlowElong) {
+            b = q.xx - q.yy + w0;
+        } else {
+            const double cn = q.xx - q.yy + w0, cxy = q.xy + w1;
+            b = (Q.er * cn + Q.sr * cxy) * Q.irn;
+            if (t == 0 && components) {
+                GlobalF64* row = xs + (size_t)at * kObsCols;
+                row[0] = cn * Q.inv_v;
+                row[1] = cxy * Q.inv_v;
+                for (int c = 2; c < kObsCols; ++c) row[c] = 0.0;
+            }
+        }
+        if (t == 0) series[at] = b;
+        return b;
+    };
+    Mom64 m{};
+    bool fresh = false;
+    int it = -1;  // steps done; -1: the forces and moments of the start state come first
+    for (;;) {
+        const double h = Q.h, tau = 0.5 * h;
+        if (it >= 0) {
+            // ---- first half
+            double s1 = 0.0, isd1 = 1.0, g1 = 1.0;
+            if constexpr (NH) {
+                zeta += tau * (m.pp - Q.nh_target) * Q.nh_iq;
+            } else {
+                const double ipp = rcp_nr(m.pp);
+                f64_flow<F>(m, Q.fa, Q.fc, Q.fd);
+                g1 = rsq_nr(m.pp * ipp);
+                double sd;
+                iso_kick_coeffs(g1 * m.fp * ipp, m.ff * ipp, tau, s1, sd);
+                isd1 = rcp_nr(sd);
+            }
+            // ---- streaming in the cell of step k, then the cell of step k + 1
+            const double ax = H.ixx, ay = H.iyy, az = h * H.izz, axy = H.hxy;
+            f64_cell_at<F, NH>(Q, sys, k + 1, zeta, H, damp);
+            float most = 0.0f;
+#pragma unroll
+            for (int j = 0; j < APT; ++j) {
+                const int a = t + j * T;
+                if constexpr (NH) {
+                    const double qx = px[j] * damp, qy = py[j] * damp;
+                    px[j] = (Q.fa * qx + Q.fc * qy) + tau * fx[j];
+                    py[j] = Q.fd * qy + tau * fy[j];
+                    pz[j] = pz[j] * damp + tau * fz[j];
+                } else {
+                    const double qx = g1 * (Q.fa * px[j] + Q.fc * py[j]);
+                    const double qy = g1 * (Q.fd * py[j]);
+                    const double qz = g1 * pz[j];
+                    px[j] = (qx + fx[j] * s1) * isd1;
+                    py[j] = (qy + fy[j] * s1) * isd1;
+                    pz[j] = (qz + fz[j] * s1) * isd1;
+                }
+                const float ux = (float)px[j], uy = (float)py[j], uz = (float)pz[j];
+                path[j] += (float)h * __builtin_sqrtf(ux * ux + uy * uy + uz * uz);
+                most = fmaxf(most, path[j]);
+                if (a < n) {
+                    double2 r = S.xy[a];
+                    if constexpr (F == kFlowShear) {
+                        r.x += h * px[j] + h * Q.sr * (r.y + tau * py[j]);
+                        r.y += h * py[j];
+                        S.z[a] += h * pz[j];
+                    } else if constexpr (F == kFlowElong) {
+                        r.x += Q.nxx * px[j] * ax;
+                        r.y += Q.nyy * py[j] * ay;
+                        S.z[a] += az * pz[j];
+                    } else {
+                        const double dsy = Q.nyy * py[j] * ay;
+                        r.x += ((Q.nxx * px[j] + Q.nxy * py[j]) - axy * dsy) * ax;
+                        r.y += dsy;
+                        S.z[a] += az * pz[j];
+                    }
+                    S.xy[a] = r;
+                }
+            }
+            k += 1;
+            if (narrow()) {
+                health = kHealthNonFinite;  // uniform: every thread stops here
+                break;
+            }
+            most = wave_max_dpp(most);
+            if ((t & 63) == 63) S.wmax[t >> 6] = most;
+            __syncthreads();
+            most = 0.0f;
+            for (int w = 0; w < (T >> 6); ++w) most = fmaxf(most, S.wmax[w]);
+            fresh = f64_fresh(Q, L, k, most);
+        }
+        if (!fresh) {
+            double x[APT], y[APT], z[APT];
+#pragma unroll
+            for (int j = 0; j < APT; ++j) {
+                const int a = t + j * T;
+                const double2 r = S.xy[a < n ? a : 0];
+                x[j] = r.x;
+                y[j] = r.y;
+                z[j] = S.z[a < n ? a : 0];
+                path[j] = 0.0f;
+            }
+            L.k = k;
+            longest = f64_build<F, APT>(S, H, n, B.cmax, Q.rc, x, y, z, L, nh);
+        }
+        f64_forces<F, APT>(S, H, n, Q.rc2, Q.ca, nh, longest, fx, fy, fz, w0, w1);
+        ++it;
+        double pos = 0.0;
+        if constexpr (F == kFlowShear) {  // carries a non-finite coordinate to the health check
+#pragma unroll
+            for (int j = 0; j < APT; ++j) {
+                const int a = t + j * T;
+                if (a < n) pos += S.xy[a].x + S.xy[a].y + S.z[a];
+            }
+        }
+        bool bad = false, drift = false;
+        if constexpr (NH) {
+            // ---- second half: K E T, then Z on the new sum p.p
+            double v[6] = {0.0, 0.0, 0.0, w0, w1, pos};
+#pragma unroll
+            for (int j = 0; j < APT; ++j) {
+                if (it > 0) {
+                    const double qx = px[j] + tau * fx[j], qy = py[j] + tau * fy[j];
+                    px[j] = (Q.fa * qx + Q.fc * qy) * damp;
+                    py[j] = (Q.fd * qy) * damp;
+                    pz[j] = (pz[j] + tau * fz[j]) * damp;
+                }
+                v[0] += px[j] * px[j] + py[j] * py[j] + pz[j] * pz[j];
+                if constexpr (F != kFlowShear) v[1] += px[j] * px[j] - py[j] * py[j];
+                if constexpr (F != kFlowElong) v[2] += px[j] * py[j];
+            }
+            f64_sum<6, 8>(v, S.red);
+            m.pp = v[0];
+            m.xx = v[1];
+            m.xy = v[2];
+            w0 = v[3];
+            w1 = v[4];
+            pos = v[5];
+            if (it > 0) zeta += tau * (m.pp - Q.nh_target) * Q.nh_iq;
+            bad = !isfinite(zeta);
+        } else {
+            m = f64_moments<F, APT>(px, py, pz, fx, fy, fz, w0, w1, pos, S.red);
+            if (it > 0) {
+                // ---- second half: K E, then the exact K0 rescale
+                const double ipp = rcp_nr(m.pp);
+                double s2, sd;
+                iso_kick_coeffs(m.fp * ipp, m.ff * ipp, tau, s2, sd);
+                const double isd2 = rcp_nr(sd);
+                f64_kick(m, s2, isd2);
+                drift = fabs(m.pp * ipp - 1.0) > 1e-10;
+                f64_flow<F>(m, Q.fa, Q.fc, Q.fd);
+                const double c = Q.root2k0 * rsq_nr(m.pp);
+                f64_scale(m, c);
+#pragma unroll
+                for (int j = 0; j < APT; ++j) {
+                    const double qx = (px[j] + fx[j] * s2) * isd2;
+                    const double qy = (py[j] + fy[j] * s2) * isd2;
+                    const double qz = (pz[j] + fz[j] * s2) * isd2;
+                    px[j] = c * (Q.fa * qx + Q.fc * qy);
+                    py[j] = c * (Q.fd * qy);
+                    pz[j] = c * qz;
+                }
+                bad = !isfinite(c);
+            }
+        }
+        if (it == 0) {
+            if (done0 == 0) {
+                (void)record(0, m);
+                if (t == 0 && (F != kFlowShear || Q.k0 <= 0.0)) {
+                    Q.k0 = 0.5 * m.pp;  // read after the barriers of the first step
+                    Q.root2k0 = sqrt(m.pp);
+                }
+            }
+        } else {
+            const double b = record(done0 + it, m);
+            // uniform: every thread holds the same sums
+            if (!isfinite(b) || (F == kFlowShear && (bad || !isfinite(pos)))) {
+                health |= kHealthNonFinite;
+            } else if (F == kFlowShear && drift) {
+                health |= kHealthDrift;
+            }
+        }
+        if (health != 0 || it == todo) break;
+    }
+    // the state, wrapped, in the coordinates of the current cell
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        const int a = t + j * T;
+        if (a < n) {
+            double2 r = S.xy[a];
+            double z = S.z[a];
+            if constexpr (F == kFlowShear) {
+                const double ny = floor(r.y * H.iyy);
+                r.y = __builtin_fma(-ny, H.hyy, r.y);
+                r.x = wrap1(__builtin_fma(-ny, H.hxy, r.x), H.hxx);
+                if (r.y < 0.0 || r.y >= H.hyy) r.y = 0.0;
+                z = wrap1(z, H.hzz);
+            } else {
+                r.y = f64_frac(r.y);
+                r.x = f64_frac(r.x) * H.hxx;
+                if constexpr (F == kFlowMixed) r.x += H.hxy * r.y;
+                r.y *= H.hyy;
+                z = f64_frac(z) * H.hzz;
+            }
+            double* q = st + atom[j];
+            q[0] = r.x;
+            q[n] = r.y;
+            q[2 * (size_t)n] = z;
+            q[3 * (size_t)n] = px[j];
+            q[4 * (size_t)n] = py[j];
+            q[5 * (size_t)n] = pz[j];
+        }
+    }
+    if (t == 0) {
+        dp->k = k;
+        dp->done = done0 + it;
+        dp->k0 = Q.k0;
+        if (NH) dp->zeta = zeta;
+        dp->health = health;
+    }
+}
+
+// A persistent grid: workgroups take daughters from a queue, largest systems first.
+template <int F, bool NH, int APT>
+__global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4) k_flow64(PefLaunch B) {
+    extern __shared__ __align__(16) char smem[];
+    __shared__ Const64 Q;
+    __shared__ SysDev sys;
+    const F64Lds S = f64_carve(smem, B.nmax, B.cmax, blockDim.x, APT);
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) S.misc[1] = atomicAdd(B.queue, 1);
+        __syncthreads();
+        const int job = __builtin_amdgcn_readfirstlane(S.misc[1]);
+        if (job >= B.n_jobs) return;
+        flow64_job<F, NH, APT>(&B.descs[B.order[job]], B, S, Q, sys);
+    }
+}
+
+// Start states of planar-elongation daughters under their mappings: bit 1 of map exchanges
+// the x and y axes of positions and momenta (the box is cubic), bit 0 reverses the momenta.
+// Mixed-flow daughters (mix): bit 1 exchanges the axes, then bit 0 reflects x
+// (x -> L_x - x, p_x -> -p_x).
+__global__ void k_spawn_pef(const double* states, int32_t n, const int32_t* state_of,
+                            const int32_t* map_of, double* const* dst, int32_t mix, double lx) {
+    const int d = blockIdx.x;
+    const double* src = states + (size_t)state_of[d] * 6 * (size_t)n;
+    double* out = dst[d];
+    const int m = map_of[d];
+    const bool sw = (m & 2) != 0;
+    const bool rev = !mix && (m & 1) != 0;
+    const bool refl = mix && (m & 1) != 0;
+    const double sg = rev ? -1.0 : 1.0;
+    for (int a = threadIdx.x; a < n; a += blockDim.x) {
+        const double x = src[a], y = src[n + a], z = src[2 * n + a];
+        const double px = src[3 * n + a], py = src[4 * n + a], pz = src[5 * n + a];
+        const double xs = sw ? y : x;
+        out[a] = refl ? (xs == 0.0 ? 0.0 : lx - xs) : xs;
+        out[n + a] = sw ? x : y;
+        out[2 * n + a] = z;
+        out[3 * n + a] = (refl ? -1.0 : sg) * (sw ? py : px);
+        out[4 * n + a] = sg * (sw ? px : py);
+        out[5 * n + a] = sg * pz;
+    }
+}
+
+
+}  // namespace
+
+int flow64_list_cap() { return kF64Cap; }
+
+// Neighbours an atom of a uniform fluid has within the list radius.
+double flow64_neighbours(double density, double rc) {
+    const double rl = rc * (1.0 + kF64Skin);
+    return 4.18879020478639 * rl * rl * rl * density;
+}
+
+// Shape of a launch. Atoms per thread: the fewest with which every daughter of the batch is on a
+// CU at once (registers: 16 waves of 128, or 8 of 256 with four atoms; and the LDS): the steps
+// of a daughter are a latency chain that more waves shorten. A batch that fills the chip either
+// way takes four: every wave repeats the step's scalars, so half the waves do it half as often
+// (N = 2048, 1024 daughters x 50 steps: 4.47 ms with two, 4.31 with four).
+bool flow64_shape(int nmax, int cells, int n_jobs, int num_cu, size_t max_lds, Flow64Shape* out) {
+    if (nmax > kPefMaxAtoms) return false;
+    bool found = false;
+    for (int apt = 1; apt <= 4; apt *= 2) {
+        Flow64Shape f{};
+        f.apt = apt;
+        f.threads = ((nmax + apt - 1) / apt + 63) / 64 * 64;
+        if (f.threads > (apt == 4 ? 512 : kMaxThreads)) continue;
+        // half cells beyond the atoms' number gain nothing
+        f.cmax = 2 * cells < nmax + 64 ? (cells < 27 ? 54 : 2 * cells) : nmax + 64;
+        const size_t lds = f64_plan(nmax, f.cmax, f.threads, apt).total + 1024;
+        if (lds > max_lds) continue;
+        const int waves = (apt == 4 ? 8 : 16) / (f.threads / 64), held = (int)(max_lds / lds);
+        int fit = waves < held ? waves : held;
+        if (fit < 1) fit = 1;
+        f.grid = n_jobs < fit * num_cu ? n_jobs : fit * num_cu;
+        *out = f;
+        found = true;
+        if (fit * num_cu >= n_jobs) break;
+    }
+    return found;
+}
+
+// The carried-flow batches taken: a cell grid at r_c fits one workgroup's LDS beside the state
+// (sparser systems are refused).
+size_t pef_grid_bytes(int nmax, int cmax) {
+    return 3 * f64_align(sizeof(double) * (size_t)nmax) + f64_align(sizeof(int32_t) * ((size_t)cmax + 1)) +
+           f64_align(sizeof(int32_t) * (size_t)cmax) + f64_align(sizeof(uint16_t) * (size_t)nmax) +
+           sizeof(double) * (kMaxWaves * kRedSlots + kRedSlots) + 64 +
+           sizeof(uint16_t) * kF64Cap * kMaxThreads;
+}
+
+int pef_max_cells(double volume, double rc) {
+    return (int)floor(volume / (rc * rc * rc));
+}
+
+namespace {
+template <int F, bool NH, int APT>
+hipError_t launch_flow64_t(const PefLaunch& L, hipStream_t s) {
+    const size_t lds = f64_plan(L.nmax, L.cmax, L.threads, APT).total;
+    (void)hipFuncSetAttribute((const void*)k_flow64<F, NH, APT>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((k_flow64<F, NH, APT>), dim3(L.grid), dim3(L.threads), lds, s, L);
+    return hipGetLastError();
+}
+
+template <int F, bool NH>
+hipError_t launch_flow64_a(const PefLaunch& L, hipStream_t s) {
+    switch (L.apt) {
+        case 1: return launch_flow64_t<F, NH, 1>(L, s);
+        case 2: return launch_flow64_t<F, NH, 2>(L, s);
+        case 4: return launch_flow64_t<F, NH, 4>(L, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int F>
+hipError_t launch_flow64_f(const PefLaunch& L, hipStream_t s) {
+    return L.thermo ? launch_flow64_a<F, true>(L, s) : launch_flow64_a<F, false>(L, s);
+}
+}  // namespace
+
+hipError_t launch_flow64(const PefLaunch& L, hipStream_t s) {
+    if (L.n_jobs <= 0) return hipSuccess;
+    if (L.threads < 64 || L.threads > (L.apt == 4 ? 512 : kMaxThreads) || L.threads % 64 != 0 ||
+        L.nmax > L.threads * L.apt || L.nmax > kPefMaxAtoms || L.cmax < 54 || L.grid < 1)
+        return hipErrorInvalidValue;
+    const hipError_t e = launch_zero_int(L.queue, s);
+    if (e != hipSuccess) return e;
+    switch (L.flow) {
+        case 0: return launch_flow64_f<kFlowShear>(L, s);
+        case 1: return launch_flow64_f<kFlowElong>(L, s);
+        case 2: return launch_flow64_f<kFlowMixed>(L, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_spawn_pef(const double* states, int32_t n, const int32_t* state_of,
+                            const int32_t* map_of, double* const* dst, int32_t n_daughters,
+                            int32_t mix, double lx, hipStream_t s) {
+    if (n_daughters <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_spawn_pef, dim3(n_daughters), dim3(256), 0, s, states, n, state_of,
+                       map_of, dst, mix, lx);
+    return hipGetLastError();
+}
+
+}  // namespace ttcf

@@ -11,7 +11,7 @@ constexpr int kMaxWaves = kMaxThreads / 64;
 constexpr int kRedSlots = 12;       // doubles reduced per block reduction
 constexpr int kMaxCells1D = 1023;   // packed cell coordinates use 10 bits each
 constexpr int kMaxAtoms = 65535;    // sorted atom ids are stored as uint16
-constexpr int kPefMaxAtoms = 2048;  // planar-elongation daughters: two atoms per thread
+constexpr int kPefMaxAtoms = 2048;  // FP64 list form (ttcf_flow64.hip): two atoms per thread
 
 // Constants of one simulated system, uniform inside a workgroup.
 struct SysDev {
@@ -125,6 +125,7 @@ struct BatchLaunch {
     int32_t thermo;        // daughter thermostat of every job (0 isokinetic, 1 Nose-Hoover)
     int32_t obs;           // 1: some job records the extra observables (list form only)
     int32_t field;         // 1: some job is a colour-field daughter (list form)
+    int32_t flow64;        // cell form: 1 to run the FP64 list kernel (ttcf_flow64.hip) instead
     int32_t pairs_lds;     // pair-list form: 1 if each job's pair words live in LDS after its
                            // layout (lds_bytes covers lds_bytes_pairs_lds of every job)
     uint32_t* pairs;       // pair-list form otherwise: grid x pair_stride pair words
@@ -132,20 +133,25 @@ struct BatchLaunch {
     size_t lds_bytes;
 };
 
-// Planar-elongation daughters (ttcf_elongation.hip): one workgroup per job, two atoms per
-// thread, FP64 forces over a cell grid rebuilt every step from the deformed box; one launch
-// per daughter thermostat.
+// Daughters with FP64 forces over neighbour lists (ttcf_flow64.hip): planar elongation, mixed flow,
+// and shear where its lists fit; one launch per flow and daughter
+// thermostat.
+struct Flow64Shape {
+    int32_t apt;           // atoms per thread: 1, 2 or 4
+    int32_t threads;       // workgroup size
+    int32_t grid;          // workgroups (persistent)
+    int32_t cmax;          // list-build cells at most (54 or more)
+};
 struct PefLaunch {
     DaughterDesc* descs;   // device array
     const int32_t* order;  // device: desc index of each job
     int32_t n_jobs;
     int32_t max_steps;     // steps this call (each daughter stops at its own N_d)
-    int32_t threads;       // pef_threads(nmax)
+    int32_t* queue;        // device counter (zeroed by the launcher)
+    int32_t threads, apt, grid, cmax;  // flow64_shape of the largest system
     int32_t nmax;          // largest system
-    int32_t cmax;          // >= the cell count of any job's box at any step
     int32_t thermo;        // daughter thermostat of every job (0 isokinetic, 1 Nose-Hoover)
-    int32_t mix;           // 1: mixed-flow daughters (k_daughters_mix)
-    size_t lds_bytes;      // lds_bytes_pef(nmax, cmax)
+    int32_t flow;          // 0 shear, 1 planar elongation, 2 mixed flow
 };
 
 struct MotherLaunch {
@@ -287,6 +293,7 @@ hipError_t launch_debug_pair_form(const SysDev& S, double gamma_dot, int64_t kst
                                   int32_t* cell_of, int32_t* rank_of, int32_t* start, double* f,
                                   double* out, hipStream_t s);
 
+hipError_t launch_zero_int(int32_t* p, hipStream_t s);
 hipError_t launch_daughters(const BatchLaunch& b, hipStream_t s);
 hipError_t launch_mothers(const MotherLaunch* dev_ms, int count, const MotherLaunch& shape,
                           hipStream_t s);
@@ -334,10 +341,14 @@ hipError_t launch_accumulate_obs(const AccumObsLaunch& a, hipStream_t s);
 // *counter += 1 (one thread)
 hipError_t launch_increment(int32_t* counter, hipStream_t s);
 hipError_t launch_response(const ResponseLaunch& r, hipStream_t s);
-int pef_threads(int nmax);
+// shape of a launch over n_jobs daughters of up to nmax atoms and `cells` r_c cells; false when
+// no workgroup holds the largest
+bool flow64_shape(int nmax, int cells, int n_jobs, int num_cu, size_t max_lds, Flow64Shape* out);
+int flow64_list_cap();  // neighbours a list holds
+double flow64_neighbours(double density, double rc);
 int pef_max_cells(double volume, double rc);
-size_t lds_bytes_pef(int nmax, int cmax);
-hipError_t launch_pef(const PefLaunch& L, hipStream_t s);
+size_t pef_grid_bytes(int nmax, int cmax);
+hipError_t launch_flow64(const PefLaunch& L, hipStream_t s);
 hipError_t launch_spawn_pef(const double* states, int32_t n, const int32_t* state_of,
                             const int32_t* map_of, double* const* dst, int32_t n_daughters,
                             int32_t mix, double lx, hipStream_t s);

@@ -1201,7 +1201,28 @@ static hipError_t launch_daughters_r(const BatchLaunch& b, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_zero_int(int32_t* p, hipStream_t s) {
+    hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, p, 1);
+    return hipGetLastError();
+}
+
 hipError_t launch_daughters(const BatchLaunch& b, hipStream_t s) {
+    if (b.flow64) {
+        PefLaunch L{};
+        L.descs = b.descs;
+        L.order = b.order;
+        L.n_jobs = b.n_jobs;
+        L.max_steps = b.max_steps;
+        L.queue = b.queue;
+        L.threads = b.threads;
+        L.apt = b.apt;
+        L.grid = b.grid;
+        L.cmax = b.cmax;
+        L.nmax = b.nmax;
+        L.thermo = b.thermo;
+        L.flow = 0;
+        return launch_flow64(L, s);
+    }
     hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, b.queue, 1);
     // one instantiation per daughter thermostat: the isokinetic build does not carry the
     // Nose-Hoover branch's registers (10% on the list form)

@@ -221,75 +221,6 @@ __device__ __forceinline__ void iso_kick_coeffs_tab(double a, double b, double t
     sdot = a * sh_q + (1.0 + b * ch1_b);
 }
 
-// 1/x to about an ulp for x of normal size: the hardware reciprocal and two Newton steps
-// (the step's scalars are one dependent chain that every wave waits on, so the short chain
-// pays where a correctly rounded division would not).
-__device__ __forceinline__ double rcp_nr(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = __builtin_fma(-x, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    e = __builtin_fma(-x, r, 1.0);
-    return __builtin_fma(r, e, r);
-}
-
-// 1/sqrt(x) to about an ulp for positive x of normal size: the hardware estimate and two
-// Newton steps y <- y (1 + (1 - x y^2) / 2).
-__device__ __forceinline__ double rsq_nr(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const double e = __builtin_fma(-(x * y), y, 1.0);
-        y = __builtin_fma(0.5 * y, e, y);
-    }
-    return y;
-}
-
-// le_offset without branches (the same value: the remainder of |v| by L_x is exact whichever
-// of the neighbouring multiples the estimate q lands on, and the fused multiply-adds
-// compute it from q - 1, q or q + 1 exactly); ilx = 1 / L_x.
-__device__ __forceinline__ double le_offset_nb(const SysDev& S, double gamma_dot, int64_t k,
-                                               double ilx) {
-    const double v = gamma_dot * S.box[1] * ((double)k * S.dt);
-    const double lx = S.box[0];
-    const double av = fabs(v);
-    const double q = floor(av * ilx);
-    const double r0 = __builtin_fma(-lx, q, av);
-    const double rm = __builtin_fma(-lx, q - 1.0, av);
-    const double rp = __builtin_fma(-lx, q + 1.0, av);
-    const double r = r0 < 0.0 ? rm : (r0 >= lx ? rp : r0);
-    const double sr = v < 0.0 ? -r : r;
-    return av < lx ? v : sr;
-}
-
-// One DPP move of a double from the lane the control selects (every lane has a source).
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo =
-        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
-    const uint32_t hi =
-        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// The value of lane ^ D (D = 16: lanes of rows 0 and 2; D = 32: lanes 0..31) from gfx950's
-// row and half swaps (the second result of a swap of x with itself holds, in those lanes, the
-// other row's or half's values).
-template <int D>
-__device__ __forceinline__ double swap_partner(double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
-    uint32_t plo, phi;
-    if constexpr (D == 16) {
-        plo = __builtin_amdgcn_permlane16_swap(lo, lo, false, false)[1];
-        phi = __builtin_amdgcn_permlane16_swap(hi, hi, false, false)[1];
-    } else {
-        plo = __builtin_amdgcn_permlane32_swap(lo, lo, false, false)[1];
-        phi = __builtin_amdgcn_permlane32_swap(hi, hi, false, false)[1];
-    }
-    return __builtin_bit_cast(double, ((uint64_t)phi << 32) | plo);
-}
-
 // Sum of red[w kPfRed] over waves w = 0..nw-1 in that order, the loads issued together (a
 // wave past nw adds an exact zero).
 __device__ __forceinline__ double waves_sum(const double* red, int nw) {
@@ -300,20 +231,6 @@ __device__ __forceinline__ double waves_sum(const double* red, int nw) {
 #pragma unroll
     for (int w = 0; w < kPairThreads / 64; ++w) s += v[w];
     return s;
-}
-
-// One stage of a transposed reduction: a lane with `upper` set keeps a[H..2H) and hands
-// a[0..H) to the lane the control selects, the others keep a[0..H) and hand a[H..2H); the
-// kept half adds what arrives. The control must pair every lane with one of the other kind
-// holding the same value subsets (an exchange, or a rotation that flips one lane bit).
-template <int H, int CTRL>
-__device__ __forceinline__ void xstage(double* a, bool upper) {
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-        const double keep = upper ? a[H + i] : a[i];
-        const double send = upper ? a[i] : a[H + i];
-        a[i] = keep + dpp_move<CTRL>(send);
-    }
 }
 
 // The 12-value sum of the step over the first nw waves; every thread receives the totals.
