@@ -756,12 +756,10 @@ int32_t ttcf_import_states(ttcf_ctx* c, int32_t mother, int32_t n_states, const 
         m.states_cap = n_states;
     }
     HIPCHECK(c, launch_fill_f64(zetas_of(m), 0.0, n_states, c->stream));
-    for (int32_t s = 0; s < n_states; ++s) {
-        HIPCHECK(c, hipMemcpyAsync(m.states + 6 * n * s, r + 3 * n * s, sizeof(double) * 3 * n,
-                                   hipMemcpyHostToDevice, c->stream));
-        HIPCHECK(c, hipMemcpyAsync(m.states + 6 * n * s + 3 * n, p + 3 * n * s,
-                                   sizeof(double) * 3 * n, hipMemcpyHostToDevice, c->stream));
-    }
+    const size_t w = sizeof(double) * 3 * n;
+    HIPCHECK(c, copy_rows((void*)r, m.states, 2 * w, w, n_states, hipMemcpyHostToDevice, c->stream));
+    HIPCHECK(c, copy_rows((void*)p, m.states + 3 * n, 2 * w, w, n_states, hipMemcpyHostToDevice,
+                          c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     m.n_states = n_states;
     return TTCF_OK;
@@ -772,14 +770,11 @@ int32_t ttcf_export_states(ttcf_ctx* c, int32_t mother, int32_t n_states, double
     Mother& m = c->mothers[mother];
     if (n_states > m.n_states) return fail(c, TTCF_EINVAL, "fewer stored states than requested");
     const size_t n = (size_t)m.dev.n;
-    for (int32_t s = 0; s < n_states; ++s) {
-        if (r)
-            HIPCHECK(c, hipMemcpyAsync(r + 3 * n * s, m.states + 6 * n * s, sizeof(double) * 3 * n,
-                                       hipMemcpyDeviceToHost, c->stream));
-        if (p)
-            HIPCHECK(c, hipMemcpyAsync(p + 3 * n * s, m.states + 6 * n * s + 3 * n,
-                                       sizeof(double) * 3 * n, hipMemcpyDeviceToHost, c->stream));
-    }
+    const size_t w = sizeof(double) * 3 * n;
+    if (r)
+        HIPCHECK(c, copy_rows(r, m.states, 2 * w, w, n_states, hipMemcpyDeviceToHost, c->stream));
+    if (p)
+        HIPCHECK(c, copy_rows(p, m.states + 3 * n, 2 * w, w, n_states, hipMemcpyDeviceToHost, c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     return TTCF_OK;
 }
@@ -2560,21 +2555,56 @@ static int32_t find_live(ttcf_ctx* c, int64_t id) {
     return (int32_t)(it - c->live.begin());
 }
 
+namespace {
+// One live daughter's series (or extra-observable series) and the batch whose block holds it.
+struct SeriesRow {
+    const double* data;
+    int32_t batch;
+};
+
+// Copies the first n_t points (`cols` values each) of the rows to the host, one copy per run of a
+// batch's daughters (their series are equally long and consecutive).
+int32_t export_rows(ttcf_ctx* c, const std::vector<SeriesRow>& src, int32_t n_t, int cols,
+                    double* out) {
+    const size_t width = sizeof(double) * (size_t)n_t * cols;
+    for (size_t q = 0; q < src.size();) {
+        const size_t pitch = sizeof(double) * (size_t)(c->batches[src[q].batch].n_steps + 1) * cols;
+        size_t e = q + 1;
+        while (e < src.size() && src[e].batch == src[q].batch &&
+               (const char*)src[e].data == (const char*)src[e - 1].data + pitch)
+            ++e;
+        HIPCHECK(c, copy_rows((char*)out + q * width, (void*)src[q].data, pitch, width, e - q,
+                              hipMemcpyDeviceToHost, c->stream));
+        q = e;
+    }
+    return TTCF_OK;
+}
+
+// Index of the live daughter `id`, looked for at `i` (its predecessor's) and after it first.
+int32_t next_live(ttcf_ctx* c, int32_t i, int64_t id) {
+    for (int32_t k = i; i >= 0 && k <= i + 1 && k < (int32_t)c->live.size(); ++k)
+        if (c->live[k].id == id) return k;
+    return find_live(c, id);
+}
+}  // namespace
+
 int32_t ttcf_export_observables(ttcf_ctx* c, int64_t first, int32_t count, int32_t n_t,
                                 double* out) {
     if (!c || count <= 0 || n_t <= 0 || !out) return TTCF_EINVAL;
     int32_t rc = sync_descs(c);
     if (rc != TTCF_OK) return rc;
+    std::vector<SeriesRow> src(count);
+    int32_t i = find_live(c, first);
     for (int32_t q = 0; q < count; ++q) {
-        const int32_t i = find_live(c, first + q);
+        i = next_live(c, i, first + q);
         if (i < 0) return fail(c, TTCF_EINVAL, "no live daughter with that id");
         const DaughterDesc& d = c->descs[i];
         if (!d.xseries) return fail(c, TTCF_ESTATE, "that daughter does not record them");
         if (n_t > d.n_steps + 1) return fail(c, TTCF_EINVAL, "n_t exceeds the daughter's length");
-        HIPCHECK(c, hipMemcpyAsync(out + (size_t)q * n_t * kObsCols, d.xseries,
-                                   sizeof(double) * (size_t)n_t * kObsCols, hipMemcpyDeviceToHost,
-                                   c->stream));
+        src[q] = SeriesRow{d.xseries, c->live[i].batch};
     }
+    rc = export_rows(c, src, n_t, kObsCols, out);
+    if (rc != TTCF_OK) return rc;
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     return TTCF_OK;
 }
@@ -2600,14 +2630,17 @@ int32_t ttcf_export_series(ttcf_ctx* c, int64_t first, int32_t count, int32_t n_
     if (!c || count <= 0 || n_t <= 0 || !vpxy) return TTCF_EINVAL;
     int32_t rc = sync_descs(c);
     if (rc != TTCF_OK) return rc;
+    std::vector<SeriesRow> src(count);
+    int32_t i = find_live(c, first);
     for (int32_t q = 0; q < count; ++q) {
-        const int32_t i = find_live(c, first + q);
+        i = next_live(c, i, first + q);
         if (i < 0) return fail(c, TTCF_EINVAL, "no such live daughter");
         const DaughterDesc& d = c->descs[i];
         if (n_t > d.n_steps + 1) return fail(c, TTCF_EINVAL, "n_t exceeds the daughter length");
-        HIPCHECK(c, hipMemcpyAsync(vpxy + (size_t)q * n_t, d.series, sizeof(double) * n_t,
-                                   hipMemcpyDeviceToHost, c->stream));
+        src[q] = SeriesRow{d.series, c->live[i].batch};
     }
+    rc = export_rows(c, src, n_t, 1, vpxy);
+    if (rc != TTCF_OK) return rc;
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     return TTCF_OK;
 }

@@ -92,8 +92,4 @@ hipError_t launch_channel_spawn(const double* states, int32_t n, int32_t n_wall,
 hipError_t launch_channel_accumulate(const ChannelAccum& a, hipStream_t s);
 hipError_t launch_channel_response(const ChannelResponse& r, hipStream_t s);
 
-// device memory through the allocator shared with the bulk runtime
-void* rt_alloc(size_t bytes, hipStream_t s);
-void rt_free(void* p);
-
 }  // namespace ttcf

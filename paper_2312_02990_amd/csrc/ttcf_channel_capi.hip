@@ -518,13 +518,11 @@ int32_t ttcf_channel_import_states(ttcf_channel_ctx* c, int32_t n_states, const 
     int32_t rc = grow_states(c, n_states);
     if (rc != TTCF_OK) return rc;
     const size_t n = (size_t)c->dev.n, sz = 6 * n + 1;
-    for (int32_t s = 0; s < n_states; ++s) {
-        double* dst = c->states + sz * s;
-        CHK(c, hipMemcpyAsync(dst, r + 3 * n * s, sizeof(double) * 3 * n, hipMemcpyHostToDevice, c->stream));
-        CHK(c, hipMemcpyAsync(dst + 3 * n, p + 3 * n * s, sizeof(double) * 3 * n, hipMemcpyHostToDevice,
-                              c->stream));
-        CHK(c, hipMemcpyAsync(dst + 6 * n, zeta + s, sizeof(double), hipMemcpyHostToDevice, c->stream));
-    }
+    const size_t w = sizeof(double) * 3 * n, pitch = sizeof(double) * sz;
+    const hipMemcpyKind to = hipMemcpyHostToDevice;
+    CHK(c, copy_rows((void*)r, c->states, pitch, w, n_states, to, c->stream));
+    CHK(c, copy_rows((void*)p, c->states + 3 * n, pitch, w, n_states, to, c->stream));
+    CHK(c, copy_rows((void*)zeta, c->states + 6 * n, pitch, sizeof(double), n_states, to, c->stream));
     CHK(c, hipStreamSynchronize(c->stream));
     c->n_states = n_states;
     return TTCF_OK;
@@ -534,14 +532,12 @@ int32_t ttcf_channel_export_states(ttcf_channel_ctx* c, int32_t n_states, double
                                    double* zeta) {
     if (!c || n_states <= 0 || n_states > c->n_states) return TTCF_EINVAL;
     const size_t n = (size_t)c->dev.n, sz = 6 * n + 1;
-    for (int32_t s = 0; s < n_states; ++s) {
-        const double* src = c->states + sz * s;
-        if (r) CHK(c, hipMemcpyAsync(r + 3 * n * s, src, sizeof(double) * 3 * n, hipMemcpyDeviceToHost, c->stream));
-        if (p)
-            CHK(c, hipMemcpyAsync(p + 3 * n * s, src + 3 * n, sizeof(double) * 3 * n,
-                                  hipMemcpyDeviceToHost, c->stream));
-        if (zeta) CHK(c, hipMemcpyAsync(zeta + s, src + 6 * n, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    }
+    const size_t w = sizeof(double) * 3 * n, pitch = sizeof(double) * sz;
+    const hipMemcpyKind to = hipMemcpyDeviceToHost;
+    if (r) CHK(c, copy_rows(r, c->states, pitch, w, n_states, to, c->stream));
+    if (p) CHK(c, copy_rows(p, c->states + 3 * n, pitch, w, n_states, to, c->stream));
+    if (zeta)
+        CHK(c, copy_rows(zeta, c->states + 6 * n, pitch, sizeof(double), n_states, to, c->stream));
     CHK(c, hipStreamSynchronize(c->stream));
     return TTCF_OK;
 }
@@ -738,7 +734,9 @@ int32_t ttcf_channel_export_series(ttcf_channel_ctx* c, int64_t first, int32_t c
                                    double* obs, double* s0) {
     if (!c || count <= 0 || n_t <= 0) return TTCF_EINVAL;
     const int nobs = 1 + c->dev.n_bins;
-    for (int32_t q = 0; q < count; ++q) {
+    // per run of one batch's daughters: its descriptors once, the (consecutive) series in one copy
+    const size_t width = sizeof(double) * (size_t)n_t * nobs;
+    for (int32_t q = 0; q < count;) {
         int bi = 0, di = 0;
         int32_t rc = find_daughter(c, first + q, &bi, &di);
         if (rc != TTCF_OK) return rc;
@@ -746,10 +744,13 @@ int32_t ttcf_channel_export_series(ttcf_channel_ctx* c, int64_t first, int32_t c
         if (n_t > b.n_steps + 1) return cfail(c, TTCF_EINVAL, "n_t beyond the daughter's length");
         rc = pull_batch(c, b);
         if (rc != TTCF_OK) return rc;
+        const int32_t run = std::min<int32_t>(count - q, b.n_daughters - di);
         if (obs)
-            CHK(c, hipMemcpyAsync(obs + (size_t)q * n_t * nobs, b.descs[di].series,
-                                  sizeof(double) * (size_t)n_t * nobs, hipMemcpyDeviceToHost, c->stream));
-        if (s0) s0[q] = b.descs[di].s0;
+            CHK(c, copy_rows(obs + (size_t)q * n_t * nobs, b.descs[di].series,
+                             sizeof(double) * (size_t)(b.n_steps + 1) * nobs, width, run,
+                             hipMemcpyDeviceToHost, c->stream));
+        for (int32_t e = 0; s0 && e < run; ++e) s0[q + e] = b.descs[di + e].s0;
+        q += run;
     }
     CHK(c, hipStreamSynchronize(c->stream));
     return TTCF_OK;

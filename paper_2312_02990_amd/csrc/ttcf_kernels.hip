@@ -1294,6 +1294,19 @@ __global__ void k_copy_words(const uint64_t* src, uint64_t* dst, int64_t count) 
         dst[i] = src[i];
 }
 
+// packed row r <-> words r * pitch .. of rows (64-bit words)
+__global__ void k_pack_rows(uint64_t* rows, int64_t pitch, uint64_t* packed, int64_t width,
+                            int64_t count, int unpack) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        uint64_t* at = rows + (i / width) * pitch + i % width;
+        if (unpack)
+            *at = packed[i];
+        else
+            packed[i] = *at;
+    }
+}
+
 __global__ void k_desc_zeta(DaughterDesc* descs, const double* zeta, const int32_t* state_of,
                             const int32_t* map_of, int32_t count) {
     const int d = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1379,6 +1392,31 @@ hipError_t launch_copy_words(const uint64_t* src, uint64_t* dst, int64_t count, 
     const int64_t blocks = want < 1024 ? want : 1024;
     hipLaunchKernelGGL(k_copy_words, dim3((unsigned)blocks), dim3(256), 0, s, src, dst, count);
     return hipGetLastError();
+}
+
+hipError_t copy_rows(void* host, void* dev, size_t pitch, size_t width, size_t rows, hipMemcpyKind kind,
+                     hipStream_t s) {
+    if (rows == 0 || width == 0) return hipSuccess;
+    const bool up = kind == hipMemcpyHostToDevice;
+    if (rows == 1 || pitch == width)
+        return hipMemcpyAsync(up ? dev : host, up ? host : dev, width * rows, kind, s);
+    void* packed = rt_alloc(width * rows, s);
+    if (!packed)
+        return hipMemcpy2DAsync(up ? dev : host, up ? pitch : width, up ? host : dev,
+                                up ? width : pitch, width, rows, kind, s);
+    const int64_t words = (int64_t)(width / 8), count = words * (int64_t)rows;
+    const int64_t want = (count + 255) / 256;
+    const unsigned blocks = (unsigned)(want < 4096 ? want : 4096);
+    hipError_t e = hipSuccess;
+    if (up) e = hipMemcpyAsync(packed, host, width * rows, kind, s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_pack_rows, dim3(blocks), dim3(256), 0, s, (uint64_t*)dev,
+                           (int64_t)(pitch / 8), (uint64_t*)packed, words, count, up ? 1 : 0);
+        e = hipGetLastError();
+    }
+    if (!up && e == hipSuccess) e = hipMemcpyAsync(host, packed, width * rows, kind, s);
+    rt_free(packed);
+    return e;
 }
 
 hipError_t launch_increment(int32_t* counter, hipStream_t s) {
