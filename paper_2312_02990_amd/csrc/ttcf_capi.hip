@@ -2794,7 +2794,6 @@ CvLayout cv_layout(int n_out) {
 // Scratch of one forward/backward pass over `rows` samples.
 struct CvWork {
     float *x, *t, *z1, *a1, *z2, *a2, *y, *dy, *dz2, *dz1;
-    double* loss;
     void* base = nullptr;
 };
 
@@ -2814,7 +2813,6 @@ int32_t cv_work_alloc(ttcf_ctx* c, int rows, CvWork* w) {
     w->dy = p; p += (size_t)rows * O;
     w->dz2 = p; p += (size_t)rows * H;
     w->dz1 = p; p += (size_t)rows * H;
-    w->loss = (double*)(((uintptr_t)p + 15) & ~(uintptr_t)15);
     return TTCF_OK;
 }
 
@@ -2841,35 +2839,49 @@ GemmArgs gemm(const float* A, int64_t sam, int64_t sak, const float* B, int64_t 
 }
 
 // y = W3 gelu(W2 gelu(W1 x + b1) + b2) + b3 for w.x (rows x kCvIn)
-int32_t cv_forward(ttcf_ctx* c, const float* P, CvWork& w, int rows) {
+// Forward pass; with `grad`, also w.dy = d(mean squared error)/dy against w.t.
+int32_t cv_forward(ttcf_ctx* c, const float* P, CvWork& w, int rows, bool grad = false) {
     const int H = kCvHidden, O = c->cv_out;
     const CvLayout l = cv_layout(O);
-    HIPCHECK(c, launch_gemm(gemm(w.x, kCvIn, 1, P + l.w1, H, 1, w.a1, H, rows, H, kCvIn, 1, P + l.b1, w.z1),
-                            c->stream));
-    HIPCHECK(c, launch_gemm(gemm(w.a1, H, 1, P + l.w2, H, 1, w.a2, H, rows, H, H, 1, P + l.b2, w.z2),
-                            c->stream));
-    HIPCHECK(c, launch_gemm(gemm(w.a2, H, 1, P + l.w3, O, 1, w.y, O, rows, O, H, 0, P + l.b3),
-                            c->stream));
+    const GemmArgs one = gemm(w.x, kCvIn, 1, P + l.w1, H, 1, w.a1, H, rows, H, kCvIn, 1, P + l.b1, w.z1);
+    const GemmArgs two = gemm(w.a1, H, 1, P + l.w2, H, 1, w.a2, H, rows, H, H, 1, P + l.b2, w.z2);
+    GemmArgs three = gemm(w.a2, H, 1, P + l.w3, O, 1, w.y, O, rows, O, H, grad ? 3 : 0, P + l.b3,
+                          grad ? w.dy : nullptr, grad ? w.t : nullptr);
+    three.scale = 2.0f / (float)((int64_t)rows * O);
+    HIPCHECK(c, launch_gemms(&one, 1, c->stream));
+    HIPCHECK(c, launch_gemms(&two, 1, c->stream));
+    HIPCHECK(c, launch_gemms(&three, 1, c->stream));
     return TTCF_OK;
 }
 
-// gradient of mean((y - t)^2) over every element into G
+// Gradients from w.dy: per layer the weights', the biases' (column sums) and the next dz in one
+// launch.
 int32_t cv_backward(ttcf_ctx* c, const float* P, float* G, CvWork& w, int rows) {
     const int H = kCvHidden, O = c->cv_out;
     const CvLayout l = cv_layout(O);
-    const int64_t cnt = (int64_t)rows * O;
-    HIPCHECK(c, launch_mse_grad(w.y, w.t, cnt, 2.0f / (float)cnt, w.dy, c->stream));
-    // W3: a2^T dy; b3: column sums of dy; dz2 = (dy W3^T) gelu'(z2)
-    HIPCHECK(c, launch_gemm(gemm(w.a2, 1, H, w.dy, O, 1, G + l.w3, O, H, O, rows, 0), c->stream));
-    HIPCHECK(c, launch_colsum(w.dy, rows, O, O, G + l.b3, c->stream));
-    HIPCHECK(c, launch_gemm(gemm(w.dy, O, 1, P + l.w3, 1, O, w.dz2, H, rows, H, O, 2, nullptr, nullptr, w.z2),
-                            c->stream));
-    HIPCHECK(c, launch_gemm(gemm(w.a1, 1, H, w.dz2, H, 1, G + l.w2, H, H, H, rows, 0), c->stream));
-    HIPCHECK(c, launch_colsum(w.dz2, rows, H, H, G + l.b2, c->stream));
-    HIPCHECK(c, launch_gemm(gemm(w.dz2, H, 1, P + l.w2, 1, H, w.dz1, H, rows, H, H, 2, nullptr, nullptr, w.z1),
-                            c->stream));
-    HIPCHECK(c, launch_gemm(gemm(w.x, 1, kCvIn, w.dz1, H, 1, G + l.w1, H, kCvIn, H, rows, 0), c->stream));
-    HIPCHECK(c, launch_colsum(w.dz1, rows, H, H, G + l.b1, c->stream));
+    auto bias = [&](const float* dz, int n, float* out) {
+        GemmArgs g{};
+        g.A = dz;
+        g.sam = n;
+        g.C = out;
+        g.M = rows;
+        g.N = n;
+        g.epi = kEpiColsum;
+        return g;
+    };
+    const GemmArgs three[3] = {
+        gemm(w.a2, 1, H, w.dy, O, 1, G + l.w3, O, H, O, rows, 0),
+        gemm(w.dy, O, 1, P + l.w3, 1, O, w.dz2, H, rows, H, O, 2, nullptr, nullptr, w.z2),
+        bias(w.dy, O, G + l.b3)};
+    const GemmArgs two[3] = {
+        gemm(w.a1, 1, H, w.dz2, H, 1, G + l.w2, H, H, H, rows, 0),
+        gemm(w.dz2, H, 1, P + l.w2, 1, H, w.dz1, H, rows, H, H, 2, nullptr, nullptr, w.z1),
+        bias(w.dz2, H, G + l.b2)};
+    const GemmArgs one[2] = {gemm(w.x, 1, kCvIn, w.dz1, H, 1, G + l.w1, H, kCvIn, H, rows, 0),
+                             bias(w.dz1, H, G + l.b1)};
+    HIPCHECK(c, launch_gemms(three, 3, c->stream));
+    HIPCHECK(c, launch_gemms(two, 3, c->stream));
+    HIPCHECK(c, launch_gemms(one, 2, c->stream));
     return TTCF_OK;
 }
 
@@ -2943,8 +2955,8 @@ int32_t cv_predict_h(ttcf_ctx* c, const float* d_feat, const double* d_b0, const
     if (rc != TTCF_OK) return rc;
     for (int r0 = 0; r0 < rows; r0 += chunk) {
         const int nr = std::min(chunk, rows - r0);
-        HIPCHECK(c, launch_gather_norm(d_feat + (size_t)r0 * kCvIn, nullptr, nr, kCvIn, xs, xs + kCvIn,
-                                       w.x, c->stream));
+        const GatherArgs gx{d_feat + (size_t)r0 * kCvIn, kCvIn, xs, xs + kCvIn, w.x};
+        HIPCHECK(c, launch_gather_norm(gx, GatherArgs{}, nullptr, nr, c->stream));
         rc = cv_forward(c, c->cv_p, w, nr);
         if (rc != TTCF_OK) return rc;
         HIPCHECK(c, launch_cv_h(w.y, nr, O, ys, ys + O, d_b0 + r0, d_om + r0, dt,
@@ -3034,7 +3046,7 @@ int32_t ttcf_mlp_gradient(ttcf_ctx* c, const float* x, const float* target, int3
     HIPCHECK(c, hipMemcpyAsync(w.x, x, sizeof(float) * rows * kCvIn, hipMemcpyHostToDevice, c->stream));
     HIPCHECK(c, hipMemcpyAsync(w.t, target, sizeof(float) * rows * c->cv_out, hipMemcpyHostToDevice,
                                c->stream));
-    rc = cv_forward(c, c->cv_p, w, rows);
+    rc = cv_forward(c, c->cv_p, w, rows, true);
     if (rc == TTCF_OK) rc = cv_backward(c, c->cv_p, c->cv_g, w, rows);
     if (rc != TTCF_OK) return rc;
     HIPCHECK(c, hipMemcpyAsync(grad, c->cv_g, sizeof(float) * c->cv_nparam, hipMemcpyDeviceToHost,
@@ -3117,37 +3129,48 @@ int32_t ttcf_cv_train(ttcf_ctx* c, int32_t epochs, int32_t batch, double lr, con
     CvWork w;
     rc = cv_work_alloc(c, batch, &w);
     if (rc != TTCF_OK) return rc;
-    int32_t* d_idx = (int32_t*)dev_alloc(sizeof(int32_t) * n, c->stream);
-    if (!d_idx) return fail(c, TTCF_ENOMEM, "index allocation failed");
+    // the row order of as many epochs as fit a bounded buffer goes up at once, and the losses come
+    // back at the end, so that the steps queue without waiting for the host
+    const int64_t steps = n / batch;
+    const int32_t held = order ? (int32_t)std::max<int64_t>(1, std::min<int64_t>(epochs, (16 << 20) / n)) : 1;
+    Scratch sc(c->stream);
+    int32_t* d_idx = sc.get<int32_t>((size_t)held * (size_t)n);
+    double* d_loss = sc.get<double>((size_t)std::max(epochs, 1));
+    if (!d_idx || !d_loss) {
+        dev_free(w.base);
+        return fail(c, TTCF_ENOMEM, "index allocation failed");
+    }
     std::vector<int32_t> nat;
     if (!order) {
         nat.resize(n);
         for (int64_t q = 0; q < n; ++q) nat[q] = (int32_t)q;
     }
-    const int64_t steps = n / batch;
+    const GatherArgs gx{c->cv_x, kCvIn, xs, xs + kCvIn, w.x}, gt{c->cv_t, O, ys, ys + O, w.t};
     for (int32_t e = 0; e < epochs; ++e) {
-        const int32_t* ord = order ? order + (int64_t)e * n : nat.data();
-        HIPCHECK(c, hipMemcpyAsync(d_idx, ord, sizeof(int32_t) * n, hipMemcpyHostToDevice, c->stream));
-        HIPCHECK(c, hipStreamSynchronize(c->stream));
+        if (order ? e % held == 0 : e == 0) {
+            const int32_t count = order ? std::min(held, epochs - e) : 1;
+            const int32_t* ord = order ? order + (int64_t)e * n : nat.data();
+            HIPCHECK(c, hipMemcpyAsync(d_idx, ord, sizeof(int32_t) * n * count, hipMemcpyHostToDevice,
+                                       c->stream));
+            HIPCHECK(c, hipStreamSynchronize(c->stream));
+        }
+        const int32_t* ei = d_idx + (order ? (int64_t)(e % held) * n : 0);
         for (int64_t s = 0; s < steps; ++s) {
-            const int32_t* bi = d_idx + s * batch;
-            HIPCHECK(c, launch_gather_norm(c->cv_x, bi, batch, kCvIn, xs, xs + kCvIn, w.x, c->stream));
-            HIPCHECK(c, launch_gather_norm(c->cv_t, bi, batch, O, ys, ys + O, w.t, c->stream));
-            rc = cv_forward(c, c->cv_p, w, batch);
+            HIPCHECK(c, launch_gather_norm(gx, gt, ei + s * batch, batch, c->stream));
+            rc = cv_forward(c, c->cv_p, w, batch, true);
             if (rc == TTCF_OK) rc = cv_backward(c, c->cv_p, c->cv_g, w, batch);
             if (rc != TTCF_OK) return rc;
             c->cv_adam_steps += 1;
             HIPCHECK(c, launch_adam(c->cv_p, c->cv_g, c->cv_m, c->cv_v, c->cv_nparam, (float)lr,
                                     c->cv_adam_steps, c->stream));
-            if (s == steps - 1 && loss_out) {
-                HIPCHECK(c, launch_mse_loss(w.y, w.t, (int64_t)batch * O, w.loss, c->stream));
-                HIPCHECK(c, hipMemcpyAsync(loss_out + e, w.loss, sizeof(double), hipMemcpyDeviceToHost,
-                                           c->stream));
-            }
+            if (s == steps - 1 && loss_out)
+                HIPCHECK(c, launch_mse_loss(w.y, w.t, (int64_t)batch * O, d_loss + e, c->stream));
         }
     }
+    if (loss_out && epochs > 0)
+        HIPCHECK(c, hipMemcpyAsync(loss_out, d_loss, sizeof(double) * epochs, hipMemcpyDeviceToHost,
+                                   c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
-    dev_free(d_idx);
     dev_free(w.base);
     return TTCF_OK;
 }

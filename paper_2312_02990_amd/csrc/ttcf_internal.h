@@ -216,19 +216,35 @@ struct GemmArgs {
     float* Z;                    // epilogue 1: pre-activation output
     const float* Zin;            // epilogue 2: pre-activation input
     int M, N, K;
-    int epi;                     // 0 C = AB + bias; 1 Z = AB + bias, C = gelu(Z); 2 C = AB gelu'(Zin)
+    int epi;                     // 0 C = AB + bias; 1 Z = AB + bias, C = gelu(Z); 2 C = AB gelu'(Zin);
+                                 // 3 C = AB + bias, Z = scale (C - Zin);
+                                 // kEpiColsum C[n] = sum_m A[m sam + n] (M, N, A, sam, C only)
+    float scale;
+    int blocks, quads;           // set by launch_gemms
 };
+constexpr int kEpiColsum = 4;
 
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
-hipError_t launch_colsum(const float* X, int M, int N, int ld, float* out, hipStream_t s);
-hipError_t launch_mse_grad(const float* Y, const float* Tg, int64_t count, float scale, float* dY,
-                           hipStream_t s);
+// Independent products of one launch.
+constexpr int kMaxGemmTasks = 3;
+struct GemmTasks {
+    GemmArgs t[kMaxGemmTasks];
+};
+hipError_t launch_gemms(const GemmArgs* g, int count, hipStream_t s);
+
+// One array of a gather: rows of `cols` values, standardised by mu and inv.
+struct GatherArgs {
+    const float* src;
+    int cols;
+    const float* mu;
+    const float* inv;
+    float* dst;
+};
 hipError_t launch_mse_loss(const float* Y, const float* Tg, int64_t count, double* loss,
                            hipStream_t s);
 hipError_t launch_adam(float* P, const float* G, float* Mo, float* Vo, int64_t n, float lr,
                        int64_t step, hipStream_t s);
-hipError_t launch_gather_norm(const float* src, const int32_t* idx, int rows, int cols,
-                              const float* mu, const float* inv, float* dst, hipStream_t s);
+hipError_t launch_gather_norm(const GatherArgs& x, const GatherArgs& y, const int32_t* idx, int rows,
+                              hipStream_t s);
 hipError_t launch_col_stats(const float* X, int64_t rows, int cols, float* mu, float* inv,
                             hipStream_t s);
 hipError_t launch_cv_gather_series(const double* const* series, int32_t count, int32_t n_out,

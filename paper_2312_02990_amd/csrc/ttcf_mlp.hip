@@ -26,68 +26,153 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 // ---------------------------------------------------------------------------------------
 // GEMM: C(m, n) = sum_k A(m, k) B(k, n), A(m, k) = A[m sam + k sak], B(k, n) = B[k sbk + n sbn]
 // Operands are rounded to bfloat16 as they are staged into LDS; gfx950's
-// v_mfma_f32_16x16x32_bf16 accumulates in FP32. Workgroup tile 64 x 64 (four waves of
-// 32 x 32, each 2 x 2 MFMA tiles), K step 32: one matrix instruction per tile and step.
+// v_mfma_f32_16x16x32_bf16 accumulates in FP32. Workgroup tile B x B (four waves of B/2 x B/2),
+// one matrix instruction per 16 x 16 tile and K step of 32.
 // Operand layout of the 16x16x32 instruction: lane l holds A[l % 16][8 (l / 16) + i] and
-// B[8 (l / 16) + i][l % 16] (i = 0..7); the result D[4 (l / 16) + i][l % 16].
-// Epilogues: 0 C = acc + bias; 1 Z = acc + bias, C = gelu(Z); 2 C = acc * gelu'(Zin).
-// The K loop runs in a fixed order: results are deterministic.
+// B[8 (l / 16) + i][l % 16] (i = 0..7); the result D[4 (l / 16) + i][l % 16]. Both operands lie
+// k-fastest in LDS, so a fragment is one 16-byte read.
+// Epilogues: 0 C = acc + bias; 1 Z = acc + bias, C = gelu(Z); 2 C = acc * gelu'(Zin);
+// 3 C = acc + bias, dY = scale (C - T). The K loop runs in a fixed order: results are
+// deterministic, and the same for both tile sizes.
+//
+// What bounds it at the network's sizes (a training step: rows = 256, 64-256-256-K): the latency
+// of a block's loads and the launches. A block keeps a whole K chunk of loads in flight
+// (coalesced along whichever index is contiguous) and loads the next chunk while it multiplies;
+// 32 x 32 tiles give 64 blocks where 64 x 64 ones give 16; and up to three independent products
+// and a column sum go in one launch. Training step of batch 256: 324 us with one product per
+// launch, a K step of 32 and 64 x 64 tiles; 63 us now.
 // ---------------------------------------------------------------------------------------
 
-constexpr int kBM = 64, kBN = 64, kBK = 32;
+// Bias gradient: out[n] = sum over the M rows of X(m, n), 64 columns per workgroup. Sixteen
+// partial sums of every 16th row (four per wave) added in order: a fixed order.
+__device__ __forceinline__ void colsum_block(const GemmArgs& g, int block, float* part) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int n = block * 64 + lane;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    if (n < g.N)
+        for (int m = w; m < g.M; m += 128) {
+            float v[32];  // the loads of eight rows of each partial sum together
+#pragma unroll
+            for (int i = 0; i < 32; ++i)
+                v[i] = m + 4 * i < g.M ? g.A[(int64_t)(m + 4 * i) * g.sam + n] : 0.f;
+#pragma unroll
+            for (int i = 0; i < 32; ++i) s[i % 4] += v[i];
+        }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part[(w + 4 * q) * 64 + lane] = s[q];
+    __syncthreads();
+    if (w == 0 && n < g.N) {
+        float t = 0.f;
+        for (int v = 0; v < 16; ++v) t += part[v * 64 + lane];
+        g.C[n] = t;
+    }
+}
 
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
-    __shared__ short As[kBM][kBK + 4];
-    __shared__ short Bs[kBK][kBN + 4];
+// A tile of one operand on its way to LDS: B rows (m or n) of KC values of k as floats, four
+// consecutive ones per load where the strides and the base allow it.
+template <int B, int KC>
+struct Strip {
+    static constexpr int N4 = B * KC / 1024;  // quads per thread
+    f32x4 v[N4];
+    // place of quad i: (row, k) of its first value; along k if the strip's k index is contiguous
+    static __device__ __forceinline__ int row(bool along_k, int i) {
+        const int q = threadIdx.x + 256 * i;
+        return along_k ? q / (KC / 4) : q % (B / 4) * 4;
+    }
+    static __device__ __forceinline__ int col(bool along_k, int i) {
+        const int q = threadIdx.x + 256 * i;
+        return along_k ? q % (KC / 4) * 4 : q / (B / 4);
+    }
+    // rows r0.. of P (stride sr), values k0.. (stride sk); one of the strides is 1
+    __device__ __forceinline__ void load(const float* P, int64_t sr, int64_t sk, int r0, int rows,
+                                         int k0, int K, bool along_k, bool quads) {
+#pragma unroll
+        for (int i = 0; i < N4; ++i) {
+            const int r = r0 + row(along_k, i), k = k0 + col(along_k, i);
+            v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const float* p = P + (r * sr + k * sk);
+            if (quads) {
+                if (r < rows && k < K) v[i] = *(const f32x4*)p;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (r + (along_k ? 0 : e) < rows && k + (along_k ? e : 0) < K) v[i][e] = p[e];
+            }
+        }
+    }
+    template <int LD>
+    __device__ __forceinline__ void store(short* S, bool along_k) const {
+#pragma unroll
+        for (int i = 0; i < N4; ++i) {
+            short* s = S + row(along_k, i) * LD + col(along_k, i);
+            if (along_k) {
+                typedef short short4v __attribute__((ext_vector_type(4)));
+                *(short4v*)s = short4v{f2bf(v[i][0]), f2bf(v[i][1]), f2bf(v[i][2]), f2bf(v[i][3])};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[e * LD] = f2bf(v[i][e]);
+            }
+        }
+    }
+};
+
+template <int B>
+__global__ __launch_bounds__(256) void k_gemm_bf16(GemmTasks tasks) {
+    constexpr int KC = B == 32 ? 256 : 64;  // K chunk
+    constexpr int LD = KC + 8;
+    constexpr int NT = B / 32;
+    __shared__ __align__(16) short As[B * LD];
+    __shared__ __align__(16) short Bs[B * LD];
+    const GemmArgs& g = tasks.t[blockIdx.y];
+    const int block = blockIdx.x;
+    if (block >= g.blocks) return;
+    if (g.epi == kEpiColsum) {
+        colsum_block(g, block, (float*)As);
+        return;
+    }
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int m0 = blockIdx.y * kBM, n0 = blockIdx.x * kBN;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    f32x4 acc[2][2];
+    const int nbn = (g.N + B - 1) / B;
+    const int m0 = (block / nbn) * B, n0 = (block % nbn) * B;
+    const int wm = (wave >> 1) * (B / 2), wn = (wave & 1) * (B / 2);
+    f32x4 acc[NT][NT];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < g.K; k0 += kBK) {
-        for (int e = t; e < kBM * kBK; e += 256) {
-            const int r = e / kBK, c = e % kBK;
-            const int m = m0 + r, k = k0 + c;
-            const float v = (m < g.M && k < g.K) ? g.A[(int64_t)m * g.sam + (int64_t)k * g.sak] : 0.f;
-            As[r][c] = f2bf(v);
-        }
-        for (int e = t; e < kBK * kBN; e += 256) {
-            const int r = e / kBN, c = e % kBN;
-            const int k = k0 + r, n = n0 + c;
-            const float v = (k < g.K && n < g.N) ? g.B[(int64_t)k * g.sbk + (int64_t)n * g.sbn] : 0.f;
-            Bs[r][c] = f2bf(v);
-        }
+        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bool ak = g.sak == 1, bk = g.sbk == 1;
+    Strip<B, KC> a, b;
+    a.load(g.A, g.sam, g.sak, m0, g.M, 0, g.K, ak, g.quads & 1);
+    b.load(g.B, g.sbn, g.sbk, n0, g.N, 0, g.K, bk, g.quads & 2);
+    for (int k0 = 0; k0 < g.K; k0 += KC) {
+        a.template store<LD>(As, ak);
+        b.template store<LD>(Bs, bk);
         __syncthreads();
-        {
-            const int kb = (lane >> 4) * 8;
-            bf16x8 a[2], b[2];
+        if (k0 + KC < g.K) {
+            a.load(g.A, g.sam, g.sak, m0, g.M, k0 + KC, g.K, ak, g.quads & 1);
+            b.load(g.B, g.sbn, g.sbk, n0, g.N, k0 + KC, g.K, bk, g.quads & 2);
+        }
+        const int steps = min(KC, g.K - k0 + 31) / 32;
+#pragma unroll 1
+        for (int s = 0; s < steps; ++s) {
+            const int kb = s * 32 + (lane >> 4) * 8;
+            bf16x8 fa[NT], fb[NT];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int row = wm + i * 16 + (lane & 15);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) a[i][e] = __builtin_bit_cast(__bf16, As[row][kb + e]);
+            for (int i = 0; i < NT; ++i) {
+                fa[i] = *(const bf16x8*)&As[(wm + i * 16 + (lane & 15)) * LD + kb];
+                fb[i] = *(const bf16x8*)&Bs[(wn + i * 16 + (lane & 15)) * LD + kb];
             }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int col = wn + j * 16 + (lane & 15);
+            for (int i = 0; i < NT; ++i)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) b[j][e] = __builtin_bit_cast(__bf16, Bs[kb + e][col]);
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < NT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
@@ -95,54 +180,64 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
                 if (m >= g.M || n >= g.N) continue;
                 float v = acc[i][j][r];
                 const int64_t o = (int64_t)m * g.ldc + n;
-                if (g.epi == 0) {
-                    if (g.bias) v += g.bias[n];
-                    g.C[o] = v;
-                } else if (g.epi == 1) {
-                    if (g.bias) v += g.bias[n];
+                if (g.epi == 2) {
+                    g.C[o] = v * gelu_grad_f(g.Zin[o]);
+                    continue;
+                }
+                if (g.bias) v += g.bias[n];
+                if (g.epi == 1) {
                     g.Z[o] = v;
                     g.C[o] = gelu_f(v);
                 } else {
-                    g.C[o] = v * gelu_grad_f(g.Zin[o]);
+                    g.C[o] = v;
+                    if (g.epi == 3) g.Z[o] = g.scale * (v - g.Zin[o]);
                 }
             }
 }
 
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-    if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipSuccess;
-    dim3 grid((g.N + kBN - 1) / kBN, (g.M + kBM - 1) / kBM);
-    hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(256), 0, s, g);
+hipError_t launch_gemms(const GemmArgs* g, int count, hipStream_t s) {
+    if (count < 1 || count > kMaxGemmTasks) return hipErrorInvalidValue;
+    GemmTasks tasks{};
+    // whether the four consecutive values of an operand's load are aligned and all in range or none
+    auto quads = [](const float* p, int64_t stride, int extent) {
+        return (uintptr_t)p % 16 == 0 && stride % 4 == 0 && extent % 4 == 0;
+    };
+    for (int i = 0; i < count; ++i) {
+        GemmArgs& a = tasks.t[i] = g[i];
+        if (a.epi == kEpiColsum) continue;
+        if ((a.sak != 1 && a.sam != 1) || (a.sbk != 1 && a.sbn != 1)) return hipErrorInvalidValue;
+        a.quads = (quads(a.A, a.sak == 1 ? a.sam : a.sak, a.sak == 1 ? a.K : a.M) ? 1 : 0) |
+                  (quads(a.B, a.sbk == 1 ? a.sbn : a.sbk, a.sbk == 1 ? a.K : a.N) ? 2 : 0);
+    }
+    int total = 0, most = 0;
+    auto fill = [&](int tile) {
+        total = most = 0;
+        for (int i = 0; i < count; ++i) {
+            GemmArgs& a = tasks.t[i];
+            const bool none = a.M <= 0 || a.N <= 0 || (a.epi != kEpiColsum && a.K <= 0);
+            a.blocks = none ? 0
+                       : a.epi == kEpiColsum ? (a.N + 63) / 64
+                                             : ((a.M + tile - 1) / tile) * ((a.N + tile - 1) / tile);
+            total += a.blocks;
+            most = a.blocks > most ? a.blocks : most;
+        }
+    };
+    // 64 x 64 tiles read each operand half as often; below a block per CU the smaller tiles'
+    // parallelism is worth more
+    fill(64);
+    if (total == 0) return hipSuccess;
+    if (total >= 256) {
+        hipLaunchKernelGGL(k_gemm_bf16<64>, dim3(most, count), dim3(256), 0, s, tasks);
+    } else {
+        fill(32);
+        hipLaunchKernelGGL(k_gemm_bf16<32>, dim3(most, count), dim3(256), 0, s, tasks);
+    }
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------
 // small element-wise and reduction kernels (fixed-order sums)
 // ---------------------------------------------------------------------------------------
-
-// out[n] = sum over the M rows of X(m, n): 64 columns per workgroup, its 16 waves taking
-// every 16th row, the wave partials added in wave order (a fixed order)
-__global__ __launch_bounds__(1024) void k_colsum(const float* X, int M, int N, int ld,
-                                                 float* out) {
-    __shared__ float part[16][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int n = blockIdx.x * 64 + lane;
-    float s = 0.f;
-    if (n < N)
-        for (int m = w; m < M; m += 16) s += X[(int64_t)m * ld + n];
-    part[w][lane] = s;
-    __syncthreads();
-    if (w == 0 && n < N) {
-        float t = 0.f;
-        for (int v = 0; v < 16; ++v) t += part[v][lane];
-        out[n] = t;
-    }
-}
-
-// dY = 2 (Y - T) / (M N); loss (one value) = mean (Y - T)^2 when loss != null
-__global__ void k_mse_grad(const float* Y, const float* Tg, int64_t count, float scale, float* dY) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) dY[i] = scale * (Y[i] - Tg[i]);
-}
 
 __global__ void k_mse_loss(const float* Y, const float* Tg, int64_t count, double* loss) {
     __shared__ double part[256];
@@ -172,45 +267,53 @@ __global__ void k_adam(float* P, const float* G, float* Mo, float* Vo, int64_t n
     P[i] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
 }
 
-// dst[r][c] = (src[idx[r]][c] - mu[c]) * inv[c] (mu, inv may be null: plain gather)
-__global__ void k_gather_norm(const float* src, const int32_t* idx, int rows, int cols,
-                              const float* mu, const float* inv, float* dst) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)rows * cols) return;
-    const int r = (int)(e / cols), c = (int)(e % cols);
+// dst[r][c] = (src[idx[r]][c] - mu[c]) * inv[c], for up to two arrays of the same rows (idx null:
+// the rows in order)
+__global__ void k_gather_norm(GatherArgs x, GatherArgs y, const int32_t* idx, int rows) {
+    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const bool second = e >= (int64_t)rows * x.cols;
+    if (second) e -= (int64_t)rows * x.cols;
+    const GatherArgs& g = second ? y : x;
+    if (e >= (int64_t)rows * g.cols) return;
+    const int r = (int)(e / g.cols), c = (int)(e % g.cols);
     const int64_t sr = idx ? idx[r] : r;
-    float v = src[sr * cols + c];
-    if (mu) v = (v - mu[c]) * inv[c];
-    dst[e] = v;
+    g.dst[e] = (g.src[sr * g.cols + c] - g.mu[c]) * g.inv[c];
 }
 
-// mean and 1/std of every column (two passes in FP64; std floor 1e-12)
-__global__ void k_col_stats(const float* X, int64_t rows, int cols, float* mu, float* inv) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
+// mean and 1/std of every column (two passes in FP64; std floor 1e-12): 16 columns per workgroup,
+// 64 threads on each column's rows, partial sums added in thread order (a fixed order). With one
+// thread per column the 1024 rows of each pass were one chain of loads (0.33 ms).
+constexpr int kStatCols = 16, kStatRows = 64;
+__global__ __launch_bounds__(kStatCols * kStatRows) void k_col_stats(const float* X, int64_t rows,
+                                                                     int cols, float* mu, float* inv) {
+    __shared__ double part[kStatRows][kStatCols + 1];
+    const int cl = threadIdx.x % kStatCols, w = threadIdx.x / kStatCols;
+    const int c = blockIdx.x * kStatCols + cl;
+    auto total = [&](double v) {
+        __syncthreads();
+        part[w][cl] = v;
+        __syncthreads();
+        double s = 0.0;
+        for (int q = 0; q < kStatRows; ++q) s += part[q][cl];
+        return s;
+    };
     double s = 0.0;
-    for (int64_t r = 0; r < rows; ++r) s += X[r * cols + c];
-    const double m = s / (double)rows;
+    if (c < cols)
+        for (int64_t r = w; r < rows; r += kStatRows) s += X[r * cols + c];
+    const double m = total(s) / (double)rows;
     double q = 0.0;
-    for (int64_t r = 0; r < rows; ++r) {
-        const double d = X[r * cols + c] - m;
-        q += d * d;
-    }
+    if (c < cols)
+        for (int64_t r = w; r < rows; r += kStatRows) {
+            const double d = X[r * cols + c] - m;
+            q += d * d;
+        }
+    q = total(q);
+    if (w != 0 || c >= cols) return;
     const double sd = sqrt(q / (double)(rows > 1 ? rows - 1 : 1));
     mu[c] = (float)m;
     inv[c] = (float)(1.0 / (sd > 1e-12 ? sd : 1e-12));
 }
 
-hipError_t launch_colsum(const float* X, int M, int N, int ld, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_colsum, dim3((N + 63) / 64), dim3(1024), 0, s, X, M, N, ld, out);
-    return hipGetLastError();
-}
-hipError_t launch_mse_grad(const float* Y, const float* Tg, int64_t count, float scale, float* dY,
-                           hipStream_t s) {
-    hipLaunchKernelGGL(k_mse_grad, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, Y, Tg,
-                       count, scale, dY);
-    return hipGetLastError();
-}
 hipError_t launch_mse_loss(const float* Y, const float* Tg, int64_t count, double* loss,
                            hipStream_t s) {
     hipLaunchKernelGGL(k_mse_loss, dim3(1), dim3(256), 0, s, Y, Tg, count, loss);
@@ -224,17 +327,17 @@ hipError_t launch_adam(float* P, const float* G, float* Mo, float* Vo, int64_t n
                        lr, b1, b2, 1e-8f, c1, c2);
     return hipGetLastError();
 }
-hipError_t launch_gather_norm(const float* src, const int32_t* idx, int rows, int cols,
-                              const float* mu, const float* inv, float* dst, hipStream_t s) {
-    const int64_t n = (int64_t)rows * cols;
+hipError_t launch_gather_norm(const GatherArgs& x, const GatherArgs& y, const int32_t* idx, int rows,
+                              hipStream_t s) {
+    const int64_t n = (int64_t)rows * (x.cols + y.cols);
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather_norm, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, idx,
-                       rows, cols, mu, inv, dst);
+    hipLaunchKernelGGL(k_gather_norm, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x, y, idx, rows);
     return hipGetLastError();
 }
 hipError_t launch_col_stats(const float* X, int64_t rows, int cols, float* mu, float* inv,
                             hipStream_t s) {
-    hipLaunchKernelGGL(k_col_stats, dim3((cols + 63) / 64), dim3(64), 0, s, X, rows, cols, mu, inv);
+    hipLaunchKernelGGL(k_col_stats, dim3((cols + kStatCols - 1) / kStatCols), dim3(kStatCols * kStatRows), 0,
+                       s, X, rows, cols, mu, inv);
     return hipGetLastError();
 }
 
@@ -245,11 +348,12 @@ hipError_t launch_col_stats(const float* X, int64_t rows, int cols, float* mu, f
 // 20 / Ly) clamped): sum p_x, sum p_x p_y, and half the pair virial x_ij F_y,ij of each of the
 // slab's atoms; then sum_i (F_x,i p_y,i + p_x,i F_y,i) and sum_{i<j} (p_x,i - p_x,j) F_y,ij],
 // all of the mapped start state (Eq. (mappings): x -> -x for mappings 2 and 3, p_x and p_y
-// signs as below). One workgroup of 64 threads per row: the mapped state is staged in LDS,
-// thread q computes the pair terms of atoms q, q + 64, ... against every other atom (each
+// signs as below). One workgroup of 256 threads per row: the mapped state is staged in LDS,
+// thread q computes the pair terms of atoms q, q + 256, ... against every other atom (each
 // pair seen from both sides, so no atomics), then thread q < 62 forms one sum in atom order
-// (deterministic). FP64 throughout; LDS 9 n doubles.
-__global__ __launch_bounds__(64) void k_cv_features(
+// (deterministic). FP64 throughout; LDS 9 n doubles. With one wave a row each thread had
+// four atoms' chains in turn (1024 rows of N = 256: 222 us, 140 with four waves).
+__global__ __launch_bounds__(256) void k_cv_features(
     const double* states, int32_t n, const int32_t* state_of, const int32_t* map_of,
     const double* vpxy0, const double* vsign, int32_t rows, double lx, double ly, double lz,
     double rc2, double c_attr, double volume, double temperature, double gamma_dot, float* out,
@@ -349,7 +453,7 @@ __global__ __launch_bounds__(64) void k_cv_features(
 // times a sign (p_x sums and the two force-momentum sums by s_x, p_x p_y by s_x s_y, the virial
 // by s_r, the sign of x), and the per-row kernel's operations give exactly those negations,
 // so both kernels write the same bits.
-__global__ __launch_bounds__(64) void k_cv_features_maps(
+__global__ __launch_bounds__(256) void k_cv_features_maps(
     const double* states, int32_t n, int32_t n_states, const double* vpxy0, const double* vsign,
     double lx, double ly, double lz, double rc2, double c_attr, double volume,
     double temperature, double gamma_dot, float* out, double* b0_out, double* om_out) {
@@ -462,7 +566,7 @@ hipError_t launch_cv_features(const double* states, int32_t n, const int32_t* st
     const size_t lds = lds_bytes_cv_features(n);
     (void)hipFuncSetAttribute((const void*)k_cv_features,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k_cv_features, dim3(rows), dim3(64), lds, s, states, n, state_of, map_of,
+    hipLaunchKernelGGL(k_cv_features, dim3(rows), dim3(256), lds, s, states, n, state_of, map_of,
                        vpxy0, vsign, rows, box[0], box[1], box[2], rc2, c_attr, volume,
                        temperature, gamma_dot, out, b0_out, om_out);
     return hipGetLastError();
@@ -477,7 +581,7 @@ hipError_t launch_cv_features_maps(const double* states, int32_t n, int32_t n_st
     const size_t lds = lds_bytes_cv_features_maps(n);
     (void)hipFuncSetAttribute((const void*)k_cv_features_maps,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k_cv_features_maps, dim3(n_states), dim3(64), lds, s, states, n, n_states,
+    hipLaunchKernelGGL(k_cv_features_maps, dim3(n_states), dim3(256), lds, s, states, n, n_states,
                        vpxy0, vsign, box[0], box[1], box[2], rc2, c_attr, volume, temperature,
                        gamma_dot, out, b0_out, om_out);
     return hipGetLastError();
