@@ -51,6 +51,7 @@ struct ChannelLaunch {
     ChannelDesc* descs;
     const int32_t* order;   // job order (null: 0..n_jobs-1)
     int32_t n_jobs, grid, cmax, max_steps;
+    int32_t win;            // whether the LDS window fits beside the rest
     int32_t* queue;
     char* scratch;          // grid x scratch_stride bytes
     size_t scratch_stride;
@@ -76,7 +77,7 @@ struct ChannelResponse {
     double* out;               // 4 planes of n_t x n_cols
 };
 
-size_t channel_lds_bytes(int nmax, int cmax);
+size_t channel_lds_bytes(int nmax, int cmax, bool win);
 // replicas of the mother (momenta plus optional kicks) and snapshots of replicas into the
 // stored start states (slot q * per + slot of replica q)
 hipError_t launch_channel_replicate(const double* r, const double* p, const double* kicks,

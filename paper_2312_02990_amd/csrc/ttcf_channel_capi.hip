@@ -175,7 +175,9 @@ int32_t ensure_scratch(ttcf_channel_ctx* c, int grid) {
 
 int32_t launch(ttcf_channel_ctx* c, ChannelDesc* d_descs, int32_t n_jobs, int32_t max_steps,
                bool timed) {
-    const size_t lds = channel_lds_bytes(c->dev.n, c->dev.lc[0] * c->dev.lc[1] * c->dev.lc[2]);
+    const int cmax = c->dev.lc[0] * c->dev.lc[1] * c->dev.lc[2];
+    const bool win = channel_lds_bytes(c->dev.n, cmax, true) <= c->max_lds;
+    const size_t lds = channel_lds_bytes(c->dev.n, cmax, win);
     if (lds > c->max_lds) return cfail(c, TTCF_EINVAL, "system exceeds the LDS of one workgroup");
     // resident workgroups per CU: the LDS and the register budget (4 SIMDs per CU)
     const int per_cu = std::max(
@@ -189,7 +191,8 @@ int32_t launch(ttcf_channel_ctx* c, ChannelDesc* d_descs, int32_t n_jobs, int32_
     L.order = nullptr;
     L.n_jobs = n_jobs;
     L.grid = grid;
-    L.cmax = c->dev.lc[0] * c->dev.lc[1] * c->dev.lc[2];
+    L.cmax = cmax;
+    L.win = win;
     L.max_steps = max_steps;
     L.queue = c->queue;
     L.scratch = c->scratch;
@@ -799,7 +802,8 @@ int32_t ttcf_channel_debug_forces(const ttcf_channel* ch, const double* r, const
     if (e != hipSuccess)
         return cfail(nullptr, TTCF_EDEVICE, std::string("device query: ") + hipGetErrorString(e));
     const int cmax = dev.lc[0] * dev.lc[1] * dev.lc[2];
-    if (channel_lds_bytes(dev.n, cmax) > prop.sharedMemPerBlock)
+    const bool win = channel_lds_bytes(dev.n, cmax, true) <= prop.sharedMemPerBlock;
+    if (channel_lds_bytes(dev.n, cmax, win) > prop.sharedMemPerBlock)
         return cfail(nullptr, TTCF_EINVAL, "system exceeds the LDS of one workgroup");
     const size_t n = (size_t)dev.n, nw = (size_t)dev.n_wall;
     const size_t sbytes = channel_scratch_bytes(dev.n, dev.kmax);
@@ -826,6 +830,7 @@ int32_t ttcf_channel_debug_forces(const ttcf_channel* ch, const double* r, const
     L.n_jobs = 1;
     L.grid = 1;
     L.cmax = cmax;
+    L.win = win;
     L.scratch = d_scr;
     L.scratch_stride = sbytes;
     std::vector<float> fh(3 * n);
