@@ -387,6 +387,14 @@ int32_t upload_mother_launches(ttcf_ctx* c, const MotherLaunch* ls, int32_t coun
     return TTCF_OK;
 }
 
+void mother_shape(const ttcf_ctx* c, const Mother& m, MotherLaunch* L) {
+    L->threads = m.threads;
+    L->apt = m.apt;
+    L->precision = m.sys.precision;
+    L->lds_bytes = lds_for(m.dev, m.sys.precision);
+    (void)mother_lists(m.dev, c->max_lds, L);
+}
+
 int32_t run_mother(ttcf_ctx* c, Mother& m, double temperature, int64_t n_chunks,
                    int64_t steps_per_chunk, double* snapshots, double* snap_zeta = nullptr) {
     if (steps_per_chunk <= 0 && n_chunks <= 0) return TTCF_OK;
@@ -408,10 +416,7 @@ int32_t run_mother(ttcf_ctx* c, Mother& m, double temperature, int64_t n_chunks,
         L.series = m.series + m.series_count;
         m.series_count += total;
     }
-    L.threads = m.threads;
-    L.apt = m.apt;
-    L.precision = m.sys.precision;
-    L.lds_bytes = lds_for(m.dev, m.sys.precision);
+    mother_shape(c, m, &L);
     int32_t rc = upload_mother_launches(c, &L, 1);
     if (rc != TTCF_OK) return rc;
     HIPCHECK(c, launch_mothers(c->d_mlaunch, 1, L, c->stream));
@@ -2168,10 +2173,7 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
             L.temperature = m.sys.temperature;
             L.nf = nf;
             L.q = nf * m.sys.temperature * m.sys.nh_tau * m.sys.nh_tau;
-            L.threads = m.threads;
-            L.apt = m.apt;
-            L.precision = m.sys.precision;
-            L.lds_bytes = lds_for(m.dev, m.sys.precision);
+            mother_shape(c, m, &L);
             L.series = nullptr;
         }
         if (rep && gd->decorrelate_steps > 0) {
@@ -2708,10 +2710,7 @@ struct Replicas {
             L.temperature = m.sys.temperature;
             L.nf = nf;
             L.q = nf * m.sys.temperature * m.sys.nh_tau * m.sys.nh_tau;
-            L.threads = m.threads;
-            L.apt = m.apt;
-            L.precision = m.sys.precision;
-            L.lds_bytes = lds_for(m.dev, m.sys.precision);
+            mother_shape(c, m, &L);
         }
         if (decorrelate > 0) return run(c, 0, decorrelate, nullptr);
         return TTCF_OK;

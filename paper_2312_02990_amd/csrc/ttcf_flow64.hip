@@ -1,5 +1,6 @@
 // ttcf_flow64.hip -- daughters with FP64 pair forces on gfx950: shear (Lees-Edwards), planar
-// elongation, and mixed flow, isokinetic or Nose-Hoover.
+// elongation, and mixed flow, isokinetic or Nose-Hoover; and mothers (FP64 or FP32 forces) over
+// the same neighbour lists.
 //
 // The Introduction names elongational and mixed flows among the fields TTCF extends to, and
 // Section Mathematical Framework notes that a field other than shear needs mappings of its
@@ -38,6 +39,8 @@
 // the force pass, a fifth the list builds, the rest the step's scalars and the two barriers.
 
 #include <math.h>
+
+#include <type_traits>
 
 #include "ttcf_device.h"
 
@@ -308,11 +311,12 @@ __device__ __forceinline__ void f64_sort(const F64Lds& S, const Cell64& H, const
 }
 
 // Builds the lists of the positions x, y, z (wrapped into the cell here) and publishes them in
-// S.xy, S.z. nh: the own atoms' list lengths; returns the wave's longest. The scan runs in FP32 over nine rows of five half cells (two ranges where a row
-// wraps in x), kScan candidates per lane per trip; the FP32 test has a margin for its own
-// rounding, so a list misses no pair of its radius.
-template <int F, int APT>
-__device__ int f64_build(const F64Lds& S, const Cell64& H, int n, int cmax, double rc,
+// S.xy, S.z; without STATE they are taken as they are (in the cell) and not published. nh: the own
+// atoms' list lengths; returns the wave's longest. The scan runs in FP32 over nine rows of five
+// half cells (two ranges where a row wraps in x), kScan candidates per lane per trip; the FP32 test
+// has a margin for its own rounding, so a list misses no pair of its radius.
+template <int F, int APT, bool STATE = true>
+__device__ __forceinline__ int f64_build(const F64Lds& S, const Cell64& H, int n, int cmax, double rc,
                          double (&x)[APT], double (&y)[APT], double (&z)[APT], List64& L,
                          int (&nh)[APT]) {
     const int T = blockDim.x, t = threadIdx.x;
@@ -322,7 +326,8 @@ __device__ int f64_build(const F64Lds& S, const Cell64& H, int n, int cmax, doub
     const double wmin = fmin(wx, fmin(H.hyy, H.hzz));
 #pragma unroll
     for (int j = 0; j < APT; ++j) {
-        if constexpr (F == kFlowShear) {
+        if constexpr (!STATE) {
+        } else if constexpr (F == kFlowShear) {
             const double ny = floor(y[j] * H.iyy);
             y[j] = __builtin_fma(-ny, H.hyy, y[j]);
             x[j] = __builtin_fma(-ny, H.hxy, x[j]);
@@ -417,7 +422,7 @@ __device__ int f64_build(const F64Lds& S, const Cell64& H, int n, int cmax, doub
 #pragma unroll
     for (int j = 0; j < APT; ++j) {
         const int a = t + j * T;
-        if (a < n) {
+        if (STATE && a < n) {
             S.xy[a] = make_double2(x[j], y[j]);
             S.z[a] = z[j];
         }
@@ -1098,6 +1103,440 @@ __global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4) k_flo
     }
 }
 
+// ---- mothers -----------------------------------------------------------------------------
+// Nose-Hoover equilibrium dynamics (the step of k_mother) over the same lists, one workgroup per
+// mother, atoms dealt to the threads as for daughters. Both force forms give what the cell form
+// gives:
+//   FP64  f64_forces (another order of the sums);
+//   FP32  the cell form's bits. Its separations come from FP32 coordinates relative to the atoms'
+//         cells, and its sums run over the stencil's cells in turn, so every step each atom's cell
+//         and relative coordinates go to LDS, and an atom's listed partners are taken in the
+//         order (dz, dy, dx of the cells, index). The list is kept in that order; a lane that meets
+//         a partner in range out of its turn (one in a hundred, each step) has its list sorted
+//         and summed by its wave.
+// What bounds a step is a CU's vector issue: about 70 instructions an entry, of which the longest
+// list of a wave sets the number (13 for a mean of 8). Measured on one MI355X, a step of one
+// mother, cell form -> lists: N = 2048 45.8 -> 28.3 us (FP64 61.7 -> 16.9), N = 1000 24.3 -> 15.0
+// (32.3 -> 9.0); 256 copies of N = 500 sampled over 150 steps 9.6 -> 2.1 ms with their export.
+
+constexpr int kSort32 = 16;  // longest list that is sorted in registers
+constexpr int kMotherAtoms = 2048;  // indexes of 11 bits
+
+// Neighbouring cells of an atom: c - own + 1 on each axis, wrapped; 0..2 for the stencil.
+struct Near32 {
+    int nc[3];
+    int before[3];  // own cell - 1
+    float w[3];
+};
+
+__device__ __forceinline__ uint32_t f32_axis(const Near32& N, int axis, uint32_t packed) {
+    uint32_t d = ((packed >> (6 * axis)) & 63u) - (uint32_t)N.before[axis];
+    d = min(d, d + (uint32_t)N.nc[axis]);
+    return min(d, d - (uint32_t)N.nc[axis]);
+}
+
+template <int APT>
+__device__ __forceinline__ void f32_publish(const F64Lds& S, const SysDev& sys, int n,
+                                            const uint16_t (&atom)[APT], const double (&x)[APT],
+                                            const double (&y)[APT], const double (&z)[APT]) {
+    float4* u = (float4*)S.xy;
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        const int a = threadIdx.x + j * blockDim.x;
+        if (a < n) {
+            const int cx = cell_coord(x[j], sys.inv_w[0], sys.nc[0]);
+            const int cy = cell_coord(y[j], sys.inv_w[1], sys.nc[1]);
+            const int cz = cell_coord(z[j], sys.inv_w[2], sys.nc[2]);
+            u[a] = make_float4((float)(x[j] - (double)cx * sys.w[0]),
+                               (float)(y[j] - (double)cy * sys.w[1]),
+                               (float)(z[j] - (double)cz * sys.w[2]),
+                               __int_as_float(cx | (cy << 6) | (cz << 12) | (atom[j] << 18)));
+        }
+    }
+}
+
+struct Sum32 {
+    float x, y, z, w;
+};
+
+struct Pair32 {
+    float x, y, z, fs;
+};
+
+// One pair's separation and force over it; whether it is in range (the force is 0 if not).
+__device__ __forceinline__ bool f32_separation(Pair32& d, const Near32& N, const float4& ui,
+                                               const float4& uj, uint32_t tx, uint32_t ty, uint32_t tz,
+                                               bool live, float rc2, float ca) {
+    d.x = (ui.x - uj.x) + N.w[0] * (1.0f - (float)tx);
+    d.y = (ui.y - uj.y) + N.w[1] * (1.0f - (float)ty);
+    d.z = (ui.z - uj.z) + N.w[2] * (1.0f - (float)tz);
+    const float r2 = d.x * d.x + d.y * d.y + d.z * d.z;
+    const bool in = live & (max(tx, max(ty, tz)) <= 2u) & (r2 < rc2);
+    const float inv = recip(r2);
+    const float s3 = inv * inv * inv;
+    d.fs = in ? s3 * (48.0f * s3 - 24.0f * ca) * inv : 0.0f;
+    return in;
+}
+
+__device__ __forceinline__ void f32_add(Sum32& g, const Pair32& d) {
+    g.x += d.fs * d.x;
+    g.y += d.fs * d.y;
+    g.z += d.fs * d.z;
+    g.w += d.x * (d.fs * d.y);
+}
+
+__device__ __forceinline__ bool f32_pair(Sum32& g, const Near32& N, const float4& ui, const float4& uj,
+                                         uint32_t tx, uint32_t ty, uint32_t tz, bool live, float rc2,
+                                         float ca) {
+    Pair32 d;
+    const bool in = f32_separation(d, N, ui, uj, tx, ty, tz, live, rc2, ca);
+    f32_add(g, d);
+    return in;
+}
+
+template <int APT>
+__device__ __forceinline__ void f32_forces(const F64Lds& S, const SysDev& sys, int n,
+                                           const int (&nh)[APT], bool rebuilt, float (&fx)[APT],
+                                           float (&fy)[APT], float (&fz)[APT], double& w0) {
+    const int t = threadIdx.x, T = blockDim.x;
+    const float4* u = (const float4*)S.xy;
+    const float rc2 = (float)sys.rc2, ca = (float)sys.c_attr;
+    const int stride = T * APT;
+    double wacc = 0.0;
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        const int a = t + j * T;
+        const bool own = a < n;
+        const int me = own ? a : 0;
+        const float4 ui = u[me];
+        Near32 N;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            N.nc[q] = sys.nc[q];
+            N.w[q] = (float)sys.w[q];
+            N.before[q] = ((__float_as_int(ui.w) >> (6 * q)) & 63) - 1;
+        }
+        uint16_t* list = S.list + (t * APT + j);
+        const bool over = own && nh[j] > kF64Cap;
+        const int len = over || !own ? 0 : nh[j];
+        // where a partner's turn comes
+        auto turn = [&](uint32_t tx, uint32_t ty, uint32_t tz, uint32_t pk) {
+            return ((tz * 9u + ty * 3u + tx) << 11) | (pk >> 18);
+        };
+        auto turn_of = [&](int id) {
+            const uint32_t pk = __float_as_uint(u[id].w);
+            return turn(min(f32_axis(N, 0, pk), 3u), min(f32_axis(N, 1, pk), 3u),
+                        min(f32_axis(N, 2, pk), 3u), pk);
+        };
+        Sum32 g{0.f, 0.f, 0.f, 0.f};
+        // the list in order; true if a partner in range came after one whose turn is later
+        auto pass = [&](int count) {
+            bool late = false;
+            uint32_t last = 0;
+            float4 v = u[0 < count ? list[0] : me];
+            int idn = 1 < count ? list[stride] : me;
+            for (int k = 0; __builtin_amdgcn_ballot_w64(k < count) != 0; ++k) {
+                const float4 uj = v;
+                v = u[idn];
+                const int ahead = list[min(k + 2, kF64Cap - 1) * stride];
+                idn = k + 2 < count ? ahead : me;
+                const uint32_t pk = __float_as_uint(uj.w);
+                const uint32_t tx = f32_axis(N, 0, pk), ty = f32_axis(N, 1, pk), tz = f32_axis(N, 2, pk);
+                const bool in = f32_pair(g, N, ui, uj, tx, ty, tz, k < count, rc2, ca);
+                const uint32_t at = turn(tx, ty, tz, pk);
+                late = late | (in & (at < last));
+                last = in ? at : last;
+            }
+            return late;
+        };
+        if (rebuilt) {  // the list by turns, for the first time
+            if (__builtin_amdgcn_ballot_w64(len > kSort32) == 0) {
+                uint32_t key[kSort32];
+#pragma unroll
+                for (int k = 0; k < kSort32; ++k) {
+                    const int id = k < len ? list[k * stride] : me;
+                    key[k] = k < len ? (turn_of(id) << 11) | (uint32_t)id : 0xFFFFFFFFu;
+                }
+                // Batcher's odd-even merge sort
+#pragma unroll
+                for (int p = 1; p < kSort32; p *= 2)
+#pragma unroll
+                    for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+                        for (int i = k % p; i + k < kSort32; i += 2 * k)
+#pragma unroll
+                            for (int q = 0; q < k; ++q)
+                                if (i + q + k < kSort32 && (i + q) / (2 * p) == (i + q + k) / (2 * p)) {
+                                    const uint32_t lo = min(key[i + q], key[i + q + k]);
+                                    key[i + q + k] = max(key[i + q], key[i + q + k]);
+                                    key[i + q] = lo;
+                                }
+#pragma unroll
+                for (int k = 0; k < kSort32; ++k)
+                    if (k < len) list[k * stride] = (uint16_t)(key[k] & 2047u);
+            } else {
+                uint32_t top = len > 0 ? turn_of(list[0]) : 0u;
+                for (int k = 1; k < len; ++k) {
+                    const int id = list[k * stride];
+                    const uint32_t at = turn_of(id);
+                    if (at >= top) {
+                        top = at;
+                        continue;
+                    }
+                    int m = k - 1;
+                    for (; m >= 0; --m) {
+                        const int before = list[m * stride];
+                        if (turn_of(before) <= at) break;
+                        list[(m + 1) * stride] = (uint16_t)before;
+                    }
+                    list[(m + 1) * stride] = (uint16_t)id;
+                }
+            }
+        }
+        const bool late = pass(len);
+        // a lane whose partners came out of turn: the wave takes its list, an entry a lane, sorts
+        // it by rank and adds up its pairs in turn
+        for (uint64_t todo = __builtin_amdgcn_ballot_w64(late); todo != 0; todo &= todo - 1) {
+            const int b = __builtin_ctzll(todo), lane = t & 63;
+            const int count = __builtin_amdgcn_readlane(len, b), it = __builtin_amdgcn_readlane(me, b);
+            uint16_t* row = S.list + ((t - lane + b) * APT + j);
+            const float4 ub = u[it];
+            Near32 B = N;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) B.before[q] = ((__float_as_int(ub.w) >> (6 * q)) & 63) - 1;
+            const bool live = lane < count;
+            const int id = live ? row[lane * stride] : it;
+            const float4 uj = u[id];
+            const uint32_t pk = __float_as_uint(uj.w);
+            const uint32_t tx = f32_axis(B, 0, pk), ty = f32_axis(B, 1, pk), tz = f32_axis(B, 2, pk);
+            const uint32_t at = (turn(min(tx, 3u), min(ty, 3u), min(tz, 3u), pk) << 1) | (live ? 0u : 1u);
+            int rank = 0;
+            for (int q = 0; q < count; ++q)
+                rank += (uint32_t)__builtin_amdgcn_readlane((int)at, q) < at ? 1 : 0;
+            if (live) row[rank * stride] = (uint16_t)id;
+            Pair32 d;
+            const bool in = f32_separation(d, B, ub, uj, tx, ty, tz, live, rc2, ca);
+            Sum32 sum{0.f, 0.f, 0.f, 0.f};
+            for (int q = 0; q < count; ++q) {
+                const uint64_t who = __builtin_amdgcn_ballot_w64(in & (rank == q));
+                if (who == 0) continue;
+                const int w = __builtin_ctzll(who);
+                auto of = [&](float v) {
+                    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), w));
+                };
+                f32_add(sum, Pair32{of(d.x), of(d.y), of(d.z), of(d.fs)});
+            }
+            if (lane == b) g = sum;
+        }
+        // an atom with more neighbours than a list holds: every other atom, cell by cell
+        if (__builtin_amdgcn_ballot_w64(over) != 0) {
+#pragma unroll 1
+            for (int c = 0; c < 27; ++c)
+#pragma unroll 1
+                for (int m = 0; m < n; ++m) {
+                    const float4 uj = u[m];
+                    const uint32_t pk = __float_as_uint(uj.w);
+                    const uint32_t tx = f32_axis(N, 0, pk), ty = f32_axis(N, 1, pk), tz = f32_axis(N, 2, pk);
+                    const bool turn_now = tz * 9u + ty * 3u + tx == (uint32_t)c;
+                    (void)f32_pair(g, N, ui, uj, tx, ty, tz, over & (m != me) & turn_now, rc2, ca);
+                }
+        }
+        fx[j] = own ? g.x : 0.0f;
+        fy[j] = own ? g.y : 0.0f;
+        fz[j] = own ? g.z : 0.0f;
+        wacc += own ? (double)g.w : 0.0;
+    }
+    w0 = 0.5 * wacc;  // every unordered pair was visited from both sides
+}
+
+template <bool F32, int APT>
+__global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4)
+    k_mother_lists(const MotherLaunch* ms, int nmax, int cmax) {
+    extern __shared__ __align__(16) char smem[];
+    __shared__ SysDev sys;
+    const MotherLaunch& m = ms[blockIdx.x];
+    const F64Lds S = f64_carve(smem, nmax, cmax, blockDim.x, APT);
+    if (threadIdx.x == 0) sys = m.sys;
+    __syncthreads();
+    const int T = blockDim.x, t = threadIdx.x, n = sys.n;
+    if (n > nmax || n > T * APT || n > kMotherAtoms) return;
+    Cell64 H;
+    H.hxx = uniform(sys.box[0]);
+    H.hyy = uniform(sys.box[1]);
+    H.hzz = uniform(sys.box[2]);
+    H.hxy = 0.0;
+    H.ixx = uniform(1.0 / sys.box[0]);
+    H.iyy = uniform(1.0 / sys.box[1]);
+    H.izz = uniform(1.0 / sys.box[2]);
+    double x[APT], y[APT], z[APT], px[APT], py[APT], pz[APT];
+    std::conditional_t<F32, float, double> fx[APT], fy[APT], fz[APT];
+    float path[APT];
+    int nh[APT], longest = 0;
+    List64 L;
+    L.rl = 0.0;
+    L.k = 0;
+    L.no_skin = false;
+    double* st = m.state;
+    uint16_t atom[APT];  // the state's atom behind the thread's atom j
+    {
+        // deal the atoms to the threads in cell order
+#pragma unroll
+        for (int j = 0; j < APT; ++j) {
+            const int a = t + j * T;
+            const bool v = a < n;
+            x[j] = v ? st[a] : 0.0;
+            y[j] = v ? st[n + a] : 0.0;
+            z[j] = v ? st[2 * n + a] : 0.0;
+        }
+        const Grid64 g = f64_grid(H, 0.0, H.hxx, sys.rc, cmax);
+        int place[APT], cell[APT];
+        float cart[APT][3];
+        f64_sort<kFlowShear, APT>(S, H, g, n, x, y, z, place, cell, cart);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < APT; ++j)
+            if (cell[j] >= 0) S.sid[place[j]] = (uint16_t)(t + j * T);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < APT; ++j) {
+            const int a = t + j * T;
+            atom[j] = a < n ? S.sid[a] : 0;
+        }
+        __syncthreads();  // the build reuses these bytes
+    }
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        const bool v = t + j * T < n;
+        const double* q = st + atom[j];
+        x[j] = v ? q[0] : 0.0;
+        y[j] = v ? q[n] : 0.0;
+        z[j] = v ? q[2 * (size_t)n] : 0.0;
+        px[j] = v ? q[3 * (size_t)n] : 0.0;
+        py[j] = v ? q[4 * (size_t)n] : 0.0;
+        pz[j] = v ? q[5 * (size_t)n] : 0.0;
+        path[j] = 0.0f;
+        nh[j] = 0;
+    }
+    double zeta = *m.zeta, pp = 0.0;
+    const double h = sys.dt, tau = 0.5 * h, gT = m.nf * m.temperature, iq = 1.0 / m.q;
+    const int64_t chunks = m.n_chunks > 0 ? m.n_chunks : 1, each = m.steps_per_chunk;
+    const int64_t total = chunks * each;
+    int64_t in_chunk = 0, ch = 0;
+    auto put = [&](double* q, int j) {
+        q[0] = x[j];
+        q[n] = y[j];
+        q[2 * (size_t)n] = z[j];
+        q[3 * (size_t)n] = px[j];
+        q[4 * (size_t)n] = py[j];
+        q[5 * (size_t)n] = pz[j];
+    };
+    auto snapshot = [&]() {
+        if (m.snap_zeta != nullptr && t == 0) m.snap_zeta[ch] = zeta;
+        if (m.snapshots != nullptr) {
+            double* dst = m.snapshots + (size_t)ch * 6 * (size_t)n;
+#pragma unroll
+            for (int j = 0; j < APT; ++j) {
+                if (t + j * T < n) put(dst + atom[j], j);
+            }
+        }
+        ++ch;
+    };
+    // step -1: the forces and the momentum sum of the start state
+    for (int64_t s = -1; s < total; ++s) {
+        const bool start = s < 0;
+        double c = 1.0;
+        float most = 0.0f;
+        if (!start) {
+            zeta += tau * (pp - gT) * iq;
+            c = exp(-zeta * tau);
+#pragma unroll
+            for (int j = 0; j < APT; ++j) {
+                px[j] = c * px[j] + tau * (double)fx[j];
+                py[j] = c * py[j] + tau * (double)fy[j];
+                pz[j] = c * pz[j] + tau * (double)fz[j];
+                x[j] += h * px[j];
+                y[j] += h * py[j];
+                z[j] += h * pz[j];
+                wrap_le(sys, 0.0, x[j], y[j], z[j]);
+                const float ux = (float)px[j], uy = (float)py[j], uz = (float)pz[j];
+                path[j] += (float)h * __builtin_sqrtf(ux * ux + uy * uy + uz * uz);
+                most = fmaxf(most, path[j]);
+            }
+        }
+        auto publish = [&]() {
+            if constexpr (F32) {
+                f32_publish<APT>(S, sys, n, atom, x, y, z);
+            } else {
+#pragma unroll
+                for (int j = 0; j < APT; ++j) {
+                    const int a = t + j * T;
+                    if (a < n) {
+                        S.xy[a] = make_double2(x[j], y[j]);
+                        S.z[a] = z[j];
+                    }
+                }
+            }
+        };
+        publish();
+        most = wave_max_dpp(most);
+        if ((t & 63) == 63) S.wmax[t >> 6] = most;
+        __syncthreads();
+        most = 0.0f;
+        for (int w = 0; w < (T >> 6); ++w) most = fmaxf(most, S.wmax[w]);
+        // (margins: FP32 paths, and FP32 separations that pass the cutoff test beyond r_c)
+        const bool stale = !(sys.rc * (1.0 + 1e-6) + 2.0 * (1.0 + 1e-5) * (double)most <= L.rl);
+        if (stale) {
+#pragma unroll
+            for (int j = 0; j < APT; ++j) path[j] = 0.0f;
+            longest = f64_build<kFlowShear, APT, false>(S, H, n, cmax, sys.rc, x, y, z, L, nh);
+            publish();
+            __syncthreads();
+        }
+        double w0, w1 = 0.0;
+        if constexpr (F32)
+            f32_forces<APT>(S, sys, n, nh, stale, fx, fy, fz, w0);
+        else
+            f64_forces<kFlowShear, APT>(S, H, n, sys.rc2, sys.c_attr, nh, longest, fx, fy, fz, w0, w1);
+        double mm[3] = {0.0, 0.0, w0};
+#pragma unroll
+        for (int j = 0; j < APT; ++j) {
+            const bool own = t + j * T < n;
+            if (!start) {
+                px[j] += tau * (own ? (double)fx[j] : 0.0);
+                py[j] += tau * (own ? (double)fy[j] : 0.0);
+                pz[j] += tau * (own ? (double)fz[j] : 0.0);
+            }
+            mm[0] += px[j] * px[j] + py[j] * py[j] + pz[j] * pz[j];
+            mm[1] += px[j] * py[j];
+        }
+        f64_sum<3, 4>(mm, S.red);
+        if (start) {
+            pp = mm[0];
+        } else {
+#pragma unroll
+            for (int j = 0; j < APT; ++j) {
+                px[j] *= c;
+                py[j] *= c;
+                pz[j] *= c;
+            }
+            pp = c * c * mm[0];
+            zeta += tau * (pp - gT) * iq;
+            if (m.series != nullptr && t == 0) m.series[s] = c * c * mm[1] + mm[2];
+        }
+        if (start ? each <= 0 : ++in_chunk == each) {
+            in_chunk = 0;
+            do {
+                snapshot();
+            } while (each <= 0 && ch < chunks);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        if (t + j * T < n) put(st + atom[j], j);
+    }
+    if (t == 0) *m.zeta = zeta;
+}
+
 // Start states of planar-elongation daughters under their mappings: bit 1 of map exchanges
 // the x and y axes of positions and momenta (the box is cubic), bit 0 reverses the momenta.
 // Mixed-flow daughters (mix): bit 1 exchanges the axes, then bit 0 reflects x
@@ -1214,6 +1653,49 @@ hipError_t launch_flow64(const PefLaunch& L, hipStream_t s) {
         case 0: return launch_flow64_f<kFlowShear>(L, s);
         case 1: return launch_flow64_f<kFlowElong>(L, s);
         case 2: return launch_flow64_f<kFlowMixed>(L, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// Mothers over lists: where an atom's neighbours leave its list room (as for daughters), the lists
+// and a grid fit one workgroup's LDS, and (FP32 form) the stencil is three cells a side and a cell
+// and an index fit one word. Otherwise (long cutoffs, more than 2048 atoms) the cell form. One atom
+// a thread as far as 1024 threads go, as the steps are a latency chain; four on half the
+// threads beyond, which doubles the registers (two on 1024 threads spilled 80 of them).
+bool mother_lists(const SysDev& S, size_t max_lds, MotherLaunch* L) {
+    L->list_lds = 0;
+    if (S.n > kMotherAtoms || 1.5 * flow64_neighbours((double)S.n / S.volume, S.rc) > kF64Cap) return false;
+    for (int a = 0; a < 3; ++a)
+        if (S.nc[a] < 3 || S.nc[a] > 63 || !(S.w[a] > S.rc * (1.0 + 2e-6))) return false;
+    const int cells = pef_max_cells(S.volume, S.rc);
+    L->list_cells = 2 * cells < S.n + 64 ? (cells < 27 ? 54 : 2 * cells) : S.n + 64;
+    L->list_apt = S.n <= kMaxThreads ? 1 : 4;
+    L->list_threads = ((S.n + L->list_apt - 1) / L->list_apt + 63) / 64 * 64;
+    const size_t lds = f64_plan(S.n, L->list_cells, L->list_threads, L->list_apt).total;
+    if (lds + sizeof(SysDev) + 256 > max_lds) return false;
+    L->list_lds = lds;
+    return true;
+}
+
+namespace {
+template <bool F32, int APT>
+hipError_t launch_mother_lists_t(const MotherLaunch* dev_ms, int count, const MotherLaunch& m,
+                                 hipStream_t s) {
+    (void)hipFuncSetAttribute((const void*)k_mother_lists<F32, APT>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)m.list_lds);
+    hipLaunchKernelGGL((k_mother_lists<F32, APT>), dim3(count), dim3(m.list_threads), m.list_lds, s, dev_ms,
+                       m.sys.n, m.list_cells);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_mother_lists(const MotherLaunch* dev_ms, int count, const MotherLaunch& m,
+                               hipStream_t s) {
+    switch (m.list_apt * 2 + (m.precision == 0 ? 0 : 1)) {
+        case 2: return launch_mother_lists_t<false, 1>(dev_ms, count, m, s);
+        case 3: return launch_mother_lists_t<true, 1>(dev_ms, count, m, s);
+        case 8: return launch_mother_lists_t<false, 4>(dev_ms, count, m, s);
+        case 9: return launch_mother_lists_t<true, 4>(dev_ms, count, m, s);
     }
     return hipErrorInvalidValue;
 }

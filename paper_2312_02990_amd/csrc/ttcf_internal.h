@@ -167,7 +167,9 @@ struct MotherLaunch {
     double* snap_zeta;     // n_chunks doubles: the thermostat variable at each snapshot, or nullptr
     double* series;        // V*P_xy after every step (n_chunks*steps_per_chunk), or nullptr
     int32_t threads, apt, precision;
-    size_t lds_bytes;
+    int32_t list_cells, list_threads, list_apt;  // mother_lists
+    size_t list_lds;       // its LDS, or 0: the cell form
+    size_t lds_bytes;      // the cell form's
 };
 
 struct AccumLaunch {
@@ -321,6 +323,9 @@ hipError_t copy_rows(void* host, void* dev, size_t pitch, size_t width, size_t r
                      hipStream_t s);
 hipError_t launch_zero_int(int32_t* p, hipStream_t s);
 hipError_t launch_daughters(const BatchLaunch& b, hipStream_t s);
+bool mother_lists(const SysDev& S, size_t max_lds, MotherLaunch* L);
+hipError_t launch_mother_lists(const MotherLaunch* dev_ms, int count, const MotherLaunch& m,
+                               hipStream_t s);
 hipError_t launch_mothers(const MotherLaunch* dev_ms, int count, const MotherLaunch& shape,
                           hipStream_t s);
 hipError_t launch_replicate(const double* src, const double* zsrc, int32_t n, const double* kicks,

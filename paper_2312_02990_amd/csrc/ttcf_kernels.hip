@@ -546,7 +546,8 @@ __global__ void k_zero_int(int32_t* p, int n) {
 }
 
 // ---------------------------------------------------------------------------------------
-// mother: Nose-Hoover equilibrium dynamics (gamma_dot = 0, plain periodic box)
+// mother: Nose-Hoover equilibrium dynamics (gamma_dot = 0, plain periodic box), cell form: what
+// mother_lists leaves (long cutoffs, more than 2048 atoms)
 // ---------------------------------------------------------------------------------------
 // zeta += tau (p.p - nf T)/Q; p = exp(-zeta tau) p + tau F; r += h p; F = F(r); p += tau F;
 // p *= exp(-zeta tau); zeta += tau (p.p - nf T)/Q. The p.p of the last update is c^2 times
@@ -1247,6 +1248,7 @@ static hipError_t launch_mother_t(const MotherLaunch* dev_ms, int count, int thr
 // dev_ms: device array of `count` mothers sharing one launch shape (threads, apt, precision)
 hipError_t launch_mothers(const MotherLaunch* dev_ms, int count, const MotherLaunch& shape,
                           hipStream_t s) {
+    if (shape.list_lds > 0) return launch_mother_lists(dev_ms, count, shape, s);
     const int nmax = shape.sys.n, cmax = shape.sys.nc[0] * shape.sys.nc[1] * shape.sys.nc[2];
     if (shape.precision == 0) {
         switch (shape.apt) {
