@@ -714,6 +714,27 @@ __device__ __forceinline__ void pf_record_obs(const SysDev& S, const double (&y)
 // one daughter
 // ---------------------------------------------------------------------------------------
 
+// Eight atoms a thread leave few vector registers: what spills went to scratch and back made up a
+// third of that build's step (64 states x 4 mappings of N = 4000 over 200 steps: 7.8 ms, 5.0 with
+// the two functions below). With four atoms a thread they are not needed (the moves of the first cost
+// 0.8% of the N = 2048 batch).
+// A step's scalars, the same in every lane, in scalar registers.
+template <int APT>
+__device__ __forceinline__ double uniform(double v) {
+    if constexpr (APT != kLargeApt) return v;
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Makes the compiler forget the FP64 values of FP32 forces, which it keeps beside them from one use
+// to the next otherwise (six registers an atom).
+template <int APT>
+__device__ __forceinline__ void forget_promoted(float& fx, float& fy, float& fz) {
+    if constexpr (APT == kLargeApt) asm volatile("" : "+v"(fx), "+v"(fy), "+v"(fz));
+}
+
 // Publish the owned atoms' fixed-point positions (unwrapped by their crossing counts) and
 // return the workgroup maximum of their path lengths since the last build (one barrier).
 template <int APT>
@@ -867,6 +888,8 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
         m0[5] += fxd(j) * fxd(j) + (double)fy[j] * (double)fy[j] +
                  (double)fz[j] * (double)fz[j];
     }
+#pragma unroll
+    for (int j = 0; j < APT; ++j) forget_promoted<APT>(fx[j], fy[j], fz[j]);
     pf_block_sum<8>(m0, L.red, nw);
     if (m0[7] != 0.0) health |= kHealthForceRange;
     if (done == 0) {
@@ -876,8 +899,8 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
         if (OBS && xs) pf_record_obs<APT>(S, y, px, py, pz, ps, xs, 0, L, nw);
     }
     if (health != 0) todo = 0;
-    const double sqrt2k0 = sqrt(2.0 * k0);
-    const double h = S.dt, tau = 0.5 * S.dt, tg = tau * gd;
+    const double sqrt2k0 = uniform<APT>(sqrt(2.0 * k0));
+    const double h = uniform<APT>(S.dt), tau = uniform<APT>(0.5 * h), tg = uniform<APT>(tau * gd);
     const float hpath = (float)h * (1.f + 0x1p-20f);
     const float reach = (float)S.rc;
     const float skin = (float)S.skin;
@@ -885,7 +908,8 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
     int since = 0;
     // First half of a step from the end-of-step moments pp, pxpy, pypy, fp, fxpy, ff (F the
     // current forces): p -> e p + g p_y x_hat + hh F.
-    double pp = m0[0], pxpy = m0[1], pypy = m0[2], fp = m0[3], fxpy = m0[4], ff = m0[5];
+    double pp = uniform<APT>(m0[0]), pxpy = uniform<APT>(m0[1]), pypy = uniform<APT>(m0[2]);
+    double fp = uniform<APT>(m0[3]), fxpy = uniform<APT>(m0[4]), ff = uniform<APT>(m0[5]);
     auto first_half = [&](double& e, double& g, double& hh) {
         if (NH) {
             zt += tau * (pp - nh_tgt) * nh_iq;
@@ -920,7 +944,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
 
     // the offset of the next step, computed a step ahead where its dependent chain overlaps
     // the kick scalars' chain
-    const double ilx = 1.0 / S.box[0];
+    const double ilx = uniform<APT>(1.0 / S.box[0]);
     double dxle_n = le_offset_nb(S, gd, k + 1, ilx);
     uint32_t dxq_n = fix32(dxle_n, S.fix_scale[0]);
     for (int step = 0; step < todo; ++step) {
@@ -928,7 +952,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
         k += 1;
         dxle = dxle_n;
         dxq = dxq_n;
-        const double lx = S.box[0], ly = S.box[1], lz = S.box[2];
+        const double lx = uniform<APT>(S.box[0]), ly = uniform<APT>(S.box[1]), lz = uniform<APT>(S.box[2]);
 #pragma unroll
         for (int j = 0; j < APT; ++j) {
             const double vx = px[j] + tg * py[j];
@@ -981,6 +1005,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
         double m[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, ps.w, (double)ps.close};
 #pragma unroll
         for (int j = 0; j < APT; ++j) {
+            forget_promoted<APT>(fx[j], fy[j], fz[j]);
             const double w1 = (COL && col) ? charge(j) : py[j];  // as for m0
             m[0] += px[j] * px[j] + py[j] * py[j] + pz[j] * pz[j] + 0.0 * (x[j] + y[j] + z[j]);
             m[1] += w1 * px[j];
@@ -994,8 +1019,12 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
             m[9] += fxd(j) * fxd(j) + (double)fy[j] * (double)fy[j] +
                     (double)fz[j] * (double)fz[j];
         }
+#pragma unroll
+        for (int j = 0; j < APT; ++j) forget_promoted<APT>(fx[j], fy[j], fz[j]);
         pf_block_sum12(m, L.red, nw);
         // ---- second half: p_end = A p + B F + (C p_y + D F_y) x_hat, end-of-step moments
+#pragma unroll
+        for (int q = 0; q < 12; ++q) m[q] = uniform<APT>(m[q]);
         double A, B, C, D, vpxy;
         bool drift = false;
         if (NH) {
@@ -1063,11 +1092,13 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
             break;
         }
         // ---- the next step's first half, applied together with this second half
-        dxle_n = le_offset_nb(S, gd, k + 1, ilx);
+        dxle_n = uniform<APT>(le_offset_nb(S, gd, k + 1, ilx));
+        for (double* q : {&pp, &pxpy, &pypy, &fp, &fxpy, &zt, &A, &B, &C, &D}) *q = uniform<APT>(*q);
         dxq_n = fix32(dxle_n, S.fix_scale[0]);
         double e, g, hh;
         first_half(e, g, hh);
-        const double K1 = e * A, K2 = e * C + g * A, K3 = e * B + hh, K4 = e * D + g * B;
+        const double K1 = uniform<APT>(e * A), K2 = uniform<APT>(e * C + g * A);
+        const double K3 = uniform<APT>(e * B + hh), K4 = uniform<APT>(e * D + g * B);
 #pragma unroll
         for (int j = 0; j < APT; ++j) {
             const double qx = K1 * px[j] + K2 * py[j] + K3 * fxd(j) + K4 * (double)fy[j];
