@@ -1102,14 +1102,44 @@ int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, b
     if (apt < 0) return fail(c, TTCF_EINVAL, "batch needs more than 4 atoms per thread");
     // pair words in LDS when every job's fit beside its layout (four atoms per thread only),
     // else in global scratch
+    const int jobs = (int)group.size(), cu_jobs = (jobs + c->num_cu - 1) / c->num_cu;
+    auto lds_lists = [&](int list_waves) {
+        size_t most = 0;
+        for (const DaughterDesc* dp : group)
+            most = std::max(most, lds_bytes_pairs_lds(dp->sys.n, dp->sys.lc[0] * dp->sys.lc[1] * dp->sys.lc[2],
+                                                      dp->kmax, apt, list_waves));
+        return most;
+    };
     size_t nl_lds_pl = 0;
-    if (nlf)
-        for (const DaughterDesc* dp : group) {
+    bool pairs_lds = false;
+    int list_waves = 1;
+    if (nlf) {
+        for (const DaughterDesc* dp : group)
             pair_stride = std::max<int64_t>(pair_stride, pair_words(dp->sys.n, dp->kmax, apt));
-            nl_lds_pl = std::max(nl_lds_pl, lds_bytes_pairs_lds(dp->sys.n, dp->sys.lc[0] * dp->sys.lc[1] *
-                                                                   dp->sys.lc[2], dp->kmax, apt));
+        nl_lds_pl = lds_lists(1);
+        pairs_lds = apt == pair_small_apt() && nl_lds_pl <= c->max_lds;
+        // A batch that leaves waves of the chip free (eight a CU) gets up to four waves for each
+        // one that owns atoms: they share the force pass, and the list build where their
+        // segments fit the LDS too. Results do not depend on it. Measured: 32 daughters of
+        // N = 256 over 100 steps, one wave each 1.00 ms, four 0.55; 256 of N = 864 over 200
+        // steps, four waves each 2.92 ms, eight 2.71. A full batch has no wave to spare.
+        const size_t base = pairs_lds ? nl_lds_pl : nl_lds;
+        const int held = std::max(1, std::min((int)(c->max_lds / base), 8 / (threads / 64)));
+        const int resident = std::min(held, cu_jobs);
+        int more = 4;
+        while (more > 1 && (threads * more > 512 || more * (threads / 64) * resident > 8)) more /= 2;
+        if (more > 1) {
+            threads *= more;
+            if (!pairs_lds) {
+                list_waves = more;
+            } else {
+                for (list_waves = more; list_waves > 1; list_waves /= 2)
+                    if (lds_lists(list_waves) * resident <= c->max_lds) break;
+                nl_lds_pl = lds_lists(list_waves);
+            }
         }
-    const bool pairs_lds = nlf && apt == pair_small_apt() && nl_lds_pl <= c->max_lds;
+        pair_stride *= list_waves;
+    }
     *L = BatchLaunch{};
     L->descs = c->d_descs;
     L->n_jobs = (int32_t)group.size();
@@ -1132,6 +1162,7 @@ int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, b
                                     "daughters recording the extra observables");
     L->pair_stride = pair_stride;
     L->pairs_lds = pairs_lds ? 1 : 0;
+    L->list_waves = list_waves;
     if (!nlf && list64 && precision == TTCF_PREC_FP64 && !L->obs && !L->field &&
         nmax <= kPefMaxAtoms) {
         // FP64 forces over neighbour lists wherever a workgroup holds them (the cell form

@@ -129,7 +129,8 @@ struct BatchLaunch {
     int32_t pairs_lds;     // pair-list form: 1 if each job's pair words live in LDS after its
                            // layout (lds_bytes covers lds_bytes_pairs_lds of every job)
     uint32_t* pairs;       // pair-list form otherwise: grid x pair_stride pair words
-    int64_t pair_stride;   // >= job_threads(n) / 64 * 256 * kmax of every job
+    int64_t pair_stride;   // >= list_waves * job_threads(n) / 64 * 256 * kmax of every job
+    int32_t list_waves;    // waves with a pair segment for each wave that owns atoms
     size_t lds_bytes;
 };
 
@@ -297,8 +298,8 @@ inline int64_t pair_words(int n, int kcap, int apt) {
     return (int64_t)pair_job_threads(n) * apt * kcap;
 }
 // LDS of one job with its pair words in LDS too (after the job's layout)
-inline size_t lds_bytes_pairs_lds(int n, int cells, int kcap, int apt) {
-    return lds_bytes_pairs(n, cells) + sizeof(uint32_t) * (size_t)pair_words(n, kcap, apt);
+inline size_t lds_bytes_pairs_lds(int n, int cells, int kcap, int apt, int list_waves) {
+    return lds_bytes_pairs(n, cells) + sizeof(uint32_t) * (size_t)pair_words(n, kcap, apt) * list_waves;
 }
 hipError_t launch_pairs(const BatchLaunch& b, hipStream_t s);
 // The pair form's list build and one force pass on given positions (inspection): per atom its

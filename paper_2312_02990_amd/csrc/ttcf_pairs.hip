@@ -18,6 +18,9 @@
 // to reach r_c (the bound of the previous list form: 2 d + |gamma_dot| t (r_c + 2 d) >= skin,
 // d the largest peculiar path length since the build).
 //
+// A workgroup may have more waves than own atoms (small batches, mixed sizes). They take part in
+// the force pass, and where the launch has segments for them in the list build.
+//
 // Forces. The 64-pair chunks of all segments are dealt round robin to the waves, every lane
 // busy. Each pair's force is truncated to 32-bit fixed point (a multiple of 2^-19 force
 // units) and added to both atoms with LDS integer atomics (+ to one, - to the other). Integer
@@ -314,13 +317,13 @@ typedef __attribute__((address_space(3))) uint32_t lu32;  // pair words in LDS
 // exceed the capacity).
 template <int APT, typename P>
 __device__ __forceinline__ int pf_gen_pairs(int n, int cells, uint32_t dxq, P seg, int seg_cap,
-                                            int tj) {
+                                            int listers) {
     const PairLds L = job_lds(n, cells);
     const SysDev& S = *L.sys;
     const int nc0 = S.lc[0], nc1 = S.lc[1], nc2 = S.lc[2];
     const int t = threadIdx.x, lane = t & 63;
     int base = 0;  // wave-uniform: pairs found so far by this wave
-    if (t >= tj) return 0;
+    if (t >= listers) return 0;
     // r_l^2 and the y and z fixed-point steps in units of the x step
     const float ux = S.fix_unit[0];
     const float rl2u = S.rl2_f / (ux * ux);
@@ -448,7 +451,7 @@ __device__ __forceinline__ int pf_rebuild(const SysDev& S, double dxle, uint32_t
                                           const double (&x)[APT], const double (&y)[APT],
                                           const double (&z)[APT], int (&rank)[APT],
                                           int (&cr)[APT], const PairLds& L, P seg, int seg_cap,
-                                          int tj, int (&cell)[APT], bool* overflow) {
+                                          int tj, int listers, int (&cell)[APT], bool* overflow) {
     const int T = blockDim.x, t = threadIdx.x, n = S.n;
     const int nc0 = S.lc[0], nc1 = S.lc[1], nc2 = S.lc[2];
     const int C = nc0 * nc1 * nc2;
@@ -537,7 +540,7 @@ __device__ __forceinline__ int pf_rebuild(const SysDev& S, double dxle, uint32_t
     }
     if (t == 0) L.scan[0] = 0;  // the list build's group counter (the scan is done with it)
     __syncthreads();
-    const int count = pf_gen_pairs<APT>(n, C, dxq, seg, seg_cap, tj);
+    const int count = pf_gen_pairs<APT>(n, C, dxq, seg, seg_cap, listers);
     const int wave = t >> 6, nwb = T >> 6;
     if ((t & 63) == 0) {
         L.flags[wave] = count > seg_cap ? 1 : 0;
@@ -781,8 +784,8 @@ __device__ __forceinline__ float pf_publish(const SysDev& S, uint32_t dxq, const
 // the colour charge +1 (even a) or -1 (odd a), the field adds charge * F_e to its x force in
 // FP64, there is no shear, and the series records V J_x = sum_a charge p_x,a.
 template <int APT, bool NH, bool OBS, bool COL, typename P>
-__device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairLds& L,
-                                   P pair_base) {
+__device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_waves,
+                                   const PairLds& L, P pair_base) {
     const int t = threadIdx.x;
     if (t == 0) {
         *L.sys = dsc->sys;
@@ -794,6 +797,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
     const int cells = S.lc[0] * S.lc[1] * S.lc[2];
     const int tj = job_threads(n);
     const int nw = blockDim.x >> 6;  // waves of the workgroup (the owners and any others)
+    const int listers = tj * list_waves;  // threads whose waves have a segment
     const int wave = t >> 6;
     double* st = dsc->state;
     const bool col = COL && dsc->field == kFieldColour;  // uniform per job
@@ -849,7 +853,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
     PfSums ps{0.0, 0.0, 0.0, 0.0, 0.0, 0};
     bool ovf = false;
     // forces of the start state
-    pf_rebuild<APT>(S, dxle, dxq, x, y, z, rank, cr, L, seg, seg_cap, tj, cell, &ovf);
+    pf_rebuild<APT>(S, dxle, dxq, x, y, z, rank, cr, L, seg, seg_cap, tj, listers, cell, &ovf);
     if (ovf) health |= kHealthListOverflow;
     ps = pf_forces<OBS>(n, cells, dxq, pair_base, seg_cap);
     __syncthreads();
@@ -988,7 +992,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, const PairL
         ++since;
         const float tsince = (float)(since * h);
         if (2.f * dm + agd * tsince * (reach + 2.f * dm) >= skin) {
-            pf_rebuild<APT>(S, dxle, dxq, x, y, z, rank, cr, L, seg, seg_cap, tj, cell, &ovf);
+            pf_rebuild<APT>(S, dxle, dxq, x, y, z, rank, cr, L, seg, seg_cap, tj, listers, cell, &ovf);
             if (ovf) {  // the same in every thread
                 health |= kHealthListOverflow;
                 break;
@@ -1162,10 +1166,10 @@ __global__ __launch_bounds__(APT == kLargeApt ? kLargeThreads : kPairThreads) vo
         // run_daughter_pairs synchronises before its first use of the counts
         if constexpr (PL)
             run_daughter_pairs<APT, NH, OBS, COL>(
-                d, b.max_steps, L, (lu32*)(pf_smem + kJobBytes + plan_pairs(n, cells).total));
+                d, b.max_steps, b.list_waves, L, (lu32*)(pf_smem + kJobBytes + plan_pairs(n, cells).total));
         else
             run_daughter_pairs<APT, NH, OBS, COL>(
-                d, b.max_steps, L, (gu32*)(b.pairs + (size_t)blockIdx.x * b.pair_stride));
+                d, b.max_steps, b.list_waves, L, (gu32*)(b.pairs + (size_t)blockIdx.x * b.pair_stride));
     }
 }
 
@@ -1209,7 +1213,7 @@ __global__ __launch_bounds__(APT == kLargeApt ? kLargeThreads : kPairThreads) vo
     const int seg_cap = kcap * 64 * APT;
     gu32* seg = (gu32*)(pairs + (size_t)wave * seg_cap);
     bool ovf = false;
-    const int count = pf_rebuild<APT>(S, dxle, dxq, x, y, z, rank, cr, L, seg, seg_cap, tj, cell, &ovf);
+    const int count = pf_rebuild<APT>(S, dxle, dxq, x, y, z, rank, cr, L, seg, seg_cap, tj, tj, cell, &ovf);
     PfSums ps{0.0, 0.0, 0.0, 0.0, 0.0, 0};
     ps = pf_forces<false>(n, cells, dxq, (const gu32*)pairs, seg_cap);
     if ((t & 63) == 0 && t < tj) seg_count[wave] = count;
