@@ -311,4 +311,30 @@ __device__ __forceinline__ uint32_t fix32(double v, double scale) {
     return (uint32_t)(int64_t)rint(v * scale);
 }
 
+// s + e = a + b exactly (Knuth's branch-free two-sum)
+__device__ __forceinline__ void two_sum(double a, double b, double& s, double& e) {
+    s = a + b;
+    const double bp = s - a;
+    e = (a - (s - bp)) + (b - bp);
+}
+
+// Inclusive prefix sum over the 64 lanes of a wave, compensated: on return s + c is the sum
+// of the lane's and all lower lanes' v, each partial carried as a two-sum pair (a fixed
+// combination order, so the result does not depend on timing).
+__device__ __forceinline__ void wave_scan_comp(double v, double& s, double& c) {
+    const int lane = threadIdx.x & 63;
+    s = v;
+    c = 0.0;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const double ls = __shfl_up(s, d, 64), lc = __shfl_up(c, d, 64);
+        if (lane >= d) {
+            double t, e;
+            two_sum(ls, s, t, e);
+            s = t;
+            c = lc + c + e;
+        }
+    }
+}
+
 }  // namespace ttcf

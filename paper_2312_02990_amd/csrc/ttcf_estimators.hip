@@ -12,7 +12,7 @@
 // the jackknife over the rows (start states), in FP64 with compensated sums.
 #include <hip/hip_runtime.h>
 
-#include "ttcf_internal.h"
+#include "ttcf_device.h"
 
 namespace ttcf {
 namespace {
@@ -81,54 +81,60 @@ __global__ void k_response_modified(ModifiedLaunch a) {
     a.out[a.n_t + k] = se;
 }
 
-// one thread per (group, extra column): mapping means of B_c(t_k) and of the trapezoid
-// integral of P_xy(0) B_c(s), compensated per daughter as in the P_xy accumulation
-__global__ void k_accumulate_obs(AccumObsLaunch a) {
+// One workgroup per group, a wave per extra column: mapping means of B_c(t_k) and of the trapezoid
+// integral of P_xy(0) B_c(s). The lanes take 64 time points at a time and sum their trapezoid
+// terms by a compensated prefix scan, as in the P_xy accumulation: the time points are what
+// there is to spread over the chip (64 groups, 201 points: 445 us with a thread per column, one
+// point after the other, 25 us so).
+__global__ __launch_bounds__(64 * kObsCols) void k_accumulate_obs(AccumObsLaunch a) {
     constexpr int kMaps = 4;
-    const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= a.n_groups * kObsCols) return;
-    const int g = id / kObsCols, col = id % kObsCols;
+    const int g = blockIdx.x, lane = threadIdx.x & 63, col = threadIdx.x >> 6;
     const int b = a.first_of[g], e = a.first_of[g + 1];
     const int nm = min(e - b, kMaps);
-    double p0[kMaps], sum[kMaps], comp[kMaps], prev[kMaps];
+    double p0[kMaps], cs[kMaps], cc[kMaps];
     const double* ser[kMaps];
     double dt = 0.0;
     for (int m = 0; m < nm; ++m) {
         const DaughterDesc& d = a.descs[b + m];
-        ser[m] = d.xseries;
+        ser[m] = d.xseries + col;
         dt = d.sys.dt;
         p0[m] = d.series[0] / d.sys.volume;
-        prev[m] = d.xseries[col];
-        sum[m] = 0.0;
-        comp[m] = 0.0;
+        cs[m] = 0.0;
+        cc[m] = 0.0;
     }
     const double inm = 1.0 / (double)nm;
     double* dout = a.d_out + (size_t)g * a.row_stride + (size_t)col * a.stride;
     double* iout = a.i_out + (size_t)g * a.row_stride + (size_t)col * a.stride;
-    double d0 = 0.0;
-    for (int m = 0; m < nm; ++m) d0 += prev[m];
-    dout[0] = d0 * inm;
-    iout[0] = 0.0;
-    for (int k = 1; k < a.n_t; ++k) {
+    for (int k0 = 0; k0 < a.n_t; k0 += 64) {
+        const int k = k0 + lane;
+        const bool live = k < a.n_t, step = live && k > 0;
         double dsum = 0.0, isum = 0.0;
         for (int m = 0; m < nm; ++m) {
-            const double cur = ser[m][(size_t)k * kObsCols + col];
-            comp_add(sum[m], comp[m], 0.5 * dt * (p0[m] * prev[m] + p0[m] * cur));
-            prev[m] = cur;
+            const double cur = live ? ser[m][(size_t)k * kObsCols] : 0.0;
+            const double prev = step ? ser[m][(size_t)(k - 1) * kObsCols] : 0.0;
+            // the trapezoid over [t_{k-1}, t_k] (none at k = 0)
+            const double term = step ? 0.5 * dt * (p0[m] * prev + p0[m] * cur) : 0.0;
+            double s, c, t, err;
+            wave_scan_comp(term, s, c);
+            two_sum(cs[m], s, t, err);
+            const double tc = cc[m] + c + err;
             dsum += cur;
-            isum += sum[m] + comp[m];
+            isum += t + tc;
+            cs[m] = __shfl(t, 63, 64);
+            cc[m] = __shfl(tc, 63, 64);
         }
-        dout[k] = dsum * inm;
-        iout[k] = isum * inm;
+        if (live) {
+            dout[k] = dsum * inm;
+            iout[k] = isum * inm;
+        }
     }
 }
 
 }  // namespace
 
 hipError_t launch_accumulate_obs(const AccumObsLaunch& a, hipStream_t s) {
-    const int total = a.n_groups * kObsCols;
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_accumulate_obs, dim3((total + 63) / 64), dim3(64), 0, s, a);
+    if (a.n_groups <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_accumulate_obs, dim3(a.n_groups), dim3(64 * kObsCols), 0, s, a);
     return hipGetLastError();
 }
 
