@@ -1122,21 +1122,16 @@ int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, b
         // one that owns atoms: they share the force pass, and the list build where their
         // segments fit the LDS too. Results do not depend on it. Measured: 32 daughters of
         // N = 256 over 100 steps, one wave each 1.00 ms, four 0.55; 256 of N = 864 over 200
-        // steps, four waves each 2.92 ms, eight 2.71. A full batch has no wave to spare.
+        // steps, four waves each 2.92 ms, eight 2.63. A full batch has no wave to spare.
         const size_t base = pairs_lds ? nl_lds_pl : nl_lds;
         const int held = std::max(1, std::min((int)(c->max_lds / base), 8 / (threads / 64)));
         const int resident = std::min(held, cu_jobs);
-        int more = 4;
-        while (more > 1 && (threads * more > 512 || more * (threads / 64) * resident > 8)) more /= 2;
-        if (more > 1) {
-            threads *= more;
-            if (!pairs_lds) {
-                list_waves = more;
-            } else {
-                for (list_waves = more; list_waves > 1; list_waves /= 2)
-                    if (lds_lists(list_waves) * resident <= c->max_lds) break;
-                nl_lds_pl = lds_lists(list_waves);
-            }
+        const int own = threads / 64, waves = std::max(own, std::min(4 * own, 8 / resident));
+        threads = 64 * waves;
+        list_waves = waves / own;
+        if (pairs_lds) {
+            while (list_waves > 1 && lds_lists(list_waves) * resident > c->max_lds) --list_waves;
+            nl_lds_pl = lds_lists(list_waves);
         }
         pair_stride *= list_waves;
     }
@@ -3624,7 +3619,7 @@ int32_t ttcf_debug_pair_form(const ttcf_system* sys, double gamma_dot, int64_t k
     std::vector<int32_t> seg(waves), rank(n);
     hipError_t e = hipMemcpyAsync(d_r, r, sizeof(double) * 3 * n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
-        e = launch_debug_pair_form(S, gamma_dot, kstep, d_r, kcap, d_pairs, d_seg, d_cell, d_rank,
+        e = launch_debug_pair_form(S, gamma_dot, kstep, d_r, kcap, waves, 1, d_pairs, d_seg, d_cell, d_rank,
                                    d_start, d_f, d_out, s);
     if (e == hipSuccess) e = hipMemcpyAsync(f, d_f, sizeof(double) * 3 * n, hipMemcpyDeviceToHost, s);
     double o3[3] = {0, 0, 0};
@@ -3759,10 +3754,18 @@ int32_t ttcf_pair_forces_static(const ttcf_system* sys, double gamma_dot, int64_
     const int waves = pair_job_threads(n) / 64;
     // scratch layout (each part 256-byte aligned): pair words, wave counts, cell and rank of
     // every atom, cell starts
-    const int64_t w_pairs = words256(pair_words(n, kcap, pair_job_apt(n)));
-    const int64_t w_seg = words256(waves), w_atoms = words256(n);
-    const int64_t need = w_pairs + w_seg + 2 * w_atoms + words256(C + 1);
-    if (need * 4 > TTCF_STATIC_SCRATCH_BYTES) return TTCF_ESCRATCH;
+    const int64_t words = pair_words(n, kcap, pair_job_apt(n));
+    const int64_t w_atoms = words256(n);
+    auto need = [&](int lists) {
+        return words256(words * lists) + words256(waves * lists) + 2 * w_atoms + words256(C + 1);
+    };
+    if (need(1) * 4 > TTCF_STATIC_SCRATCH_BYTES) return TTCF_ESCRATCH;
+    // one workgroup on an idle chip: up to four waves for each one that owns atoms (N = 256:
+    // 36.4 -> 16.6 us), with pair segments of their own where the scratch has room
+    const int all = std::max(waves, std::min(4 * waves, 8));
+    int lists = all / waves;
+    while (lists > 1 && need(lists) * 4 > TTCF_STATIC_SCRATCH_BYTES) --lists;
+    const int64_t w_pairs = words256(words * lists), w_seg = words256(waves * lists);
     StaticScratch d;
     rc = static_scratch(&d);
     if (rc != TTCF_OK) return rc;
@@ -3772,7 +3775,7 @@ int32_t ttcf_pair_forces_static(const ttcf_system* sys, double gamma_dot, int64_
     int32_t* cell_of = seg + w_seg;
     int32_t* rank_of = cell_of + w_atoms;
     int32_t* start = rank_of + w_atoms;
-    const hipError_t e = launch_debug_pair_form(S, gamma_dot, kstep, r, kcap, pairs, seg,
+    const hipError_t e = launch_debug_pair_form(S, gamma_dot, kstep, r, kcap, all, lists, pairs, seg,
                                                 cell_of, rank_of, start, f, out,
                                                 (hipStream_t)stream);
     return e == hipSuccess ? TTCF_OK : TTCF_EDEVICE;

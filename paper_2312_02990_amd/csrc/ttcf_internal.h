@@ -307,10 +307,11 @@ hipError_t launch_pairs(const BatchLaunch& b, hipStream_t s);
 // (kcap * 64 * apt per wave) and their counts, the forces (3n), out[0] = W_xy, out[1] = 1 if
 // a pair fell inside the guard radius, out[2] = the Lees-Edwards offset used, out[3] = 1 if
 // a wave's pair list outgrew its segment (the list then incomplete).
+// waves: of the workgroup; list_waves: with a segment, for each one that owns atoms
 hipError_t launch_debug_pair_form(const SysDev& S, double gamma_dot, int64_t kstep, const double* r,
-                                  int32_t kcap, uint32_t* pairs, int32_t* seg_count,
-                                  int32_t* cell_of, int32_t* rank_of, int32_t* start, double* f,
-                                  double* out, hipStream_t s);
+                                  int32_t kcap, int32_t waves, int32_t list_waves, uint32_t* pairs,
+                                  int32_t* seg_count, int32_t* cell_of, int32_t* rank_of,
+                                  int32_t* start, double* f, double* out, hipStream_t s);
 
 // device memory through the runtime's allocator (ttcf_set_allocator)
 void* rt_alloc(size_t bytes, hipStream_t s);

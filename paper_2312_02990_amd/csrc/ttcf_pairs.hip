@@ -550,6 +550,12 @@ __device__ __forceinline__ int pf_rebuild(const SysDev& S, double dxle, uint32_t
     int any = 0;
 #pragma unroll
     for (int w = 0; w < kPairThreads / 64; ++w) any |= w < nwb ? L.flags[w] : 0;
+    if (listers > tj) {
+        // segments of waves that own no atoms do not add to what a list may hold
+        int total = 0;
+        for (int w = 0; w < nwb; ++w) total += L.wcnt[w];
+        any |= total > (tj >> 6) * seg_cap ? 1 : 0;
+    }
     *overflow = any != 0;
     return count;
 }
@@ -797,7 +803,8 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
     const int cells = S.lc[0] * S.lc[1] * S.lc[2];
     const int tj = job_threads(n);
     const int nw = blockDim.x >> 6;  // waves of the workgroup (the owners and any others)
-    const int listers = tj * list_waves;  // threads whose waves have a segment
+    // threads whose waves have a segment (eight atoms a thread fill the workgroup)
+    const int listers = APT == kLargeApt ? tj : tj * list_waves;
     const int wave = t >> 6;
     double* st = dsc->state;
     const bool col = COL && dsc->field == kFieldColour;  // uniform per job
@@ -1179,8 +1186,8 @@ __global__ __launch_bounds__(APT == kLargeApt ? kLargeThreads : kPairThreads) vo
 // integrator would use, W_xy, and flags.
 template <int APT>
 __global__ __launch_bounds__(APT == kLargeApt ? kLargeThreads : kPairThreads) void k_debug_pair_form(
-    SysDev Sg, double gamma_dot, int64_t kstep, const double* r, int32_t kcap, uint32_t* pairs,
-    int32_t* seg_count, int32_t* cell_of, int32_t* rank_of, int32_t* start, double* f,
+    SysDev Sg, double gamma_dot, int64_t kstep, const double* r, int32_t kcap, int32_t list_waves,
+    uint32_t* pairs, int32_t* seg_count, int32_t* cell_of, int32_t* rank_of, int32_t* start, double* f,
     double* out) {
     const int cells = Sg.lc[0] * Sg.lc[1] * Sg.lc[2];
     const PairLds L = job_lds(Sg.n, cells);
@@ -1213,10 +1220,16 @@ __global__ __launch_bounds__(APT == kLargeApt ? kLargeThreads : kPairThreads) vo
     const int seg_cap = kcap * 64 * APT;
     gu32* seg = (gu32*)(pairs + (size_t)wave * seg_cap);
     bool ovf = false;
-    const int count = pf_rebuild<APT>(S, dxle, dxq, x, y, z, rank, cr, L, seg, seg_cap, tj, tj, cell, &ovf);
+    int count = 0;
+    // (a list that is too long is cut off as the owners' waves alone cut it off)
+    for (int listers = APT == kLargeApt ? tj : tj * list_waves;; listers = tj) {
+        count = pf_rebuild<APT>(S, dxle, dxq, x, y, z, rank, cr, L, seg, seg_cap, tj, listers, cell, &ovf);
+        if (!ovf || listers == tj) break;
+        __syncthreads();
+    }
     PfSums ps{0.0, 0.0, 0.0, 0.0, 0.0, 0};
     ps = pf_forces<false>(n, cells, dxq, (const gu32*)pairs, seg_cap);
-    if ((t & 63) == 0 && t < tj) seg_count[wave] = count;
+    if ((t & 63) == 0 && t < tj * list_waves) seg_count[wave] = count;
     __syncthreads();
     double m[2] = {ps.w, (double)ps.close};
     pf_block_sum<2>(m, L.red, blockDim.x >> 6);
@@ -1288,22 +1301,25 @@ hipError_t launch_pairs(const BatchLaunch& b, hipStream_t s) {
 }
 
 hipError_t launch_debug_pair_form(const SysDev& S, double gamma_dot, int64_t kstep, const double* r,
-                                  int32_t kcap, uint32_t* pairs, int32_t* seg_count,
-                                  int32_t* cell_of, int32_t* rank_of, int32_t* start, double* f,
-                                  double* out, hipStream_t s) {
-    const int threads = job_threads(S.n);
+                                  int32_t kcap, int32_t waves, int32_t list_waves, uint32_t* pairs,
+                                  int32_t* seg_count, int32_t* cell_of, int32_t* rank_of,
+                                  int32_t* start, double* f, double* out, hipStream_t s) {
+    const int threads = 64 * waves;
+    if (threads > kPairThreads || list_waves < 1 || list_waves * job_threads(S.n) > threads)
+        return hipErrorInvalidValue;
     const size_t lds = lds_bytes_pairs(S.n, S.lc[0] * S.lc[1] * S.lc[2]);
     if (job_apt(S.n) == kSmallApt) {
         (void)hipFuncSetAttribute((const void*)k_debug_pair_form<kSmallApt>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         hipLaunchKernelGGL(k_debug_pair_form<kSmallApt>, dim3(1), dim3(threads), lds, s, S,
-                           gamma_dot, kstep, r, kcap, pairs, seg_count, cell_of, rank_of, start, f,
-                           out);
+                           gamma_dot, kstep, r, kcap, list_waves, pairs, seg_count, cell_of, rank_of,
+                           start, f, out);
     } else {
         (void)hipFuncSetAttribute((const void*)k_debug_pair_form<kLargeApt>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         hipLaunchKernelGGL(k_debug_pair_form<kLargeApt>, dim3(1), dim3(threads), lds, s, S, gamma_dot,
-                           kstep, r, kcap, pairs, seg_count, cell_of, rank_of, start, f, out);
+                           kstep, r, kcap, list_waves, pairs, seg_count, cell_of, rank_of, start,
+                           f, out);
     }
     return hipGetLastError();
 }
