@@ -392,7 +392,9 @@ void mother_shape(const ttcf_ctx* c, const Mother& m, MotherLaunch* L) {
     L->apt = m.apt;
     L->precision = m.sys.precision;
     L->lds_bytes = lds_for(m.dev, m.sys.precision);
-    (void)mother_lists(m.dev, c->max_lds, L);
+    // (a system that fixes its workgroup size asks for the cell form, as for daughters)
+    L->list_lds = 0;
+    if (m.sys.block_threads <= 0) (void)mother_lists(m.dev, c->max_lds, L);
 }
 
 int32_t run_mother(ttcf_ctx* c, Mother& m, double temperature, int64_t n_chunks,

@@ -34,8 +34,8 @@
 // step spends most of its lanes on candidates out of range; a list of about 8 entries per atom of
 // which 5 are in range leaves the pair arithmetic (32 FP64 instructions a pair). Measured on one
 // MI355X against the kernels that scanned the stencil every step: 1024 daughters of N = 2048 over
-// 50 steps, shear 14.97 ms -> 4.14 (2.5e10 atom-steps/s), elongation 15.09 -> 4.02; 256 mixed-flow
-// Nose-Hoover daughters of N = 864 over 100 steps 4.91 -> 1.12. Of a step's time about half is
+// 50 steps, shear 14.97 ms -> 3.80 (2.8e10 atom-steps/s), elongation 15.09 -> 3.64; 256 mixed-flow
+// Nose-Hoover daughters of N = 864 over 100 steps 4.91 -> 1.05. Of a step's time about half is
 // the force pass, a fifth the list builds, the rest the step's scalars and the two barriers.
 
 #include <math.h>

@@ -32,8 +32,8 @@ def state(n, density, seed, slab=False):
     return np.ascontiguousarray(r), I.maxwell_boltzmann(n, TEMP, seed + 1), box
 
 
-def system(T, n, box, rc, precision):
-    return T.make_system(n, box, TEMP, DT, r_cut=rc, precision=precision, nh_tau=TAU,
+def system(T, n, box, rc, precision, threads=0):
+    return T.make_system(n, box, TEMP, DT, r_cut=rc, precision=precision, nh_tau=TAU, block_threads=threads,
                          potential=T.TTCF_WCA if rc == I.WCA_RC else T.TTCF_LJ)
 
 
@@ -80,4 +80,20 @@ def test_fp32_sums_do_not_depend_on_the_lists(T, n):
             out.append(np.concatenate(ctx.ttcf_export_states(mid, 1)))
     # sums of p^2 in another order: 1e-16, grown less than a thousandfold; another order of an
     # FP32 force sum would show at 1e-7
+    assert np.abs(out[0] - out[1]).max() <= 1e-12 * edge
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,density,threads", [(108, 1.1, 128), (500, 0.8442, 512), (1025, 0.8442, 1024)])
+def test_lists_and_cells_agree(T, n, density, threads, precision):
+    """A system that fixes its workgroup size runs in the cell form: the same separations and the
+    same order of every FP32 sum, so the same trajectory but for FP64 sums."""
+    print(f"mother n={n} precision={precision} lists against cells", flush=True)
+    r, p, edge = state(n, density, 7 * n)
+    out = []
+    for t in (0, threads):
+        with T.Context() as ctx:
+            mid = ctx.ttcf_init_mother(system(T, n, edge, I.WCA_RC, precision, t), r, p, n_equil=0)
+            ctx.ttcf_sample_states(mid, 1, 40)
+            out.append(np.concatenate(ctx.ttcf_export_states(mid, 1)))
     assert np.abs(out[0] - out[1]).max() <= 1e-12 * edge
