@@ -242,6 +242,7 @@ hipError_t launch_gemms(const GemmArgs* g, int count, hipStream_t s) {
 __global__ void k_mse_loss(const float* Y, const float* Tg, int64_t count, double* loss) {
     __shared__ double part[256];
     double s = 0.0;
+#pragma unroll 8
     for (int64_t i = threadIdx.x; i < count; i += 256) {
         const double d = (double)Y[i] - (double)Tg[i];
         s += d * d;
@@ -344,15 +345,98 @@ hipError_t launch_col_stats(const float* X, int64_t rows, int cols, float* mu, f
 // ---------------------------------------------------------------------------------------
 // features of mapped start states
 // ---------------------------------------------------------------------------------------
+// Pair sums of atom i: the force, half the pair virials x_ij F_y,ij and half of (p_x,i - p_x,j)
+// F_y,ij. First 64 distances at a time make a bit mask of the partners in range, then its bits, in
+// order: evaluated where they are found, some lane of the wave had a partner in nearly every trip
+// and all of them paid for its division.
+struct CvPairs {
+    double fx, fy, vir, d2;
+};
+
+__device__ __forceinline__ CvPairs cv_pairs(int i, int n, const double* X, const double* Y,
+                                            const double* Z, const double* PX, double lx, double ly,
+                                            double lz, double ilx, double ily, double ilz, double rc2,
+                                            double c_attr) {
+    const double xi = X[i], yi = Y[i], zi = Z[i], pxi = PX[i];
+    CvPairs c{0.0, 0.0, 0.0, 0.0};
+    auto separation = [&](int j, double& dx, double& dy, double& dz) {
+        dx = xi - X[j], dy = yi - Y[j], dz = zi - Z[j];
+        dx -= lx * rint(dx * ilx);
+        dy -= ly * rint(dy * ily);
+        dz -= lz * rint(dz * ilz);
+        return dx * dx + dy * dy + dz * dz;
+    };
+    for (int j0 = 0; j0 < n; j0 += 64) {
+        const int count = min(64, n - j0);
+        uint64_t near = 0;
+        double dx, dy, dz;
+#pragma unroll 4
+        for (int k = 0; k < count; ++k)
+            near |= (uint64_t)(separation(j0 + k, dx, dy, dz) < rc2 ? 1 : 0) << k;
+        if ((unsigned)(i - j0) < 64u) near &= ~(1ull << (i - j0));
+        for (; near != 0; near &= near - 1) {
+            const int j = j0 + __builtin_ctzll(near);
+            const double r2 = separation(j, dx, dy, dz);
+            const double inv2 = 1.0 / r2;
+            const double inv6 = inv2 * inv2 * inv2;
+            const double fs = 24.0 * inv6 * (2.0 * inv6 - c_attr) * inv2;
+            c.fx += fs * dx;
+            c.fy += fs * dy;
+            c.vir += 0.5 * dx * (fs * dy);
+            c.d2 += 0.5 * (pxi - PX[j]) * (fs * dy);
+        }
+    }
+    return c;
+}
+
+// The row's sums, each by one thread in atom order: slab sums of p_x, p_x p_y and the virial in
+// wave 0, the two force-momentum sums in waves 1 and 2. Every atom's slab goes to LDS first (over
+// the z positions, which the pair sums are done with; D2 is read by its sum alone).
+template <typename Put>
+__device__ __forceinline__ void cv_sums(int q, int n, double ly, const double* Y, double* Z,
+                                        const double* PX, const double* PY, const double* FX,
+                                        const double* FY, const double* VIR, const double* D2, Put put) {
+    int* slab = (int*)Z;
+    const double inv = (double)kCvSlabs / ly;
+    for (int a = q; a < n; a += blockDim.x) {
+        const int k = (int)floor(Y[a] * inv);
+        slab[a] = k < 0 ? 0 : (k > kCvSlabs - 1 ? kCvSlabs - 1 : k);
+    }
+    __syncthreads();
+    if (q < 3 * kCvSlabs) {
+        const int own = q % kCvSlabs;
+        const int kind = q / kCvSlabs;  // 0 p_x, 1 p_x p_y, 2 virial
+        const double* u = kind == 2 ? VIR : PX;
+        double acc = 0.0;
+#pragma unroll 8
+        for (int a = 0; a < n; ++a) {
+            const double v = kind == 1 ? u[a] * PY[a] : u[a];
+            acc = slab[a] == own ? acc + v : acc;
+        }
+        put(q, acc);
+    } else if (q == 64) {
+        double acc = 0.0;
+#pragma unroll 8
+        for (int a = 0; a < n; ++a) acc += FX[a] * PY[a] + PX[a] * FY[a];
+        put(3 * kCvSlabs, acc);
+    } else if (q == 128) {
+        double acc = 0.0;
+#pragma unroll 8
+        for (int a = 0; a < n; ++a) acc += D2[a];
+        put(3 * kCvSlabs + 1, acc);
+    }
+}
+
 // Row layout (kCvIn = 64): [P_xy(0), Omega(0); per slab k of kCvSlabs = 20 in y (k = floor(y
 // 20 / Ly) clamped): sum p_x, sum p_x p_y, and half the pair virial x_ij F_y,ij of each of the
 // slab's atoms; then sum_i (F_x,i p_y,i + p_x,i F_y,i) and sum_{i<j} (p_x,i - p_x,j) F_y,ij],
 // all of the mapped start state (Eq. (mappings): x -> -x for mappings 2 and 3, p_x and p_y
 // signs as below). One workgroup of 256 threads per row: the mapped state is staged in LDS,
 // thread q computes the pair terms of atoms q, q + 256, ... against every other atom (each
-// pair seen from both sides, so no atomics), then thread q < 62 forms one sum in atom order
-// (deterministic). FP64 throughout; LDS 9 n doubles. With one wave a row each thread had
-// four atoms' chains in turn (1024 rows of N = 256: 222 us, 140 with four waves).
+// pair seen from both sides, so no atomics), then one thread a sum forms the 62 sums in atom order
+// (deterministic). FP64 throughout; LDS 9 n doubles. 1024 rows of N = 256: one wave a row 222 us, four
+// waves 140, partners found before they are evaluated 113, sums over stored slab numbers on
+// three waves 84.
 __global__ __launch_bounds__(256) void k_cv_features(
     const double* states, int32_t n, const int32_t* state_of, const int32_t* map_of,
     const double* vpxy0, const double* vsign, int32_t rows, double lx, double ly, double lz,
@@ -389,53 +473,15 @@ __global__ __launch_bounds__(256) void k_cv_features(
     // only for separations within rounding of half a box, far beyond r_c)
     const double ilx = 1.0 / lx, ily = 1.0 / ly, ilz = 1.0 / lz;
     for (int i = q; i < n; i += blockDim.x) {
-        const double xi = X[i], yi = Y[i], zi = Z[i], pxi = PX[i];
-        double fx = 0.0, fy = 0.0, vir = 0.0, d2 = 0.0;
-        for (int j = 0; j < n; ++j) {
-            if (j == i) continue;
-            double dx = xi - X[j], dy = yi - Y[j], dz = zi - Z[j];
-            dx -= lx * rint(dx * ilx);
-            dy -= ly * rint(dy * ily);
-            dz -= lz * rint(dz * ilz);
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            if (r2 < rc2) {
-                const double inv2 = 1.0 / r2;
-                const double inv6 = inv2 * inv2 * inv2;
-                const double fs = 24.0 * inv6 * (2.0 * inv6 - c_attr) * inv2;
-                fx += fs * dx;
-                fy += fs * dy;
-                vir += 0.5 * dx * (fs * dy);
-                d2 += 0.5 * (pxi - PX[j]) * (fs * dy);
-            }
-        }
-        FX[i] = fx;
-        FY[i] = fy;
-        VIR[i] = vir;
-        D2[i] = d2;
+        const CvPairs c = cv_pairs(i, n, X, Y, Z, PX, lx, ly, lz, ilx, ily, ilz, rc2, c_attr);
+        FX[i] = c.fx;
+        FY[i] = c.fy;
+        VIR[i] = c.vir;
+        D2[i] = c.d2;
     }
     __syncthreads();
     float* o = out + (size_t)row * kCvIn;
-    if (q < 3 * kCvSlabs) {
-        const int slab = q % kCvSlabs;
-        const int kind = q / kCvSlabs;  // 0 p_x, 1 p_x p_y, 2 virial
-        const double inv = (double)kCvSlabs / ly;
-        double acc = 0.0;
-        for (int a = 0; a < n; ++a) {
-            int k = (int)floor(Y[a] * inv);
-            k = k < 0 ? 0 : (k > kCvSlabs - 1 ? kCvSlabs - 1 : k);
-            if (k != slab) continue;
-            acc += kind == 0 ? PX[a] : (kind == 1 ? PX[a] * PY[a] : VIR[a]);
-        }
-        o[2 + q] = (float)acc;
-    } else if (q == 3 * kCvSlabs) {
-        double acc = 0.0;
-        for (int a = 0; a < n; ++a) acc += FX[a] * PY[a] + PX[a] * FY[a];
-        o[2 + q] = (float)acc;
-    } else if (q == 3 * kCvSlabs + 1) {
-        double acc = 0.0;
-        for (int a = 0; a < n; ++a) acc += D2[a];
-        o[2 + q] = (float)acc;
-    }
+    cv_sums(q, n, ly, Y, Z, PX, PY, FX, FY, VIR, D2, [&](int f, double v) { o[2 + f] = (float)v; });
     if (q == 0) {
         // vpxy0 indexed by row (vsign null) or by state with the mapping's sign of P_xy
         const double vp = vsign ? vpxy0[state_of[row]] * vsign[m] : vpxy0[row];
@@ -482,52 +528,14 @@ __global__ __launch_bounds__(256) void k_cv_features_maps(
     __syncthreads();
     const double ilx = 1.0 / lx, ily = 1.0 / ly, ilz = 1.0 / lz;
     for (int i = q; i < n; i += blockDim.x) {
-        const double xi = X[i], yi = Y[i], zi = Z[i], pxi = PX[i];
-        double fx = 0.0, fy = 0.0, vir = 0.0, d2 = 0.0;
-        for (int j = 0; j < n; ++j) {
-            if (j == i) continue;
-            double dx = xi - X[j], dy = yi - Y[j], dz = zi - Z[j];
-            dx -= lx * rint(dx * ilx);
-            dy -= ly * rint(dy * ily);
-            dz -= lz * rint(dz * ilz);
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            if (r2 < rc2) {
-                const double inv2 = 1.0 / r2;
-                const double inv6 = inv2 * inv2 * inv2;
-                const double fs = 24.0 * inv6 * (2.0 * inv6 - c_attr) * inv2;
-                fx += fs * dx;
-                fy += fs * dy;
-                vir += 0.5 * dx * (fs * dy);
-                d2 += 0.5 * (pxi - PX[j]) * (fs * dy);
-            }
-        }
-        FX[i] = fx;
-        FY[i] = fy;
-        VIR[i] = vir;
-        D2[i] = d2;
+        const CvPairs c = cv_pairs(i, n, X, Y, Z, PX, lx, ly, lz, ilx, ily, ilz, rc2, c_attr);
+        FX[i] = c.fx;
+        FY[i] = c.fy;
+        VIR[i] = c.vir;
+        D2[i] = c.d2;
     }
     __syncthreads();
-    if (q < 3 * kCvSlabs) {
-        const int slab = q % kCvSlabs;
-        const int kind = q / kCvSlabs;  // 0 p_x, 1 p_x p_y, 2 virial
-        const double inv = (double)kCvSlabs / ly;
-        double acc = 0.0;
-        for (int a = 0; a < n; ++a) {
-            int k = (int)floor(Y[a] * inv);
-            k = k < 0 ? 0 : (k > kCvSlabs - 1 ? kCvSlabs - 1 : k);
-            if (k != slab) continue;
-            acc += kind == 0 ? PX[a] : (kind == 1 ? PX[a] * PY[a] : VIR[a]);
-        }
-        feat[q] = acc;
-    } else if (q == 3 * kCvSlabs) {
-        double acc = 0.0;
-        for (int a = 0; a < n; ++a) acc += FX[a] * PY[a] + PX[a] * FY[a];
-        feat[q] = acc;
-    } else if (q == 3 * kCvSlabs + 1) {
-        double acc = 0.0;
-        for (int a = 0; a < n; ++a) acc += D2[a];
-        feat[q] = acc;
-    }
+    cv_sums(q, n, ly, Y, Z, PX, PY, FX, FY, VIR, D2, [&](int f, double v) { feat[f] = v; });
     __syncthreads();
     // row 4 st_i + m: mapping signs p -> -p (m=1); (x, px) -> (-x, -px) (m=2);
     // (x, py, pz) -> -(...) (m=3)
