@@ -1114,25 +1114,41 @@ __global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4) k_flo
 //         order (dz, dy, dx of the cells, index). The list is kept in that order; a lane that meets
 //         a partner in range out of its turn (one in a hundred, each step) has its list sorted
 //         and summed by its wave.
-// What bounds a step is a CU's vector issue: about 70 instructions an entry, of which the longest
-// list of a wave sets the number (13 for a mean of 8). Measured on one MI355X, a step of one
-// mother, cell form -> lists: N = 2048 45.8 -> 28.3 us (FP64 61.7 -> 16.9), N = 1000 24.3 -> 15.0
-// (32.3 -> 9.0); 256 copies of N = 500 sampled over 150 steps 9.6 -> 2.1 ms with their export.
+// What bounds a step is a CU's vector issue in the pair sums, of which the longest list of a wave
+// sets the number of trips (13 for a mean of 8), then the builds (a fifth) and the waves that wait
+// for one with several lanes out of turn. Measured on one MI355X, a step of one mother, cell form
+// -> lists: N = 2048 45.8 -> 27.1 us (FP64 61.7 -> 16.9), N = 1000 24.3 -> 14.6 (32.3 -> 9.0); 256
+// copies of N = 500 sampled over 150 steps 9.6 -> 2.0 ms with their export.
 
 constexpr int kSort32 = 16;  // longest list that is sorted in registers
 constexpr int kMotherAtoms = 2048;  // indexes of 11 bits
 
-// Neighbouring cells of an atom: c - own + 1 on each axis, wrapped; 0..2 for the stencil.
+typedef uint16_t ushort2v __attribute__((ext_vector_type(2)));
+
+// Neighbouring cells of an atom, x and y in one word, z beside the atom's index in another (packed
+// 16-bit arithmetic): c - own + 1 on each axis, wrapped, 0..2 for the stencil. A pair whose cells
+// are further apart is out of range by its separation (a cell is wider than r_c).
 struct Near32 {
-    int nc[3];
-    int before[3];  // own cell - 1
+    ushort2v nc_xy, nc_z;
+    ushort2v before_xy, before_z;  // own cell - 1
     float w[3];
 };
 
-__device__ __forceinline__ uint32_t f32_axis(const Near32& N, int axis, uint32_t packed) {
-    uint32_t d = ((packed >> (6 * axis)) & 63u) - (uint32_t)N.before[axis];
-    d = min(d, d + (uint32_t)N.nc[axis]);
-    return min(d, d - (uint32_t)N.nc[axis]);
+__device__ __forceinline__ ushort2v f32_near(uint32_t cells, ushort2v before, ushort2v nc) {
+    ushort2v d = __builtin_bit_cast(ushort2v, cells) - before;
+    d = __builtin_elementwise_min(d, (ushort2v)(d + nc));
+    return __builtin_elementwise_min(d, (ushort2v)(d - nc));
+}
+
+__device__ __forceinline__ void f32_own(Near32& N, uint32_t xy, uint32_t z) {
+    N.before_xy = __builtin_bit_cast(ushort2v, xy) - ushort2v{1, 1};
+    N.before_z = ushort2v{(uint16_t)((z & 0xFFFFu) - 1u), 0};
+}
+
+// Where a partner's turn comes: (9 tz + 3 ty + tx) 2^11 + its index.
+__device__ __forceinline__ uint32_t f32_turn(ushort2v xy, ushort2v z) {
+    return __builtin_amdgcn_udot2(xy, ushort2v{2048, 6144},
+                                  __builtin_amdgcn_udot2(z, ushort2v{18432, 1}, 0u, false), false);
 }
 
 template <int APT>
@@ -1140,6 +1156,7 @@ __device__ __forceinline__ void f32_publish(const F64Lds& S, const SysDev& sys, 
                                             const uint16_t (&atom)[APT], const double (&x)[APT],
                                             const double (&y)[APT], const double (&z)[APT]) {
     float4* u = (float4*)S.xy;
+    uint32_t* uz = (uint32_t*)S.z;
 #pragma unroll
     for (int j = 0; j < APT; ++j) {
         const int a = threadIdx.x + j * blockDim.x;
@@ -1150,7 +1167,8 @@ __device__ __forceinline__ void f32_publish(const F64Lds& S, const SysDev& sys, 
             u[a] = make_float4((float)(x[j] - (double)cx * sys.w[0]),
                                (float)(y[j] - (double)cy * sys.w[1]),
                                (float)(z[j] - (double)cz * sys.w[2]),
-                               __int_as_float(cx | (cy << 6) | (cz << 12) | (atom[j] << 18)));
+                               __int_as_float(cx | (cy << 16)));
+            uz[a] = (uint32_t)cz | ((uint32_t)atom[j] << 16);
         }
     }
 }
@@ -1165,13 +1183,13 @@ struct Pair32 {
 
 // One pair's separation and force over it; whether it is in range (the force is 0 if not).
 __device__ __forceinline__ bool f32_separation(Pair32& d, const Near32& N, const float4& ui,
-                                               const float4& uj, uint32_t tx, uint32_t ty, uint32_t tz,
-                                               bool live, float rc2, float ca) {
-    d.x = (ui.x - uj.x) + N.w[0] * (1.0f - (float)tx);
-    d.y = (ui.y - uj.y) + N.w[1] * (1.0f - (float)ty);
-    d.z = (ui.z - uj.z) + N.w[2] * (1.0f - (float)tz);
+                                               const float4& uj, ushort2v xy, ushort2v z, bool live,
+                                               float rc2, float ca) {
+    d.x = (ui.x - uj.x) + N.w[0] * (1.0f - (float)xy.x);
+    d.y = (ui.y - uj.y) + N.w[1] * (1.0f - (float)xy.y);
+    d.z = (ui.z - uj.z) + N.w[2] * (1.0f - (float)z.x);
     const float r2 = d.x * d.x + d.y * d.y + d.z * d.z;
-    const bool in = live & (max(tx, max(ty, tz)) <= 2u) & (r2 < rc2);
+    const bool in = live & (r2 < rc2);
     const float inv = recip(r2);
     const float s3 = inv * inv * inv;
     d.fs = in ? s3 * (48.0f * s3 - 24.0f * ca) * inv : 0.0f;
@@ -1186,10 +1204,9 @@ __device__ __forceinline__ void f32_add(Sum32& g, const Pair32& d) {
 }
 
 __device__ __forceinline__ bool f32_pair(Sum32& g, const Near32& N, const float4& ui, const float4& uj,
-                                         uint32_t tx, uint32_t ty, uint32_t tz, bool live, float rc2,
-                                         float ca) {
+                                         ushort2v xy, ushort2v z, bool live, float rc2, float ca) {
     Pair32 d;
-    const bool in = f32_separation(d, N, ui, uj, tx, ty, tz, live, rc2, ca);
+    const bool in = f32_separation(d, N, ui, uj, xy, z, live, rc2, ca);
     f32_add(g, d);
     return in;
 }
@@ -1200,6 +1217,7 @@ __device__ __forceinline__ void f32_forces(const F64Lds& S, const SysDev& sys, i
                                            float (&fy)[APT], float (&fz)[APT], double& w0) {
     const int t = threadIdx.x, T = blockDim.x;
     const float4* u = (const float4*)S.xy;
+    const uint32_t* uz = (const uint32_t*)S.z;
     const float rc2 = (float)sys.rc2, ca = (float)sys.c_attr;
     const int stride = T * APT;
     double wacc = 0.0;
@@ -1210,40 +1228,38 @@ __device__ __forceinline__ void f32_forces(const F64Lds& S, const SysDev& sys, i
         const int me = own ? a : 0;
         const float4 ui = u[me];
         Near32 N;
+        N.nc_xy = ushort2v{(uint16_t)sys.nc[0], (uint16_t)sys.nc[1]};
+        N.nc_z = ushort2v{(uint16_t)sys.nc[2], 0};
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            N.nc[q] = sys.nc[q];
-            N.w[q] = (float)sys.w[q];
-            N.before[q] = ((__float_as_int(ui.w) >> (6 * q)) & 63) - 1;
-        }
+        for (int q = 0; q < 3; ++q) N.w[q] = (float)sys.w[q];
+        f32_own(N, __float_as_uint(ui.w), uz[me]);
         uint16_t* list = S.list + (t * APT + j);
         const bool over = own && nh[j] > kF64Cap;
         const int len = over || !own ? 0 : nh[j];
-        // where a partner's turn comes
-        auto turn = [&](uint32_t tx, uint32_t ty, uint32_t tz, uint32_t pk) {
-            return ((tz * 9u + ty * 3u + tx) << 11) | (pk >> 18);
-        };
         auto turn_of = [&](int id) {
-            const uint32_t pk = __float_as_uint(u[id].w);
-            return turn(min(f32_axis(N, 0, pk), 3u), min(f32_axis(N, 1, pk), 3u),
-                        min(f32_axis(N, 2, pk), 3u), pk);
+            return f32_turn(f32_near(__float_as_uint(u[id].w), N.before_xy, N.nc_xy),
+                            f32_near(uz[id], N.before_z, N.nc_z));
         };
         Sum32 g{0.f, 0.f, 0.f, 0.f};
         // the list in order; true if a partner in range came after one whose turn is later
         auto pass = [&](int count) {
             bool late = false;
             uint32_t last = 0;
-            float4 v = u[0 < count ? list[0] : me];
+            const int first = 0 < count ? list[0] : me;
+            float4 v = u[first];
+            uint32_t vz = uz[first];
             int idn = 1 < count ? list[stride] : me;
             for (int k = 0; __builtin_amdgcn_ballot_w64(k < count) != 0; ++k) {
                 const float4 uj = v;
+                const uint32_t ujz = vz;
                 v = u[idn];
+                vz = uz[idn];
                 const int ahead = list[min(k + 2, kF64Cap - 1) * stride];
                 idn = k + 2 < count ? ahead : me;
-                const uint32_t pk = __float_as_uint(uj.w);
-                const uint32_t tx = f32_axis(N, 0, pk), ty = f32_axis(N, 1, pk), tz = f32_axis(N, 2, pk);
-                const bool in = f32_pair(g, N, ui, uj, tx, ty, tz, k < count, rc2, ca);
-                const uint32_t at = turn(tx, ty, tz, pk);
+                const ushort2v xy = f32_near(__float_as_uint(uj.w), N.before_xy, N.nc_xy);
+                const ushort2v z = f32_near(ujz, N.before_z, N.nc_z);
+                const bool in = f32_pair(g, N, ui, uj, xy, z, k < count, rc2, ca);
+                const uint32_t at = f32_turn(xy, z);
                 late = late | (in & (at < last));
                 last = in ? at : last;
             }
@@ -1302,25 +1318,27 @@ __device__ __forceinline__ void f32_forces(const F64Lds& S, const SysDev& sys, i
             uint16_t* row = S.list + ((t - lane + b) * APT + j);
             const float4 ub = u[it];
             Near32 B = N;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) B.before[q] = ((__float_as_int(ub.w) >> (6 * q)) & 63) - 1;
+            f32_own(B, __float_as_uint(ub.w), uz[it]);
             const bool live = lane < count;
             const int id = live ? row[lane * stride] : it;
-            const float4 uj = u[id];
-            const uint32_t pk = __float_as_uint(uj.w);
-            const uint32_t tx = f32_axis(B, 0, pk), ty = f32_axis(B, 1, pk), tz = f32_axis(B, 2, pk);
-            const uint32_t at = (turn(min(tx, 3u), min(ty, 3u), min(tz, 3u), pk) << 1) | (live ? 0u : 1u);
+            const uint32_t at = f32_turn(f32_near(__float_as_uint(u[id].w), B.before_xy, B.nc_xy),
+                                         f32_near(uz[id], B.before_z, B.nc_z));
             int rank = 0;
             for (int q = 0; q < count; ++q)
                 rank += (uint32_t)__builtin_amdgcn_readlane((int)at, q) < at ? 1 : 0;
             if (live) row[rank * stride] = (uint16_t)id;
+            // (one wave's LDS operations complete in order; the other lanes' stores are news to
+            // the compiler)
+            __builtin_amdgcn_wave_barrier();
+            asm volatile("" ::: "memory");
+            const int mine = live ? row[lane * stride] : it;
+            const float4 uj = u[mine];
             Pair32 d;
-            const bool in = f32_separation(d, B, ub, uj, tx, ty, tz, live, rc2, ca);
+            const bool in = f32_separation(d, B, ub, uj, f32_near(__float_as_uint(uj.w), B.before_xy, B.nc_xy),
+                                           f32_near(uz[mine], B.before_z, B.nc_z), live, rc2, ca);
             Sum32 sum{0.f, 0.f, 0.f, 0.f};
-            for (int q = 0; q < count; ++q) {
-                const uint64_t who = __builtin_amdgcn_ballot_w64(in & (rank == q));
-                if (who == 0) continue;
-                const int w = __builtin_ctzll(who);
+            for (uint64_t hits = __builtin_amdgcn_ballot_w64(in); hits != 0; hits &= hits - 1) {
+                const int w = __builtin_ctzll(hits);
                 auto of = [&](float v) {
                     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), w));
                 };
@@ -1335,10 +1353,10 @@ __device__ __forceinline__ void f32_forces(const F64Lds& S, const SysDev& sys, i
 #pragma unroll 1
                 for (int m = 0; m < n; ++m) {
                     const float4 uj = u[m];
-                    const uint32_t pk = __float_as_uint(uj.w);
-                    const uint32_t tx = f32_axis(N, 0, pk), ty = f32_axis(N, 1, pk), tz = f32_axis(N, 2, pk);
-                    const bool turn_now = tz * 9u + ty * 3u + tx == (uint32_t)c;
-                    (void)f32_pair(g, N, ui, uj, tx, ty, tz, over & (m != me) & turn_now, rc2, ca);
+                    const ushort2v xy = f32_near(__float_as_uint(uj.w), N.before_xy, N.nc_xy);
+                    const ushort2v z = f32_near(uz[m], N.before_z, N.nc_z);
+                    const bool now = max(xy.x, max(xy.y, z.x)) <= 2 && z.x * 9 + xy.y * 3 + xy.x == c;
+                    (void)f32_pair(g, N, ui, uj, xy, z, over & (m != me) & now, rc2, ca);
                 }
         }
         fx[j] = own ? g.x : 0.0f;
