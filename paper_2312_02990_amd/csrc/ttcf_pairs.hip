@@ -724,13 +724,18 @@ __device__ __forceinline__ void pf_record_obs(const SysDev& S, const double (&y)
 // ---------------------------------------------------------------------------------------
 
 // Eight atoms a thread leave few vector registers: what spills went to scratch and back made up a
-// third of that build's step (64 states x 4 mappings of N = 4000 over 200 steps: 7.8 ms, 5.0 with
-// the two functions below). With four atoms a thread they are not needed (the moves of the first cost
-// 0.8% of the N = 2048 batch).
+// third of that build's step. The two functions below are used where they gain (64 states x 4
+// mappings of N = 4000 over 100 steps, none, the first, the second, both; spilled registers):
+//   isokinetic                  3.91  3.56  3.21  2.64 ms (258, 209, 145, 84): both
+//   Nose-Hoover                 3.36  3.64  3.26  4.51 ms (183, 217, 116, 268): the second
+//   isokinetic, observables     4.52  4.86  5.79  5.75 ms (372, 340, 358, 333): none
+//   Nose-Hoover, observables    5.47  5.64  5.58  5.70 ms (387, 382, 330, 360): none
+// (colour field: as without it). With four atoms a thread they are not needed (the moves of the
+// first cost 0.8% of the N = 2048 batch).
 // A step's scalars, the same in every lane, in scalar registers.
-template <int APT>
+template <bool ON>
 __device__ __forceinline__ double uniform(double v) {
-    if constexpr (APT != kLargeApt) return v;
+    if constexpr (!ON) return v;
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
@@ -739,9 +744,9 @@ __device__ __forceinline__ double uniform(double v) {
 
 // Makes the compiler forget the FP64 values of FP32 forces, which it keeps beside them from one use
 // to the next otherwise (six registers an atom).
-template <int APT>
+template <bool ON>
 __device__ __forceinline__ void forget_promoted(float& fx, float& fy, float& fz) {
-    if constexpr (APT == kLargeApt) asm volatile("" : "+v"(fx), "+v"(fy), "+v"(fz));
+    if constexpr (ON) asm volatile("" : "+v"(fx), "+v"(fy), "+v"(fz));
 }
 
 // Publish the owned atoms' fixed-point positions (unwrapped by their crossing counts) and
@@ -805,6 +810,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
     const int nw = blockDim.x >> 6;  // waves of the workgroup (the owners and any others)
     // threads whose waves have a segment (eight atoms a thread fill the workgroup)
     const int listers = APT == kLargeApt ? tj : tj * list_waves;
+    constexpr bool kUni = APT == kLargeApt && !NH && !OBS, kForget = APT == kLargeApt && !OBS;
     const int wave = t >> 6;
     double* st = dsc->state;
     const bool col = COL && dsc->field == kFieldColour;  // uniform per job
@@ -900,7 +906,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
                  (double)fz[j] * (double)fz[j];
     }
 #pragma unroll
-    for (int j = 0; j < APT; ++j) forget_promoted<APT>(fx[j], fy[j], fz[j]);
+    for (int j = 0; j < APT; ++j) forget_promoted<kForget>(fx[j], fy[j], fz[j]);
     pf_block_sum<8>(m0, L.red, nw);
     if (m0[7] != 0.0) health |= kHealthForceRange;
     if (done == 0) {
@@ -910,8 +916,8 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
         if (OBS && xs) pf_record_obs<APT>(S, y, px, py, pz, ps, xs, 0, L, nw);
     }
     if (health != 0) todo = 0;
-    const double sqrt2k0 = uniform<APT>(sqrt(2.0 * k0));
-    const double h = uniform<APT>(S.dt), tau = uniform<APT>(0.5 * h), tg = uniform<APT>(tau * gd);
+    const double sqrt2k0 = uniform<kUni>(sqrt(2.0 * k0));
+    const double h = uniform<kUni>(S.dt), tau = uniform<kUni>(0.5 * h), tg = uniform<kUni>(tau * gd);
     const float hpath = (float)h * (1.f + 0x1p-20f);
     const float reach = (float)S.rc;
     const float skin = (float)S.skin;
@@ -919,8 +925,8 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
     int since = 0;
     // First half of a step from the end-of-step moments pp, pxpy, pypy, fp, fxpy, ff (F the
     // current forces): p -> e p + g p_y x_hat + hh F.
-    double pp = uniform<APT>(m0[0]), pxpy = uniform<APT>(m0[1]), pypy = uniform<APT>(m0[2]);
-    double fp = uniform<APT>(m0[3]), fxpy = uniform<APT>(m0[4]), ff = uniform<APT>(m0[5]);
+    double pp = uniform<kUni>(m0[0]), pxpy = uniform<kUni>(m0[1]), pypy = uniform<kUni>(m0[2]);
+    double fp = uniform<kUni>(m0[3]), fxpy = uniform<kUni>(m0[4]), ff = uniform<kUni>(m0[5]);
     auto first_half = [&](double& e, double& g, double& hh) {
         if (NH) {
             zt += tau * (pp - nh_tgt) * nh_iq;
@@ -955,7 +961,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
 
     // the offset of the next step, computed a step ahead where its dependent chain overlaps
     // the kick scalars' chain
-    const double ilx = uniform<APT>(1.0 / S.box[0]);
+    const double ilx = uniform<kUni>(1.0 / S.box[0]);
     double dxle_n = le_offset_nb(S, gd, k + 1, ilx);
     uint32_t dxq_n = fix32(dxle_n, S.fix_scale[0]);
     for (int step = 0; step < todo; ++step) {
@@ -963,7 +969,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
         k += 1;
         dxle = dxle_n;
         dxq = dxq_n;
-        const double lx = uniform<APT>(S.box[0]), ly = uniform<APT>(S.box[1]), lz = uniform<APT>(S.box[2]);
+        const double lx = uniform<kUni>(S.box[0]), ly = uniform<kUni>(S.box[1]), lz = uniform<kUni>(S.box[2]);
 #pragma unroll
         for (int j = 0; j < APT; ++j) {
             const double vx = px[j] + tg * py[j];
@@ -1016,7 +1022,7 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
         double m[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, ps.w, (double)ps.close};
 #pragma unroll
         for (int j = 0; j < APT; ++j) {
-            forget_promoted<APT>(fx[j], fy[j], fz[j]);
+            forget_promoted<kForget>(fx[j], fy[j], fz[j]);
             const double w1 = (COL && col) ? charge(j) : py[j];  // as for m0
             m[0] += px[j] * px[j] + py[j] * py[j] + pz[j] * pz[j] + 0.0 * (x[j] + y[j] + z[j]);
             m[1] += w1 * px[j];
@@ -1031,11 +1037,11 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
                     (double)fz[j] * (double)fz[j];
         }
 #pragma unroll
-        for (int j = 0; j < APT; ++j) forget_promoted<APT>(fx[j], fy[j], fz[j]);
+        for (int j = 0; j < APT; ++j) forget_promoted<kForget>(fx[j], fy[j], fz[j]);
         pf_block_sum12(m, L.red, nw);
         // ---- second half: p_end = A p + B F + (C p_y + D F_y) x_hat, end-of-step moments
 #pragma unroll
-        for (int q = 0; q < 12; ++q) m[q] = uniform<APT>(m[q]);
+        for (int q = 0; q < 12; ++q) m[q] = uniform<kUni>(m[q]);
         double A, B, C, D, vpxy;
         bool drift = false;
         if (NH) {
@@ -1103,13 +1109,13 @@ __device__ void run_daughter_pairs(DaughterDesc* dsc, int steps_cap, int list_wa
             break;
         }
         // ---- the next step's first half, applied together with this second half
-        dxle_n = uniform<APT>(le_offset_nb(S, gd, k + 1, ilx));
-        for (double* q : {&pp, &pxpy, &pypy, &fp, &fxpy, &zt, &A, &B, &C, &D}) *q = uniform<APT>(*q);
+        dxle_n = uniform<kUni>(le_offset_nb(S, gd, k + 1, ilx));
+        for (double* q : {&pp, &pxpy, &pypy, &fp, &fxpy, &zt, &A, &B, &C, &D}) *q = uniform<kUni>(*q);
         dxq_n = fix32(dxle_n, S.fix_scale[0]);
         double e, g, hh;
         first_half(e, g, hh);
-        const double K1 = uniform<APT>(e * A), K2 = uniform<APT>(e * C + g * A);
-        const double K3 = uniform<APT>(e * B + hh), K4 = uniform<APT>(e * D + g * B);
+        const double K1 = uniform<kUni>(e * A), K2 = uniform<kUni>(e * C + g * A);
+        const double K3 = uniform<kUni>(e * B + hh), K4 = uniform<kUni>(e * D + g * B);
 #pragma unroll
         for (int j = 0; j < APT; ++j) {
             const double qx = K1 * px[j] + K2 * py[j] + K3 * fxd(j) + K4 * (double)fy[j];
