@@ -177,7 +177,7 @@ struct ttcf_ctx {
     std::vector<char> row_x;
     // external field of each accumulated row (kFieldShear or kFieldColour)
     std::vector<int32_t> row_field;
-    // pair-list form: the pair lists of the persistent workgroups (global scratch)
+    // global scratch of the persistent workgroups' lists
     uint32_t* nl_scratch = nullptr;
     size_t nl_scratch_bytes = 0;
     // learned control variate
@@ -387,6 +387,18 @@ int32_t upload_mother_launches(ttcf_ctx* c, const MotherLaunch* ls, int32_t coun
     return TTCF_OK;
 }
 
+// The context's list scratch, grown (after the stream drains) to `bytes`; launches on the context's
+// stream take turns in it.
+int32_t ensure_nl_scratch(ttcf_ctx* c, size_t bytes) {
+    if (bytes <= c->nl_scratch_bytes) return TTCF_OK;
+    HIPCHECK(c, hipStreamSynchronize(c->stream));
+    dev_free(c->nl_scratch);
+    c->nl_scratch = (uint32_t*)dev_alloc(bytes, c->stream);
+    c->nl_scratch_bytes = c->nl_scratch ? bytes : 0;
+    if (!c->nl_scratch) return fail(c, TTCF_ENOMEM, "list scratch allocation failed");
+    return TTCF_OK;
+}
+
 void mother_shape(const ttcf_ctx* c, const Mother& m, MotherLaunch* L) {
     L->threads = m.threads;
     L->apt = m.apt;
@@ -395,6 +407,17 @@ void mother_shape(const ttcf_ctx* c, const Mother& m, MotherLaunch* L) {
     // (a system that fixes its workgroup size asks for the cell form, as for daughters)
     L->list_lds = 0;
     if (m.sys.block_threads <= 0) (void)mother_lists(m.dev, c->max_lds, L);
+}
+
+// Launches mothers whose launch blocks are on the device, with the context's list scratch.
+int32_t run_mothers(ttcf_ctx* c, int32_t count, MotherLaunch& shape) {
+    if (shape.list_lds > 0) {
+        const int32_t rc = ensure_nl_scratch(c, flow64_ext_bytes(shape.list_threads, shape.list_apt, count));
+        if (rc != TTCF_OK) return rc;
+        shape.ext = (uint16_t*)c->nl_scratch;
+    }
+    HIPCHECK(c, launch_mothers(c->d_mlaunch, count, shape, c->stream));
+    return TTCF_OK;
 }
 
 int32_t run_mother(ttcf_ctx* c, Mother& m, double temperature, int64_t n_chunks,
@@ -420,8 +443,8 @@ int32_t run_mother(ttcf_ctx* c, Mother& m, double temperature, int64_t n_chunks,
     }
     mother_shape(c, m, &L);
     int32_t rc = upload_mother_launches(c, &L, 1);
+    if (rc == TTCF_OK) rc = run_mothers(c, 1, L);
     if (rc != TTCF_OK) return rc;
-    HIPCHECK(c, launch_mothers(c->d_mlaunch, 1, L, c->stream));
     m.steps += total;
     return TTCF_OK;
 }
@@ -1238,15 +1261,11 @@ int32_t apply_shape(ttcf_ctx* c, const StepShape& e, int precision, DaughterDesc
     return TTCF_OK;
 }
 
-// The context's pair-list scratch, grown (after the stream drains) to `bytes`.
-int32_t ensure_nl_scratch(ttcf_ctx* c, size_t bytes) {
-    if (bytes <= c->nl_scratch_bytes) return TTCF_OK;
-    HIPCHECK(c, hipStreamSynchronize(c->stream));
-    dev_free(c->nl_scratch);
-    c->nl_scratch = (uint32_t*)dev_alloc(bytes, c->stream);
-    c->nl_scratch_bytes = c->nl_scratch ? bytes : 0;
-    if (!c->nl_scratch) return fail(c, TTCF_ENOMEM, "list scratch allocation failed");
-    return TTCF_OK;
+// Global scratch of a launch's lists.
+size_t list_scratch_bytes(const BatchLaunch& L) {
+    if (L.flow64) return flow64_ext_bytes(L.threads, L.apt, L.grid);
+    return L.variant == kVariantCells || L.pairs_lds ? 0
+               : sizeof(uint32_t) * (size_t)L.grid * (size_t)L.pair_stride;
 }
 
 // Advances the live daughters selected by `only` (all when null) by up to n_steps. `force`
@@ -1340,8 +1359,8 @@ int32_t step_impl(ttcf_ctx* c, int32_t n_steps, const std::vector<char>* only,
         rc = plan_group(c, ds, !force && !c->shape_explicit && !block_explicit, form == 1 ? kVariantCells : kVariantNeighbourList,
                         precision, n_steps, eff[group[0]].threads, &L);
         if (rc != TTCF_OK) return rc;
-        if (form != 1 && !L.pairs_lds) {
-            rc = ensure_nl_scratch(c, sizeof(uint32_t) * (size_t)L.grid * (size_t)L.pair_stride);
+        if (list_scratch_bytes(L) > 0) {
+            rc = ensure_nl_scratch(c, list_scratch_bytes(L));
             if (rc != TTCF_OK) return rc;
             L.pairs = c->nl_scratch;
         }
@@ -1385,6 +1404,9 @@ int32_t step_impl(ttcf_ctx* c, int32_t n_steps, const std::vector<char>* only,
         P.grid = f.grid;
         P.cmax = f.cmax;
         P.queue = c->d_queue;
+        rc = ensure_nl_scratch(c, flow64_ext_bytes(P.threads, P.apt, P.grid));
+        if (rc != TTCF_OK) return rc;
+        P.ext = (uint16_t*)c->nl_scratch;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (timing) {
             HIPCHECK(c, hipEventCreate(&e0));
@@ -2212,9 +2234,13 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
                 L.snapshots = nullptr;
             }
             rc = upload_mother_launches(c, P.ml.data(), P.n_copies);
+            if (rc == TTCF_OK) rc = run_mothers(c, P.n_copies, P.ml[0]);
             if (rc != TTCF_OK) return bail(rc, c->err);
-            if (launch_mothers(c->d_mlaunch, P.n_copies, P.ml[0], c->stream) != hipSuccess)
-                return bail(TTCF_EDEVICE, "decorrelation launch failed");
+        }
+        if (P.ml[0].list_lds > 0) {  // the graph owns the scratch its replays use
+            P.ml[0].ext = (uint16_t*)g->get(
+                flow64_ext_bytes(P.ml[0].list_threads, P.ml[0].list_apt, P.n_copies));
+            if (!P.ml[0].ext) return bail(TTCF_ENOMEM, "list scratch allocation failed");
         }
         for (int r = 0; r < P.n_copies; ++r) {
             P.ml[r].n_chunks = gd->states_per_replica;
@@ -2302,10 +2328,10 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
         rc = plan_group(c, hp, !c->shape_explicit && !block_explicit, form == 1 ? kVariantCells : kVariantNeighbourList,
                         precision, n_steps, threads_req, &B);
         if (rc != TTCF_OK) return bail(rc, c->err);
-        if (form != 1 && !B.pairs_lds) {
-            // the graph owns the pair-list scratch its replays use
-            B.pairs = (uint32_t*)g->get(sizeof(uint32_t) * (size_t)B.grid * (size_t)B.pair_stride);
-            if (!B.pairs) return bail(TTCF_ENOMEM, "pair-list scratch allocation failed");
+        if (list_scratch_bytes(B) > 0) {
+            // the graph owns the list scratch its replays use
+            B.pairs = (uint32_t*)g->get(list_scratch_bytes(B));
+            if (!B.pairs) return bail(TTCF_ENOMEM, "list scratch allocation failed");
         }
         B.descs = descs;
         B.order = order + offset;
@@ -2756,9 +2782,7 @@ struct Replicas {
             ls[r].snap_zeta = zsnaps ? zsnaps + (size_t)r * (size_t)n_chunks : nullptr;
         }
         int32_t rc = upload_mother_launches(c, ls.data(), count);
-        if (rc != TTCF_OK) return rc;
-        HIPCHECK(c, launch_mothers(c->d_mlaunch, count, ls[0], c->stream));
-        return TTCF_OK;
+        return rc != TTCF_OK ? rc : run_mothers(c, count, ls[0]);
     }
 
     int32_t sample(ttcf_ctx* c, int32_t per_copy, int64_t between, double* snaps,

@@ -226,7 +226,8 @@ __device__ __forceinline__ void block_sum(double (&v)[K], double* red) {
 }
 
 // Exclusive scan of cnt[0..C) into start[0..C) (and into cnt as placement cursors).
-__device__ __forceinline__ void scan_cells(int32_t* cnt, int32_t* start, int C, int32_t* ws) {
+template <typename Start>
+__device__ __forceinline__ void scan_cells(int32_t* cnt, Start* start, int C, int32_t* ws) {
     const int T = blockDim.x, t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6, nw = T >> 6;
     const int chunk = (C + T - 1) / T;
@@ -254,7 +255,7 @@ __device__ __forceinline__ void scan_cells(int32_t* cnt, int32_t* start, int C, 
     int run = ws[wave] + x - local;
     for (int c = b; c < e; ++c) {
         int v = cnt[c];
-        start[c] = run;
+        start[c] = (Start)run;
         cnt[c] = run;
         run += v;
     }

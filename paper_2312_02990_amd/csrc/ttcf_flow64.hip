@@ -26,7 +26,11 @@
 // coordinates). The atoms go to the threads in the cell order of the call's start, which atoms
 // leave slowly, so a wave's lanes work on neighbours: their list builds read the same cells.
 // Each atom has the list of every atom within r_c + skin of it, built from a cell grid and kept
-// until the atoms may have moved too far (f64_fresh). A list holds both sides of a pair, so each
+// until the atoms may have moved too far (f64_fresh). The first 24 entries lie in LDS; clustered
+// systems have more, the rest in global scratch, up to 128 in all; an atom with more still looks its
+// partners up in the build's grid every step. (64 FP64 daughters of N = 600 in a dense slab, r_c =
+// 1.75, density 0.45, over 50 steps: 1.1 ms so; 3.6 in the cell form; 9.5 with the atoms past 24
+// entries tried against every other atom.) A list holds both sides of a pair, so each
 // force is one thread's sum in list order: results are deterministic (they follow the rebuilds,
 // so splitting a run over calls changes roundings).
 //
@@ -47,7 +51,8 @@
 namespace ttcf {
 namespace {
 
-constexpr int kF64Cap = 24;        // list entries per atom
+constexpr int kF64Cap = 24;        // list entries per atom in LDS
+constexpr int kF64Ext = 104;       // and further ones in global scratch
 constexpr double kF64Skin = 0.15;   // list skin, in units of r_c (0.12: +5%, 0.2: +1%)
 constexpr int kF64Red = 16;        // doubles per wave in the reduction scratch
 constexpr int kF64Side = 4;        // atoms of a thread whose pairs are evaluated side by side
@@ -71,14 +76,13 @@ __host__ __device__ inline F64Plan f64_plan(int nmax, int cmax, int threads, int
     };
     p.xy = take(2 * sizeof(double) * (size_t)nmax);
     p.z = take(sizeof(double) * (size_t)nmax);
-    p.start = take(sizeof(int32_t) * (size_t)(cmax + 1));
-    // the build's counts and ids live in the list's bytes until the list is written
-    const size_t cnt = f64_align(sizeof(int32_t) * (size_t)cmax);
-    const size_t build = cnt + sizeof(uint16_t) * (size_t)nmax;
+    p.start = take(sizeof(uint16_t) * (size_t)(cmax + 1));
+    p.sid = take(sizeof(uint16_t) * (size_t)nmax);
+    // the build's counts live in the list's bytes until the list is written
+    const size_t cnt = sizeof(int32_t) * (size_t)cmax;
     const size_t list = sizeof(uint16_t) * (size_t)kF64Cap * threads * apt;
-    p.list = take(list > build ? list : build);
+    p.list = take(list > cnt ? list : cnt);
     p.cnt = p.list;
-    p.sid = p.list + cnt;
     p.red = take(sizeof(double) * kF64Red * kMaxWaves);
     p.wmax = take(sizeof(float) * kMaxWaves);
     p.scan = take(sizeof(int32_t) * kMaxWaves);
@@ -88,26 +92,29 @@ __host__ __device__ inline F64Plan f64_plan(int nmax, int cmax, int threads, int
 }
 
 typedef __attribute__((address_space(1))) double GlobalF64;
+typedef __attribute__((address_space(1))) uint16_t GlobalU16;
 
 struct F64Lds {
     double2* xy;       // [nmax] positions; during a build the same bytes hold
     double* z;         //        float4 sorted[nmax]
-    int32_t* start;    // [cells + 1] first sorted slot of each cell
-    int32_t* cnt;      // [cells] counts, then cursors (build only)
-    uint16_t* sid;     // [nmax] atoms by cell (build only)
+    uint16_t* start;   // [cells + 1] first sorted slot of each cell of the last build
+    uint16_t* sid;     // [nmax] its atoms by cell
+    int32_t* cnt;      // [cells] counts (build only)
     uint16_t* list;    // [kF64Cap][threads][APT]
     double* red;       // [waves][kF64Red]
     float* wmax;       // [waves]
     int32_t* scan;     // [waves]
-    int32_t* misc;     // [0]: an atom's list outgrew its capacity; [1]: the job
+    int32_t* misc;     // [0]: the job
+    GlobalU16* ext;    // [kF64Ext][threads][APT]: list entries from kF64Cap on
 };
 
-__device__ __forceinline__ F64Lds f64_carve(char* base, int nmax, int cmax, int threads, int apt) {
+__device__ __forceinline__ F64Lds f64_carve(char* base, uint16_t* ext, int nmax, int cmax, int threads,
+                                            int apt) {
     const F64Plan p = f64_plan(nmax, cmax, threads, apt);
     F64Lds S;
     S.xy = (double2*)(base + p.xy);
     S.z = (double*)(base + p.z);
-    S.start = (int32_t*)(base + p.start);
+    S.start = (uint16_t*)(base + p.start);
     S.cnt = (int32_t*)(base + p.cnt);
     S.sid = (uint16_t*)(base + p.sid);
     S.list = (uint16_t*)(base + p.list);
@@ -115,6 +122,7 @@ __device__ __forceinline__ F64Lds f64_carve(char* base, int nmax, int cmax, int 
     S.wmax = (float*)(base + p.wmax);
     S.scan = (int32_t*)(base + p.scan);
     S.misc = (int32_t*)(base + p.misc);
+    S.ext = (GlobalU16*)ext + (size_t)blockIdx.x * kF64Ext * threads * apt;
     return S;
 }
 
@@ -215,13 +223,6 @@ __device__ __forceinline__ int f64_cell(double s, int nc) {
     return c < 0 ? 0 : (c > nc - 1 ? nc - 1 : c);
 }
 
-// What a list was built for.
-struct List64 {
-    double rl;        // list radius: every pair closer than this at the build is listed
-    int64_t k;        // strain counter at the build
-    bool no_skin;     // a list with a skin outgrew its capacity: build at r_c every step
-};
-
 // Grid of a build: the tilted cell (shear: the offset reduced to half an edge) and cells at least
 // the list radius wide in its perpendicular widths, 3 or more a side, split in half along x (a
 // row's members lie consecutively, so the scan takes 5 half cells of it in place of 3 cells: a
@@ -230,6 +231,17 @@ struct Grid64 {
     double hxy;
     int nx, ny, nz;  // nx counts half cells: twice as many along x
 };
+
+// What a list was built for.
+struct List64 {
+    double rl;       // list radius: every pair closer than this at the build is listed
+    int64_t k;       // strain counter at the build
+    int nx, ny, nz;  // the grid
+};
+
+// From this list length on it names the atom's cell instead, in whose stencil its partners are looked
+// up.
+constexpr int kF64Over = kF64Cap + kF64Ext + 1;
 
 template <int F>
 __device__ __forceinline__ double f64_tilt(const Cell64& H) {
@@ -255,6 +267,30 @@ __device__ __forceinline__ Grid64 f64_grid(const Cell64& H, double hxy, double w
     g.ny = __builtin_amdgcn_readfirstlane(ny);
     g.nz = __builtin_amdgcn_readfirstlane(nz);
     return g;
+}
+
+// Sorted slots of the stencil's row (dy, dz) of an atom's half cell (cx, cy, cz): slot(v) for v below
+// len. Half cells cx - 2 .. cx + 2 of the row; where they wrap in x a second range follows from v =
+// len0 on (nx is 6 or more). yy and zz wrap too.
+struct Row64 {
+    int lo0, len0, off1, len;
+    __device__ __forceinline__ int slot(int v) const { return v + (v < len0 ? lo0 : off1); }
+};
+
+__device__ __forceinline__ Row64 f64_row(const uint16_t* start, int nx, int ny, int nz, int cx, int yy,
+                                         int zz, bool own) {
+    zz += zz < 0 ? nz : (zz >= nz ? -nz : 0);
+    yy += yy < 0 ? ny : (yy >= ny ? -ny : 0);
+    const int row = nx * (yy + ny * zz);
+    const int m0 = max(cx - 2, 0), m1 = min(cx + 3, nx);
+    const int w0 = cx < 2 ? nx + cx - 2 : 0, w1 = cx < 2 ? nx : max(cx + 3 - nx, 0);
+    Row64 r;
+    r.lo0 = start[row + m0];
+    r.len0 = own ? start[row + m1] - r.lo0 : 0;
+    const int lo1 = start[row + w0];
+    r.len = r.len0 + (own ? start[row + w1] - lo1 : 0);
+    r.off1 = lo1 - r.len0;
+    return r;
 }
 
 // Counting sort of the atoms into the grid's cells, members of a cell in index order (an atom's
@@ -292,7 +328,7 @@ __device__ __forceinline__ void f64_sort(const F64Lds& S, const Cell64& H, const
     }
     __syncthreads();
     scan_cells(S.cnt, S.start, C, S.scan);
-    if (t == 0) S.start[C] = n;
+    if (t == 0) S.start[C] = (uint16_t)n;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < APT; ++j)
@@ -312,9 +348,8 @@ __device__ __forceinline__ void f64_sort(const F64Lds& S, const Cell64& H, const
 
 // Builds the lists of the positions x, y, z (wrapped into the cell here) and publishes them in
 // S.xy, S.z; without STATE they are taken as they are (in the cell) and not published. nh: the own
-// atoms' list lengths; returns the wave's longest. The scan runs in FP32 over nine rows of five
-// half cells (two ranges where a row wraps in x), kScan candidates per lane per trip; the FP32 test
-// has a margin for its own rounding, so a list misses no pair of its radius.
+// atoms' list lengths (kF64Over + cell: longer than any list); returns the wave's longest. The scan runs in FP32 over nine rows of five half cells, kScan candidates per lane per
+// trip; the FP32 test has a margin for its own rounding, so a list misses no pair of its radius.
 template <int F, int APT, bool STATE = true>
 __device__ __forceinline__ int f64_build(const F64Lds& S, const Cell64& H, int n, int cmax, double rc,
                          double (&x)[APT], double (&y)[APT], double (&z)[APT], List64& L,
@@ -340,85 +375,104 @@ __device__ __forceinline__ int f64_build(const F64Lds& S, const Cell64& H, int n
             z[j] = f64_frac(z[j]);
         }
     }
-    for (;;) {
-        double skin = L.no_skin ? 0.0 : fmin(kF64Skin * rc, wmin * (1.0 / 3.0) - rc);
-        if (skin < 0.05 * rc) skin = 0.0;
-        L.rl = rc + skin;
-        // FP32 positions and images are off by less than 2^-23 edges, separations by 2^-21
-        const double pad = L.rl + 5e-7 * (H.hxx + fabs(hxy) + H.hyy + H.hzz);
-        const Grid64 g = f64_grid(H, hxy, wx, pad, cmax);
-        if (t == 0) S.misc[0] = 0;
-        int place[APT], cell[APT];
-        float cart[APT][3];
-        f64_sort<F, APT>(S, H, g, n, x, y, z, place, cell, cart);
+    double skin = fmin(kF64Skin * rc, wmin * (1.0 / 3.0) - rc);
+    if (skin < 0.05 * rc) skin = 0.0;
+    L.rl = rc + skin;
+    // FP32 positions and images are off by less than 2^-23 edges, separations by 2^-21
+    const double pad = L.rl + 5e-7 * (H.hxx + fabs(hxy) + H.hyy + H.hzz);
+    const Grid64 g = f64_grid(H, hxy, wx, pad, cmax);
+    int place[APT], cell[APT];
+    float cart[APT][3];
+    f64_sort<F, APT>(S, H, g, n, x, y, z, place, cell, cart);
 #pragma unroll
-        for (int j = 0; j < APT; ++j)
-            if (cell[j] >= 0)
-                sorted[place[j]] =
-                    make_float4(cart[j][0], cart[j][1], cart[j][2], __int_as_float(t + j * T));
-        __syncthreads();
-        const float fxx = (float)H.hxx, fxy = (float)hxy, fyy = (float)H.hyy, fzz = (float)H.hzz;
-        const float rl2 = (float)(pad * pad) * (1.0f + 1e-6f);
-        bool over = false;
-#pragma unroll
-        for (int j = 0; j < APT; ++j) {
-            const int self = t + j * T;
-            const bool own = cell[j] >= 0;
-            const int c0 = own ? cell[j] : 0;
-            const int cx = c0 % g.nx, cy = (c0 / g.nx) % g.ny, cz = c0 / (g.nx * g.ny);
-            // half cells m0..m1-1 of a row, and w0..w1-1 across the x edge (nx is 6 or more)
-            const int m0 = max(cx - 2, 0), m1 = min(cx + 3, g.nx);
-            const int w0 = cx < 2 ? g.nx + cx - 2 : 0, w1 = cx < 2 ? g.nx : max(cx + 3 - g.nx, 0);
-            const float wrap = cx < 2 ? fxx : -fxx;
-            uint16_t* list = S.list + (t * APT + j);
-            int got = 0;
+    for (int j = 0; j < APT; ++j)
+        if (cell[j] >= 0)
+            sorted[place[j]] =
+                make_float4(cart[j][0], cart[j][1], cart[j][2], __int_as_float(t + j * T));
+    __syncthreads();
+    const float fxx = (float)H.hxx, fxy = (float)hxy, fyy = (float)H.hyy, fzz = (float)H.hzz;
+    const float rl2 = (float)(pad * pad) * (1.0f + 1e-6f);
+    // found(id) for each partner of an atom of cell c0 at (px, py, pz)
+    auto scan = [&](int self, bool own, int c0, float px, float py, float pz, auto found) {
+        const int cx = c0 % g.nx, cy = (c0 / g.nx) % g.ny, cz = c0 / (g.nx * g.ny);
+        const float wrap = cx < 2 ? fxx : -fxx;
 #pragma unroll 1
-            for (int r = 0; r < 9; ++r) {
-                const int dz = r / 3 - 1, dy = r % 3 - 1;
-                int zz = cz + dz, yy = cy + dy;
-                const float uz = cart[j][2] + (zz < 0 ? fzz : (zz >= g.nz ? -fzz : 0.0f));
-                zz += zz < 0 ? g.nz : (zz >= g.nz ? -g.nz : 0);
-                const float uy = cart[j][1] + (yy < 0 ? fyy : (yy >= g.ny ? -fyy : 0.0f));
-                float ux = cart[j][0];
-                if constexpr (F != kFlowElong) ux += yy < 0 ? fxy : (yy >= g.ny ? -fxy : 0.0f);
-                const float uw = ux + wrap;
-                yy += yy < 0 ? g.ny : (yy >= g.ny ? -g.ny : 0);
-                const int rowb = g.nx * (yy + g.ny * zz);
-                const int lo0 = S.start[rowb + m0];
-                const int len0 = own ? S.start[rowb + m1] - lo0 : 0;
-                const int lo1 = S.start[rowb + w0];
-                const int len = len0 + (own ? S.start[rowb + w1] - lo1 : 0);
-                const int off1 = lo1 - len0;
-                for (int v = 0; __builtin_amdgcn_ballot_w64(v < len) != 0; v += kScan) {
-                    float4 m[kScan];
+        for (int r = 0; r < 9; ++r) {
+            const int zz = cz + r / 3 - 1, yy = cy + r % 3 - 1;
+            const float uz = pz + (zz < 0 ? fzz : (zz >= g.nz ? -fzz : 0.0f));
+            const float uy = py + (yy < 0 ? fyy : (yy >= g.ny ? -fyy : 0.0f));
+            float ux = px;
+            if constexpr (F != kFlowElong) ux += yy < 0 ? fxy : (yy >= g.ny ? -fxy : 0.0f);
+            const float uw = ux + wrap;
+            const Row64 row = f64_row(S.start, g.nx, g.ny, g.nz, cx, yy, zz, own);
+            for (int v = 0; __builtin_amdgcn_ballot_w64(v < row.len) != 0; v += kScan) {
+                float4 m[kScan];
 #pragma unroll
-                    for (int i = 0; i < kScan; ++i) {
-                        const int vv = v + i;
-                        m[i] = sorted[vv < len ? vv + (vv < len0 ? lo0 : off1) : 0];
-                    }
+                for (int i = 0; i < kScan; ++i) {
+                    const int vv = v + i;
+                    m[i] = sorted[vv < row.len ? row.slot(vv) : 0];
+                }
 #pragma unroll
-                    for (int i = 0; i < kScan; ++i) {
-                        const int vv = v + i;
-                        const float d0 = (vv < len0 ? ux : uw) - m[i].x;
-                        const float d1 = uy - m[i].y, d2 = uz - m[i].z;
-                        const float r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                        const int id = __float_as_int(m[i].w);
-                        if ((vv < len) & (id != self) & (r2 < rl2)) {
-                            if (got < kF64Cap) list[got * (T * APT)] = (uint16_t)id;
-                            ++got;
-                        }
-                    }
+                for (int i = 0; i < kScan; ++i) {
+                    const int vv = v + i;
+                    const float d0 = (vv < row.len0 ? ux : uw) - m[i].x;
+                    const float d1 = uy - m[i].y, d2 = uz - m[i].z;
+                    const float r2 = d0 * d0 + d1 * d1 + d2 * d2;
+                    const int id = __float_as_int(m[i].w);
+                    if ((vv < row.len) & (id != self) & (r2 < rl2)) found(id);
                 }
             }
-            nh[j] = got;
-            over = over || got > kF64Cap;
         }
-        if (over) S.misc[0] = 1;
-        __syncthreads();
-        if (S.misc[0] == 0 || skin == 0.0) break;
-        L.no_skin = true;  // again at r_c (uniform: every thread read the same flag)
-        __syncthreads();
+    };
+    int most = 0;
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+        const bool own = cell[j] >= 0;
+        if (own) S.sid[place[j]] = (uint16_t)(t + j * T);  // (each thread has read its cell's ids)
+        uint16_t* list = S.list + (t * APT + j);
+        int got = 0;
+        scan(t + j * T, own, own ? cell[j] : 0, cart[j][0], cart[j][1], cart[j][2], [&](int id) {
+            if (got < kF64Cap) list[got * (T * APT)] = (uint16_t)id;
+            ++got;
+        });
+        nh[j] = got;
+        most = max(most, got);
     }
+    most = __builtin_amdgcn_readlane((int)wave_max_dpp((float)most), 63);
+    if (__builtin_expect(most > kF64Cap, 0)) {
+        // the entries that found no room in LDS (a second scan, so that the first one, which most
+        // builds end with, is no longer)
+#pragma unroll 1
+        for (int j = 0; j < APT; ++j) {
+            int c0 = cell[0], count = nh[0];
+            float px = cart[0][0], py = cart[0][1], pz = cart[0][2];
+#pragma unroll
+            for (int q = 1; q < APT; ++q)
+                if (q == j) {
+                    c0 = cell[q];
+                    count = nh[q];
+                    px = cart[q][0];
+                    py = cart[q][1];
+                    pz = cart[q][2];
+                }
+            const bool own = count > kF64Cap;
+            GlobalU16* ext = S.ext + (t * APT + j);
+            int got = 0;
+            scan(t + j * T, own, own ? c0 : 0, px, py, pz, [&](int id) {
+                if (got >= kF64Cap && got < kF64Cap + kF64Ext)
+                    ext[(got - kF64Cap) * (T * APT)] = (uint16_t)id;
+                ++got;
+            });
+            count = count >= kF64Over ? kF64Over + c0 : count;
+#pragma unroll
+            for (int q = 0; q < APT; ++q)
+                if (q == j) nh[q] = count;
+        }
+    }
+    L.nx = g.nx;
+    L.ny = g.ny;
+    L.nz = g.nz;
+    __syncthreads();
 #pragma unroll
     for (int j = 0; j < APT; ++j) {
         const int a = t + j * T;
@@ -427,26 +481,70 @@ __device__ __forceinline__ int f64_build(const F64Lds& S, const Cell64& H, int n
             S.z[a] = z[j];
         }
     }
-    int most = 0;
-#pragma unroll
-    for (int j = 0; j < APT; ++j) most = max(most, min(nh[j], kF64Cap));
-    most = __builtin_amdgcn_readlane((int)wave_max_dpp((float)most), 63);
     __syncthreads();
     return most;
 }
 
+// What lies beyond the LDS lists of a wave's lanes (nh: their list lengths): calls see(atom, whether
+// it counts) for the further entries of a lane's list, kMore at a time, or for every atom of its
+// stencil in the last build's grid if no list holds its partners. ext: the lane's row, its entries
+// `stride` apart. One call of see in the code: with two, the two-atom builds spill ten more registers.
+constexpr int kMore = 2;
+template <typename See>
+__device__ __forceinline__ void f64_more(const F64Lds& S, const List64& L, int nh, const GlobalU16* ext,
+                                         int stride, See see) {
+    const bool over = nh >= kF64Over;
+    const int rows = __builtin_amdgcn_ballot_w64(over) != 0 ? 9 : 0;
+    const int cell = over ? nh - kF64Over : 0;
+    const int cx = cell % L.nx, cy = (cell / L.nx) % L.ny, cz = cell / (L.nx * L.ny);
+#pragma unroll 1
+    for (int r = -1; r < rows; ++r) {
+        Row64 row{0, 0, 0, over ? 0 : nh - kF64Cap};
+        if (r >= 0)
+            row = f64_row(S.start, L.nx, L.ny, L.nz, cx, cy + r % 3 - 1, cz + r / 3 - 1, over);
+#pragma unroll 1
+        for (int v = 0; __builtin_amdgcn_ballot_w64(v < row.len) != 0; v += kMore) {
+            int m[kMore];
+#pragma unroll
+            for (int i = 0; i < kMore; ++i) {
+                m[i] = 0;
+                if (v + i < row.len) m[i] = r < 0 ? ext[(v + i) * stride] : S.sid[row.slot(v + i)];
+            }
+#pragma unroll
+            for (int i = 0; i < kMore; ++i) see(m[i], v + i < row.len);
+        }
+    }
+}
+
 // Forces of the own atoms over their lists, and the thread's share of the pair virials: shear
 // w0 = W_xy; elongation w0 = W_xx - W_yy; mixed both (w0 = W_xx - W_yy, w1 = W_xy). Every pair is
-// seen from both sides, so each side adds half. The thread's atoms run side by side (two
+// seen from both sides, so each side adds half. The thread's atoms run side by side (up to four
 // independent chains), the next list word and positions loaded a trip ahead.
 template <int F, int APT>
-__device__ __forceinline__ void f64_forces(const F64Lds& S, const Cell64& H, int n, double rc2,
+__device__ __forceinline__ void f64_forces(const F64Lds& S, const Cell64& H, const List64& L, int n, double rc2,
                                            double ca, const int (&nh)[APT], int longest,
                                            double (&fx)[APT], double (&fy)[APT],
                                            double (&fz)[APT], double& w0, double& w1) {
     const int T = blockDim.x, t = threadIdx.x;
     double a0 = 0.0, a1 = 0.0;
     constexpr int P = APT < kF64Side ? APT : kF64Side;  // atoms side by side
+    const int trips = min(longest, kF64Cap);
+    // force over separation of a pair d apart
+    auto factor = [&](const double (&d)[3], bool listed) {
+        const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+        const double inv = f64_recip(r2);
+        const double s3 = inv * inv * inv;
+        const double fs = s3 * (48.0 * s3 - 24.0 * ca) * inv;
+        return (listed && r2 < rc2) ? fs : 0.0;
+    };
+    auto virial = [&](const double (&d)[3], double fs) {
+        if constexpr (F == kFlowShear) {
+            a0 += d[0] * (fs * d[1]);
+        } else {
+            a0 += fs * (d[0] * d[0] - d[1] * d[1]);
+            if constexpr (F == kFlowMixed) a1 += fs * (d[0] * d[1]);
+        }
+    };
 #pragma unroll
     for (int q = 0; q < APT; q += P) {
         double xi[P], yi[P], zi[P], gx[P], gy[P], gz[P];
@@ -462,19 +560,14 @@ __device__ __forceinline__ void f64_forces(const F64Lds& S, const Cell64& H, int
             gx[j] = gy[j] = gz[j] = 0.0;
         }
         int len[P];
-        bool over = false;  // an atom has no complete list (only ever at r_c)
 #pragma unroll
-        for (int j = 0; j < P; ++j) {
-            const bool o = nh[q + j] > kF64Cap;
-            len[j] = o ? 0 : nh[q + j];
-            over = over || o;
-        }
+        for (int j = 0; j < P; ++j) len[j] = nh[q + j] >= kF64Over ? 0 : min(nh[q + j], kF64Cap);
         // entries k of the P atoms (clamped: nothing past the longest list is read)
         struct Word {
             uint16_t id[P];
         };
         auto word = [&](int k) -> Word {
-            k = k < longest ? k : longest - 1;
+            k = k < trips ? k : trips - 1;
             Word w;
             __builtin_memcpy(&w, __builtin_assume_aligned(S.list + (k * T + t) * APT + q, 2 * P), 2 * P);
             return w;
@@ -492,28 +585,19 @@ __device__ __forceinline__ void f64_forces(const F64Lds& S, const Cell64& H, int
         auto pair = [&](int j, const double2& p, double z, bool listed) {
             double d[3];
             f64_sep<F>(H, xi[j] - p.x, yi[j] - p.y, zi[j] - z, d);
-            const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-            const double inv = f64_recip(r2);
-            const double s3 = inv * inv * inv;
-            double fs = s3 * (48.0 * s3 - 24.0 * ca) * inv;
-            fs = (listed && r2 < rc2) ? fs : 0.0;
+            const double fs = factor(d, listed);
             gx[j] += fs * d[0];
             gy[j] += fs * d[1];
             gz[j] += fs * d[2];
-            if constexpr (F == kFlowShear) {
-                a0 += d[0] * (fs * d[1]);
-            } else {
-                a0 += fs * (d[0] * d[0] - d[1] * d[1]);
-                if constexpr (F == kFlowMixed) a1 += fs * (d[0] * d[1]);
-            }
+            virial(d, fs);
         };
         Word next{};
-        if (longest > 0) {
+        if (trips > 0) {
             load(word(0), 0);
             next = word(1);
         }
 #pragma unroll 1
-        for (int k = 0; k < longest; ++k) {
+        for (int k = 0; k < trips; ++k) {
             double2 pc[P];
             double zc[P];
 #pragma unroll
@@ -527,25 +611,56 @@ __device__ __forceinline__ void f64_forces(const F64Lds& S, const Cell64& H, int
             for (int j = 0; j < P; ++j)
                 pair(j, pc[j], zc[j], k < len[j]);
         }
-        if constexpr (F == kFlowShear) {
-            // an atom with more neighbours than a list holds: every other atom is tried
-            if (__builtin_amdgcn_ballot_w64(over) != 0) {
-#pragma unroll 1
-                for (int m = 0; m < n; ++m) {
-                    const double2 pm = S.xy[m];
-                    const double zm = S.z[m];
-#pragma unroll
-                    for (int j = 0; j < P; ++j)
-                        pair(j, pm, zm, nh[q + j] > kF64Cap && m != own[j]);
-                }
-            }
-        }
 #pragma unroll
         for (int j = 0; j < P; ++j) {
-            // a carried-flow daughter this dense fails its health check
-            fx[q + j] = F != kFlowShear && nh[q + j] > kF64Cap ? __builtin_nan("") : gx[j];
+            fx[q + j] = gx[j];
             fy[q + j] = gy[j];
             fz[q + j] = gz[j];
+        }
+    }
+    if (__builtin_expect(longest > kF64Cap, 0)) {  // entries beyond LDS, an atom at a time (most waves have none)
+#pragma unroll 1
+        for (int j = 0; j < APT; ++j) {
+            int count = nh[0];
+#pragma unroll
+            for (int q = 1; q < APT; ++q) count = q == j ? nh[q] : count;
+            const int a = t + j * T, own = a < n ? a : 0;
+            const double2 pi = S.xy[own];
+            const double zi = S.z[own];
+            const GlobalU16* ext = S.ext + (t * APT + j);
+            double gx = 0.0, gy = 0.0, gz = 0.0;
+            int near = 0;  // partners in range
+            auto separation = [&](int m, double (&d)[3]) {
+                const double2 pm = S.xy[m];
+                f64_sep<F>(H, pi.x - pm.x, pi.y - pm.y, zi - S.z[m], d);
+                return d[0] * d[0] + d[1] * d[1] + d[2] * d[2] < rc2;
+            };
+            f64_more(S, L, count, ext, T * APT, [&](int m, bool live) {
+                double d[3];
+                live = live && m != own;
+                near += separation(m, d) && live ? 1 : 0;
+                const double fs = factor(d, live);
+                gx += fs * d[0];
+                gy += fs * d[1];
+                gz += fs * d[2];
+                virial(d, fs);
+            });
+            if constexpr (F != kFlowShear) {
+                // a carried-flow daughter this dense fails its health check
+                if (count > kF64Cap && count < kF64Over)
+                    for (int k = 0; k < kF64Cap; ++k) {
+                        double d[3];
+                        near += separation(S.list[(k * T + t) * APT + j], d) ? 1 : 0;
+                    }
+                if (near > kF64Cap) gx = __builtin_nan("");
+            }
+#pragma unroll
+            for (int q = 0; q < APT; ++q)
+                if (q == j) {
+                    fx[q] += gx;
+                    fy[q] += gy;
+                    fz[q] += gz;
+                }
         }
     }
     w0 = 0.5 * a0;
@@ -797,8 +912,7 @@ __device__ __forceinline__ void flow64_job(DaughterDesc* dp, const PefLaunch& B,
     float path[APT];
     int nh[APT], longest = 0;
     uint16_t atom[APT];  // the state's atom behind the thread's atom j
-    List64 L;
-    L.no_skin = false;
+    List64 L{};
     double w0, w1 = 0.0;
     // a coordinate of the state as the kernel holds it
     auto stored = [&](double& x, double& y, double& z) {
@@ -969,7 +1083,7 @@ __device__ __forceinline__ void flow64_job(DaughterDesc* dp, const PefLaunch& B,
             L.k = k;
             longest = f64_build<F, APT>(S, H, n, B.cmax, Q.rc, x, y, z, L, nh);
         }
-        f64_forces<F, APT>(S, H, n, Q.rc2, Q.ca, nh, longest, fx, fy, fz, w0, w1);
+        f64_forces<F, APT>(S, H, L, n, Q.rc2, Q.ca, nh, longest, fx, fy, fz, w0, w1);
         ++it;
         double pos = 0.0;
         if constexpr (F == kFlowShear) {  // carries a non-finite coordinate to the health check
@@ -1092,12 +1206,12 @@ __global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4) k_flo
     extern __shared__ __align__(16) char smem[];
     __shared__ Const64 Q;
     __shared__ SysDev sys;
-    const F64Lds S = f64_carve(smem, B.nmax, B.cmax, blockDim.x, APT);
+    const F64Lds S = f64_carve(smem, B.ext, B.nmax, B.cmax, blockDim.x, APT);
     for (;;) {
         __syncthreads();
-        if (threadIdx.x == 0) S.misc[1] = atomicAdd(B.queue, 1);
+        if (threadIdx.x == 0) S.misc[0] = atomicAdd(B.queue, 1);
         __syncthreads();
-        const int job = __builtin_amdgcn_readfirstlane(S.misc[1]);
+        const int job = __builtin_amdgcn_readfirstlane(S.misc[0]);
         if (job >= B.n_jobs) return;
         flow64_job<F, NH, APT>(&B.descs[B.order[job]], B, S, Q, sys);
     }
@@ -1108,7 +1222,8 @@ __global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4) k_flo
 // mother, atoms dealt to the threads as for daughters. Both force forms give what the cell form
 // gives:
 //   FP64  f64_forces (another order of the sums);
-//   FP32  the cell form's bits. Its separations come from FP32 coordinates relative to the atoms'
+//   FP32  the cell form's bits, for atoms whose list fits LDS (the others' forces are summed in FP64
+//         and rounded). Its separations come from FP32 coordinates relative to the atoms'
 //         cells, and its sums run over the stencil's cells in turn, so every step each atom's cell
 //         and relative coordinates go to LDS, and an atom's listed partners are taken in the
 //         order (dz, dy, dx of the cells, index). The list is kept in that order; a lane that meets
@@ -1212,7 +1327,7 @@ __device__ __forceinline__ bool f32_pair(Sum32& g, const Near32& N, const float4
 }
 
 template <int APT>
-__device__ __forceinline__ void f32_forces(const F64Lds& S, const SysDev& sys, int n,
+__device__ __forceinline__ void f32_forces(const F64Lds& S, const SysDev& sys, const List64& L, int n,
                                            const int (&nh)[APT], bool rebuilt, float (&fx)[APT],
                                            float (&fy)[APT], float (&fz)[APT], double& w0) {
     const int t = threadIdx.x, T = blockDim.x;
@@ -1346,18 +1461,27 @@ __device__ __forceinline__ void f32_forces(const F64Lds& S, const SysDev& sys, i
             }
             if (lane == b) g = sum;
         }
-        // an atom with more neighbours than a list holds: every other atom, cell by cell
+        // an atom whose list goes beyond LDS: its partners in the list's order, summed in FP64 (any
+        // order gives the same FP32 force to a rounding)
         if (__builtin_amdgcn_ballot_w64(over) != 0) {
-#pragma unroll 1
-            for (int c = 0; c < 27; ++c)
-#pragma unroll 1
-                for (int m = 0; m < n; ++m) {
-                    const float4 uj = u[m];
-                    const ushort2v xy = f32_near(__float_as_uint(uj.w), N.before_xy, N.nc_xy);
-                    const ushort2v z = f32_near(uz[m], N.before_z, N.nc_z);
-                    const bool now = max(xy.x, max(xy.y, z.x)) <= 2 && z.x * 9 + xy.y * 3 + xy.x == c;
-                    (void)f32_pair(g, N, ui, uj, xy, z, over & (m != me) & now, rc2, ca);
-                }
+            double sx = 0.0, sy = 0.0, sz = 0.0, sw = 0.0;
+            auto see = [&](int m, bool live) {
+                const float4 uj = u[m];
+                Pair32 d;
+                (void)f32_separation(d, N, ui, uj, f32_near(__float_as_uint(uj.w), N.before_xy, N.nc_xy),
+                                     f32_near(uz[m], N.before_z, N.nc_z), live & (m != me), rc2, ca);
+                sx += (double)d.fs * (double)d.x;
+                sy += (double)d.fs * (double)d.y;
+                sz += (double)d.fs * (double)d.z;
+                sw += (double)d.x * ((double)d.fs * (double)d.y);
+            };
+            const bool listed = over && nh[j] < kF64Over;
+            for (int k = 0; k < kF64Cap; ++k) {
+                const int m = list[k * stride];
+                see(listed ? m : me, listed);
+            }
+            f64_more(S, L, over ? nh[j] : 0, S.ext + (t * APT + j), stride, see);
+            if (over) g = Sum32{(float)sx, (float)sy, (float)sz, (float)sw};
         }
         fx[j] = own ? g.x : 0.0f;
         fy[j] = own ? g.y : 0.0f;
@@ -1369,11 +1493,11 @@ __device__ __forceinline__ void f32_forces(const F64Lds& S, const SysDev& sys, i
 
 template <bool F32, int APT>
 __global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4)
-    k_mother_lists(const MotherLaunch* ms, int nmax, int cmax) {
+    k_mother_lists(const MotherLaunch* ms, uint16_t* ext, int nmax, int cmax) {
     extern __shared__ __align__(16) char smem[];
     __shared__ SysDev sys;
     const MotherLaunch& m = ms[blockIdx.x];
-    const F64Lds S = f64_carve(smem, nmax, cmax, blockDim.x, APT);
+    const F64Lds S = f64_carve(smem, ext, nmax, cmax, blockDim.x, APT);
     if (threadIdx.x == 0) sys = m.sys;
     __syncthreads();
     const int T = blockDim.x, t = threadIdx.x, n = sys.n;
@@ -1390,10 +1514,7 @@ __global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4)
     std::conditional_t<F32, float, double> fx[APT], fy[APT], fz[APT];
     float path[APT];
     int nh[APT], longest = 0;
-    List64 L;
-    L.rl = 0.0;
-    L.k = 0;
-    L.no_skin = false;
+    List64 L{};
     double* st = m.state;
     uint16_t atom[APT];  // the state's atom behind the thread's atom j
     {
@@ -1512,9 +1633,9 @@ __global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4)
         }
         double w0, w1 = 0.0;
         if constexpr (F32)
-            f32_forces<APT>(S, sys, n, nh, stale, fx, fy, fz, w0);
+            f32_forces<APT>(S, sys, L, n, nh, stale, fx, fy, fz, w0);
         else
-            f64_forces<kFlowShear, APT>(S, H, n, sys.rc2, sys.c_attr, nh, longest, fx, fy, fz, w0, w1);
+            f64_forces<kFlowShear, APT>(S, H, L, n, sys.rc2, sys.c_attr, nh, longest, fx, fy, fz, w0, w1);
         double mm[3] = {0.0, 0.0, w0};
 #pragma unroll
         for (int j = 0; j < APT; ++j) {
@@ -1586,6 +1707,10 @@ __global__ void k_spawn_pef(const double* states, int32_t n, const int32_t* stat
 }  // namespace
 
 int flow64_list_cap() { return kF64Cap; }
+
+size_t flow64_ext_bytes(int threads, int apt, int grid) {
+    return sizeof(uint16_t) * (size_t)kF64Ext * threads * apt * grid;
+}
 
 // Neighbours an atom of a uniform fluid has within the list radius.
 double flow64_neighbours(double density, double rc) {
@@ -1702,7 +1827,7 @@ hipError_t launch_mother_lists_t(const MotherLaunch* dev_ms, int count, const Mo
     (void)hipFuncSetAttribute((const void*)k_mother_lists<F32, APT>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)m.list_lds);
     hipLaunchKernelGGL((k_mother_lists<F32, APT>), dim3(count), dim3(m.list_threads), m.list_lds, s, dev_ms,
-                       m.sys.n, m.list_cells);
+                       m.ext, m.sys.n, m.list_cells);
     return hipGetLastError();
 }
 }  // namespace

@@ -128,7 +128,8 @@ struct BatchLaunch {
     int32_t flow64;        // cell form: 1 to run the FP64 list kernel (ttcf_flow64.hip) instead
     int32_t pairs_lds;     // pair-list form: 1 if each job's pair words live in LDS after its
                            // layout (lds_bytes covers lds_bytes_pairs_lds of every job)
-    uint32_t* pairs;       // pair-list form otherwise: grid x pair_stride pair words
+    uint32_t* pairs;       // pair-list form otherwise: grid x pair_stride pair words; flow64: its
+                           // flow64_ext_bytes
     int64_t pair_stride;   // >= list_waves * job_threads(n) / 64 * 256 * kmax of every job
     int32_t list_waves;    // waves with a pair segment for each wave that owns atoms
     size_t lds_bytes;
@@ -150,6 +151,7 @@ struct PefLaunch {
     int32_t max_steps;     // steps this call (each daughter stops at its own N_d)
     int32_t* queue;        // device counter (zeroed by the launcher)
     int32_t threads, apt, grid, cmax;  // flow64_shape of the largest system
+    uint16_t* ext;         // flow64_ext_bytes of the launch
     int32_t nmax;          // largest system
     int32_t thermo;        // daughter thermostat of every job (0 isokinetic, 1 Nose-Hoover)
     int32_t flow;          // 0 shear, 1 planar elongation, 2 mixed flow
@@ -170,6 +172,7 @@ struct MotherLaunch {
     int32_t threads, apt, precision;
     int32_t list_cells, list_threads, list_apt;  // mother_lists
     size_t list_lds;       // its LDS, or 0: the cell form
+    uint16_t* ext;         // (launch shape) flow64_ext_bytes of the launch
     size_t lds_bytes;      // the cell form's
 };
 
@@ -377,7 +380,8 @@ hipError_t launch_response(const ResponseLaunch& r, hipStream_t s);
 // shape of a launch over n_jobs daughters of up to nmax atoms and `cells` r_c cells; false when
 // no workgroup holds the largest
 bool flow64_shape(int nmax, int cells, int n_jobs, int num_cu, size_t max_lds, Flow64Shape* out);
-int flow64_list_cap();  // neighbours a list holds
+int flow64_list_cap();  // neighbours a list holds in LDS
+size_t flow64_ext_bytes(int threads, int apt, int grid);  // global scratch for longer lists
 double flow64_neighbours(double density, double rc);
 int pef_max_cells(double volume, double rc);
 size_t pef_grid_bytes(int nmax, int cmax);

@@ -1195,6 +1195,7 @@ hipError_t launch_daughters(const BatchLaunch& b, hipStream_t s) {
         L.cmax = b.cmax;
         L.nmax = b.nmax;
         L.thermo = b.thermo;
+        L.ext = (uint16_t*)b.pairs;
         L.flow = 0;
         return launch_flow64(L, s);
     }
