@@ -399,14 +399,21 @@ int32_t ensure_nl_scratch(ttcf_ctx* c, size_t bytes) {
     return TTCF_OK;
 }
 
-void mother_shape(const ttcf_ctx* c, const Mother& m, MotherLaunch* L) {
+// Shape of a launch of `steps` steps.
+void mother_shape(const ttcf_ctx* c, const Mother& m, int64_t steps, MotherLaunch* L) {
     L->threads = m.threads;
     L->apt = m.apt;
     L->precision = m.sys.precision;
     L->lds_bytes = lds_for(m.dev, m.sys.precision);
-    // (a system that fixes its workgroup size asks for the cell form, as for daughters)
+    // A system that fixes its workgroup size asks for the cell form, as for daughters. The list form
+    // deals the atoms and builds its lists first, which FP32 forces (their lists are sorted, too) make
+    // up for from the second or third step on. A call of one, two and three steps, cell form and lists:
+    // N = 1000 77, 102, 127 and 81, 86, 101 us; N = 1025 91, 123, 154 and 128, 142, 165; N = 2048 110,
+    // 151, 193 and 128, 145, 161; N = 500 and fewer, and FP64, gain at one step.
     L->list_lds = 0;
-    if (m.sys.block_threads <= 0) (void)mother_lists(m.dev, c->max_lds, L);
+    const int64_t few =
+        m.sys.precision != TTCF_PREC_FP32_FORCES ? 0 : (m.dev.n > 1024 ? 2 : (m.dev.n > 512 ? 1 : 0));
+    if (m.sys.block_threads <= 0 && steps > few) (void)mother_lists(m.dev, c->max_lds, L);
 }
 
 // Launches mothers whose launch blocks are on the device, with the context's list scratch.
@@ -441,7 +448,7 @@ int32_t run_mother(ttcf_ctx* c, Mother& m, double temperature, int64_t n_chunks,
         L.series = m.series + m.series_count;
         m.series_count += total;
     }
-    mother_shape(c, m, &L);
+    mother_shape(c, m, total, &L);
     int32_t rc = upload_mother_launches(c, &L, 1);
     if (rc == TTCF_OK) rc = run_mothers(c, 1, L);
     if (rc != TTCF_OK) return rc;
@@ -2223,12 +2230,12 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
             L.temperature = m.sys.temperature;
             L.nf = nf;
             L.q = nf * m.sys.temperature * m.sys.nh_tau * m.sys.nh_tau;
-            mother_shape(c, m, &L);
             L.series = nullptr;
         }
         if (rep && gd->decorrelate_steps > 0) {
             // once, outside the graph, through the context's own launch block
             for (auto& L : P.ml) {
+                mother_shape(c, m, gd->decorrelate_steps, &L);
                 L.n_chunks = 0;
                 L.steps_per_chunk = gd->decorrelate_steps;
                 L.snapshots = nullptr;
@@ -2237,6 +2244,8 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
             if (rc == TTCF_OK) rc = run_mothers(c, P.n_copies, P.ml[0]);
             if (rc != TTCF_OK) return bail(rc, c->err);
         }
+        for (auto& L : P.ml)
+            mother_shape(c, m, (int64_t)gd->states_per_replica * gd->steps_between, &L);
         if (P.ml[0].list_lds > 0) {  // the graph owns the scratch its replays use
             P.ml[0].ext = (uint16_t*)g->get(
                 flow64_ext_bytes(P.ml[0].list_threads, P.ml[0].list_apt, P.n_copies));
@@ -2738,6 +2747,7 @@ struct Replicas {
     Scratch* sc = nullptr;
     std::vector<MotherLaunch> ls;
     double* rep = nullptr;
+    const Mother* of = nullptr;
     int32_t count = 0;
     ~Replicas() { delete sc; }
 
@@ -2764,8 +2774,8 @@ struct Replicas {
             L.temperature = m.sys.temperature;
             L.nf = nf;
             L.q = nf * m.sys.temperature * m.sys.nh_tau * m.sys.nh_tau;
-            mother_shape(c, m, &L);
         }
+        of = &m;
         if (decorrelate > 0) return run(c, 0, decorrelate, nullptr);
         return TTCF_OK;
     }
@@ -2776,6 +2786,7 @@ struct Replicas {
                 double* zsnaps = nullptr) {
         const size_t sz = 6 * (size_t)ls[0].sys.n;
         for (int r = 0; r < count; ++r) {
+            mother_shape(c, *of, std::max<int64_t>(n_chunks, 1) * steps, &ls[r]);
             ls[r].n_chunks = n_chunks;
             ls[r].steps_per_chunk = steps;
             ls[r].snapshots = snaps ? snaps + sz * (size_t)r * (size_t)n_chunks : nullptr;
