@@ -29,7 +29,10 @@ void* dev_alloc(size_t bytes, hipStream_t s) {
     if (bytes == 0) bytes = 8;
     if (g_alloc) return g_alloc((uint64_t)bytes, (void*)s, g_user);
     void* p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();  // the caller reports it, or does without
+        return nullptr;
+    }
     return p;
 }
 
@@ -164,6 +167,7 @@ struct ttcf_ctx {
     // mother launch blocks (device array)
     MotherLaunch* d_mlaunch = nullptr;
     int32_t mlaunch_cap = 0;
+    RowStage stage;  // exports and imports of rows
     // accumulated control-variate series (same rows as acc_d)
     double* acc_h = nullptr;
     std::vector<int32_t> row_cv;
@@ -616,6 +620,7 @@ void ttcf_destroy(ttcf_ctx* c) {
     dev_free(c->d_row_coef);
     dev_free(c->d_row_health);
     dev_free(c->d_mlaunch);
+    c->stage.release();
     dev_free(c->acc_h);
     dev_free(c->cv_p);
     dev_free(c->cv_x);
@@ -794,8 +799,8 @@ int32_t ttcf_import_states(ttcf_ctx* c, int32_t mother, int32_t n_states, const 
     }
     HIPCHECK(c, launch_fill_f64(zetas_of(m), 0.0, n_states, c->stream));
     const size_t w = sizeof(double) * 3 * n;
-    HIPCHECK(c, copy_rows((void*)r, m.states, 2 * w, w, n_states, hipMemcpyHostToDevice, c->stream));
-    HIPCHECK(c, copy_rows((void*)p, m.states + 3 * n, 2 * w, w, n_states, hipMemcpyHostToDevice,
+    HIPCHECK(c, copy_rows(c->stage, (void*)r, m.states, 2 * w, w, n_states, hipMemcpyHostToDevice, c->stream));
+    HIPCHECK(c, copy_rows(c->stage, (void*)p, m.states + 3 * n, 2 * w, w, n_states, hipMemcpyHostToDevice,
                           c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     m.n_states = n_states;
@@ -809,9 +814,9 @@ int32_t ttcf_export_states(ttcf_ctx* c, int32_t mother, int32_t n_states, double
     const size_t n = (size_t)m.dev.n;
     const size_t w = sizeof(double) * 3 * n;
     if (r)
-        HIPCHECK(c, copy_rows(r, m.states, 2 * w, w, n_states, hipMemcpyDeviceToHost, c->stream));
+        HIPCHECK(c, copy_rows(c->stage, r, m.states, 2 * w, w, n_states, hipMemcpyDeviceToHost, c->stream));
     if (p)
-        HIPCHECK(c, copy_rows(p, m.states + 3 * n, 2 * w, w, n_states, hipMemcpyDeviceToHost, c->stream));
+        HIPCHECK(c, copy_rows(c->stage, p, m.states + 3 * n, 2 * w, w, n_states, hipMemcpyDeviceToHost, c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     return TTCF_OK;
 }
@@ -2638,7 +2643,7 @@ int32_t export_rows(ttcf_ctx* c, const std::vector<SeriesRow>& src, int32_t n_t,
         while (e < src.size() && src[e].batch == src[q].batch &&
                (const char*)src[e].data == (const char*)src[e - 1].data + pitch)
             ++e;
-        HIPCHECK(c, copy_rows((char*)out + q * width, (void*)src[q].data, pitch, width, e - q,
+        HIPCHECK(c, copy_rows(c->stage, (char*)out + q * width, (void*)src[q].data, pitch, width, e - q,
                               hipMemcpyDeviceToHost, c->stream));
         q = e;
     }

@@ -41,6 +41,7 @@ struct ttcf_channel_ctx {
     ChannelDev dev{};
     int num_cu = 0;
     size_t max_lds = 0;
+    RowStage stage;  // exports and imports of rows
     // mother
     double* m_r = nullptr;
     double* m_p = nullptr;
@@ -381,6 +382,7 @@ void ttcf_channel_destroy(ttcf_channel_ctx* c) {
         (void)hipEventDestroy(e.first);
         (void)hipEventDestroy(e.second);
     }
+    c->stage.release();
     rt_free(c->m_r);
     rt_free(c->m_p);
     rt_free(c->m_f);
@@ -523,9 +525,9 @@ int32_t ttcf_channel_import_states(ttcf_channel_ctx* c, int32_t n_states, const 
     const size_t n = (size_t)c->dev.n, sz = 6 * n + 1;
     const size_t w = sizeof(double) * 3 * n, pitch = sizeof(double) * sz;
     const hipMemcpyKind to = hipMemcpyHostToDevice;
-    CHK(c, copy_rows((void*)r, c->states, pitch, w, n_states, to, c->stream));
-    CHK(c, copy_rows((void*)p, c->states + 3 * n, pitch, w, n_states, to, c->stream));
-    CHK(c, copy_rows((void*)zeta, c->states + 6 * n, pitch, sizeof(double), n_states, to, c->stream));
+    CHK(c, copy_rows(c->stage, (void*)r, c->states, pitch, w, n_states, to, c->stream));
+    CHK(c, copy_rows(c->stage, (void*)p, c->states + 3 * n, pitch, w, n_states, to, c->stream));
+    CHK(c, copy_rows(c->stage, (void*)zeta, c->states + 6 * n, pitch, sizeof(double), n_states, to, c->stream));
     CHK(c, hipStreamSynchronize(c->stream));
     c->n_states = n_states;
     return TTCF_OK;
@@ -537,10 +539,10 @@ int32_t ttcf_channel_export_states(ttcf_channel_ctx* c, int32_t n_states, double
     const size_t n = (size_t)c->dev.n, sz = 6 * n + 1;
     const size_t w = sizeof(double) * 3 * n, pitch = sizeof(double) * sz;
     const hipMemcpyKind to = hipMemcpyDeviceToHost;
-    if (r) CHK(c, copy_rows(r, c->states, pitch, w, n_states, to, c->stream));
-    if (p) CHK(c, copy_rows(p, c->states + 3 * n, pitch, w, n_states, to, c->stream));
+    if (r) CHK(c, copy_rows(c->stage, r, c->states, pitch, w, n_states, to, c->stream));
+    if (p) CHK(c, copy_rows(c->stage, p, c->states + 3 * n, pitch, w, n_states, to, c->stream));
     if (zeta)
-        CHK(c, copy_rows(zeta, c->states + 6 * n, pitch, sizeof(double), n_states, to, c->stream));
+        CHK(c, copy_rows(c->stage, zeta, c->states + 6 * n, pitch, sizeof(double), n_states, to, c->stream));
     CHK(c, hipStreamSynchronize(c->stream));
     return TTCF_OK;
 }
@@ -749,7 +751,7 @@ int32_t ttcf_channel_export_series(ttcf_channel_ctx* c, int64_t first, int32_t c
         if (rc != TTCF_OK) return rc;
         const int32_t run = std::min<int32_t>(count - q, b.n_daughters - di);
         if (obs)
-            CHK(c, copy_rows(obs + (size_t)q * n_t * nobs, b.descs[di].series,
+            CHK(c, copy_rows(c->stage, obs + (size_t)q * n_t * nobs, b.descs[di].series,
                              sizeof(double) * (size_t)(b.n_steps + 1) * nobs, width, run,
                              hipMemcpyDeviceToHost, c->stream));
         for (int32_t e = 0; s0 && e < run; ++e) s0[q + e] = b.descs[di + e].s0;

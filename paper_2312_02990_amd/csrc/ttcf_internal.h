@@ -320,12 +320,26 @@ hipError_t launch_debug_pair_form(const SysDev& S, double gamma_dot, int64_t kst
 void* rt_alloc(size_t bytes, hipStream_t s);
 void rt_free(void* p);
 
+// Device buffer that a context keeps for packing rows that lie apart, at most kStageBytes: one of a
+// call's own would be allocated and freed by each, where a hipFree waits for every stream of the
+// device, and be freed before the copies have run.
+constexpr size_t kStageBytes = (size_t)16 << 20;
+struct RowStage {
+    void* p = nullptr;
+    size_t bytes = 0;
+    void release() {  // (the stream it was used on is idle)
+        rt_free(p);
+        p = nullptr;
+        bytes = 0;
+    }
+};
+
 // `rows` rows of `width` bytes between a contiguous host array and device rows `pitch` bytes apart
-// (width or more; all multiples of 8): one linear copy, through a packed device buffer where the
-// rows are apart. A copy of its own per row costs about 11 us each (N = 2048, 4096 daughters of
-// 501 points: 47 ms for 16 MB), a 2D copy 7 us.
-hipError_t copy_rows(void* host, void* dev, size_t pitch, size_t width, size_t rows, hipMemcpyKind kind,
-                     hipStream_t s);
+// (width or more; all multiples of 8): linear copies through the packed buffer where the rows are
+// apart. A copy of its own per row costs about 11 us each (N = 2048, 4096 daughters of 501 points:
+// 47 ms for 16 MB), a 2D copy 7 us.
+hipError_t copy_rows(RowStage& stage, void* host, void* dev, size_t pitch, size_t width, size_t rows,
+                     hipMemcpyKind kind, hipStream_t s);
 hipError_t launch_zero_int(int32_t* p, hipStream_t s);
 hipError_t launch_daughters(const BatchLaunch& b, hipStream_t s);
 bool mother_lists(const SysDev& S, size_t max_lds, MotherLaunch* L);

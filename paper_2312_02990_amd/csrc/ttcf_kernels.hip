@@ -1371,28 +1371,48 @@ hipError_t launch_copy_words(const uint64_t* src, uint64_t* dst, int64_t count, 
     return hipGetLastError();
 }
 
-hipError_t copy_rows(void* host, void* dev, size_t pitch, size_t width, size_t rows, hipMemcpyKind kind,
-                     hipStream_t s) {
+hipError_t copy_rows(RowStage& stage, void* host, void* dev, size_t pitch, size_t width, size_t rows,
+                     hipMemcpyKind kind, hipStream_t s) {
     if (rows == 0 || width == 0) return hipSuccess;
     const bool up = kind == hipMemcpyHostToDevice;
-    if (rows == 1 || pitch == width)
-        return hipMemcpyAsync(up ? dev : host, up ? host : dev, width * rows, kind, s);
-    void* packed = rt_alloc(width * rows, s);
-    if (!packed)
-        return hipMemcpy2DAsync(up ? dev : host, up ? pitch : width, up ? host : dev,
-                                up ? width : pitch, width, rows, kind, s);
-    const int64_t words = (int64_t)(width / 8), count = words * (int64_t)rows;
-    const int64_t want = (count + 255) / 256;
-    const unsigned blocks = (unsigned)(want < 4096 ? want : 4096);
-    hipError_t e = hipSuccess;
-    if (up) e = hipMemcpyAsync(packed, host, width * rows, kind, s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_pack_rows, dim3(blocks), dim3(256), 0, s, (uint64_t*)dev,
-                           (int64_t)(pitch / 8), (uint64_t*)packed, words, count, up ? 1 : 0);
-        e = hipGetLastError();
+    auto copy = [&](void* d, size_t row, size_t bytes) {
+        char* h = (char*)host + row * width;
+        return hipMemcpyAsync(up ? d : h, up ? h : d, bytes, kind, s);
+    };
+    if (rows == 1 || pitch == width) return copy(dev, 0, width * rows);
+    // Long rows gain nothing by packing, and a few on the way up are sooner copied one by one (the
+    // import of two states of 256 atoms takes 41 us so, 46 packed; of four 100 us, 56 packed).
+    if (width > kStageBytes / 4 || (up && rows <= 3)) {
+        hipError_t e = hipSuccess;
+        for (size_t r = 0; r < rows && e == hipSuccess; ++r) e = copy((char*)dev + r * pitch, r, width);
+        return e;
     }
-    if (!up && e == hipSuccess) e = hipMemcpyAsync(host, packed, width * rows, kind, s);
-    rt_free(packed);
+    const size_t held = kStageBytes / width < rows ? kStageBytes / width : rows;
+    if (stage.bytes < held * width) {
+        const hipError_t e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return e;
+        stage.release();
+        stage.p = rt_alloc(held * width, s);
+        if (!stage.p)
+            return hipMemcpy2DAsync(up ? dev : host, up ? pitch : width, up ? host : dev,
+                                    up ? width : pitch, width, rows, kind, s);
+        stage.bytes = held * width;
+    }
+    hipError_t e = hipSuccess;
+    for (size_t r = 0; r < rows && e == hipSuccess; r += held) {
+        const size_t part = rows - r < held ? rows - r : held;
+        const int64_t words = (int64_t)(width / 8), count = words * (int64_t)part;
+        const int64_t want = (count + 255) / 256;
+        const unsigned blocks = (unsigned)(want < 4096 ? want : 4096);
+        if (up) e = copy(stage.p, r, width * part);
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(k_pack_rows, dim3(blocks), dim3(256), 0, s,
+                               (uint64_t*)((char*)dev + r * pitch), (int64_t)(pitch / 8),
+                               (uint64_t*)stage.p, words, count, up ? 1 : 0);
+            e = hipGetLastError();
+        }
+        if (!up && e == hipSuccess) e = copy(stage.p, r, width * part);
+    }
     return e;
 }
 
