@@ -1109,12 +1109,46 @@ int32_t spawn_impl(ttcf_ctx* c, int32_t mother, int32_t n_states, int64_t steps_
     return TTCF_OK;
 }
 
+// Whether a shear daughter with FP64 forces runs over neighbour lists (ttcf_flow64.hip), unless a
+// step shape is set: a system that fixes its workgroup size asks for the cell form.
+bool takes_lists64(const ttcf_ctx* c, const Mother& m, const DaughterDesc& d) {
+    return m.sys.precision == TTCF_PREC_FP64 && m.sys.block_threads <= 0 && d.field == kFieldShear &&
+           !d.xseries && flow64_takes(d.sys, c->max_lds);
+}
+
+// Launch groups of a step, by kernel form: pair lists at four and (more than 2048 atoms) at eight
+// atoms per thread, cells, FP64 lists.
+enum Form { kFormPairs = 0, kFormCells = 1, kFormPairsLarge = 2, kFormLists64 = 3, kForms = 4 };
+
 // Launch shape of one group of daughters in one kernel form. threads_req > 0 fixes the
-// workgroup size; kmax is the list capacity of the neighbour-list form.
-// list64: FP64 forces may run over neighbour lists (no step shape was set and no member's system
-// fixes its workgroup size, which ask for the cell form).
-int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, bool list64,
-                   int variant, int precision, int32_t n_steps, int threads_req, BatchLaunch* L) {
+// workgroup size of the cell form; kmax is the list capacity of the pair-list form.
+int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, int form,
+                   int precision, int32_t n_steps, int threads_req, BatchLaunch* L) {
+    if (form == kFormLists64) {
+        *L = BatchLaunch{};
+        L->descs = c->d_descs;
+        L->n_jobs = (int32_t)group.size();
+        L->queue = c->d_queue;
+        L->max_steps = n_steps;
+        L->precision = precision;
+        L->variant = kVariantCells;
+        L->thermo = group[0]->thermo;
+        L->flow64 = 1;
+        int cells = 0;
+        for (const DaughterDesc* dp : group) {
+            L->nmax = std::max(L->nmax, dp->sys.n);
+            cells = std::max(cells, pef_max_cells(dp->sys.volume, dp->sys.rc) + 8);
+        }
+        Flow64Shape f{};
+        if (!flow64_shape(L->nmax, cells, L->n_jobs, c->num_cu, c->max_lds, &f))
+            return fail(c, TTCF_EINVAL, "batch exceeds the LDS of one workgroup");
+        L->apt = f.apt;
+        L->threads = f.threads;
+        L->cmax = f.cmax;
+        L->grid = f.grid;
+        return TTCF_OK;
+    }
+    const int variant = form == kFormCells ? kVariantCells : kVariantNeighbourList;
     int nmax = 0, cmax = 0, lcmax = 0, threads = 0, kmax = 0;
     size_t nl_lds = 0;
     int64_t pair_stride = 0;
@@ -1195,28 +1229,6 @@ int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, b
     L->pair_stride = pair_stride;
     L->pairs_lds = pairs_lds ? 1 : 0;
     L->list_waves = list_waves;
-    if (!nlf && list64 && precision == TTCF_PREC_FP64 && !L->obs && !L->field &&
-        nmax <= kPefMaxAtoms) {
-        // FP64 forces over neighbour lists wherever a workgroup holds them (the cell form
-        // rebuilds its grid and scans 27 cells in FP64 every step) and a list has room for half
-        // as many neighbours again as its radius holds on average (atoms with more are tried
-        // against every other atom)
-        int cells = 0;
-        double most = 0.0;
-        for (const DaughterDesc* dp : group) {
-            cells = std::max(cells, pef_max_cells(dp->sys.volume, dp->sys.rc) + 8);
-            most = std::max(most, flow64_neighbours(dp->sys.n / dp->sys.volume, dp->sys.rc));
-        }
-        Flow64Shape f{};
-        if (1.5 * most <= flow64_list_cap() && flow64_shape(nmax, cells, L->n_jobs, c->num_cu, c->max_lds, &f)) {
-            L->flow64 = 1;
-            L->apt = f.apt;
-            L->threads = f.threads;
-            L->cmax = f.cmax;
-            L->grid = f.grid;
-            return TTCF_OK;
-        }
-    }
     L->lds_bytes = nlf ? (pairs_lds ? nl_lds_pl : nl_lds) : lds_bytes_for(nmax, cmax, threads, precision);
     if (L->lds_bytes > c->max_lds) return fail(c, TTCF_EINVAL, "batch exceeds the LDS of one workgroup");
     const int per_cu_lds = (int)(c->max_lds / L->lds_bytes);
@@ -1288,11 +1300,11 @@ int32_t step_impl(ttcf_ctx* c, int32_t n_steps, const std::vector<char>* only,
     if (c->descs.empty() || n_steps == 0) return TTCF_OK;
     int32_t rc = sync_descs(c);
     if (rc != TTCF_OK) return rc;
-    // daughters still to run; each goes to the pair-list form when it may, else to the cell
-    // form; each (form, thermostat) is one persistent launch, largest systems first.
-    // groups[2 form + thermo], form 0 pair lists (4 atoms per thread), 1 cells, 2 pair lists
-    // (8 atoms per thread: more than 2048 atoms)
-    std::vector<int32_t> groups[6];
+    // daughters still to run; each goes to the list form of its precision when it may, else to the
+    // cell form; each (form, thermostat) is one persistent launch, largest systems first.
+    // groups[2 form + thermo]
+    std::vector<int32_t> groups[2 * kForms];
+    const bool automatic = force ? force->variant == 0 && force->threads == 0 : !c->shape_explicit;
     // planar-elongation (0, 1) and mixed-flow (2, 3) daughters by thermostat: own kernels, FP64
     std::vector<int32_t> pef[4];
     std::vector<StepShape> eff(c->descs.size());
@@ -1320,12 +1332,13 @@ int32_t step_impl(ttcf_ctx* c, int32_t n_steps, const std::vector<char>* only,
         if (d.field != kFieldShear && !nl)
             return fail(c, TTCF_EINVAL, "colour-field daughters need the neighbour-list form, "
                                         "and this system runs in cells");
-        const int form = !nl ? 1 : (pair_job_apt(d.sys.n) == pair_small_apt() ? 0 : 2);
+        const int form = nl ? (pair_job_apt(d.sys.n) == pair_small_apt() ? kFormPairs : kFormPairsLarge)
+                            : (automatic && takes_lists64(c, m, d) ? kFormLists64 : kFormCells);
         groups[2 * form + (d.thermo ? 1 : 0)].push_back((int32_t)i);
     }
-    const bool any_nl = !groups[0].empty() || !groups[1].empty() || !groups[4].empty() ||
-                        !groups[5].empty();
-    const bool any_cell = !groups[2].empty() || !groups[3].empty();
+    auto any = [&](int form) { return !groups[2 * form].empty() || !groups[2 * form + 1].empty(); };
+    const bool any_nl = any(kFormPairs) || any(kFormPairsLarge);
+    const bool any_cell = any(kFormCells) || any(kFormLists64);
     if (!any_nl && !any_cell && pef[0].empty() && pef[1].empty() && pef[2].empty() &&
         pef[3].empty())
         return TTCF_OK;
@@ -1355,21 +1368,14 @@ int32_t step_impl(ttcf_ctx* c, int32_t n_steps, const std::vector<char>* only,
     if (any_nl || any_cell)
         c->last_variant = !any_nl ? kVariantCells : (!any_cell ? kVariantNeighbourList : 3);
     size_t offset = 0;
-    for (int gi = 0; gi < 6; ++gi) {
-        const int form = gi / 2;
+    for (int gi = 0; gi < 2 * kForms; ++gi) {
         const std::vector<int32_t>& group = groups[gi];
         if (group.empty()) continue;
         // the largest system's shape sets the workgroup size
         std::vector<const DaughterDesc*> ds;
-        bool block_explicit = false;
-        for (int32_t i : group) {
-            ds.push_back(&c->descs[i]);
-            block_explicit = block_explicit ||
-                             c->mothers[c->batches[c->live[i].batch].mother].sys.block_threads > 0;
-        }
+        for (int32_t i : group) ds.push_back(&c->descs[i]);
         BatchLaunch L{};
-        rc = plan_group(c, ds, !force && !c->shape_explicit && !block_explicit, form == 1 ? kVariantCells : kVariantNeighbourList,
-                        precision, n_steps, eff[group[0]].threads, &L);
+        rc = plan_group(c, ds, gi / 2, precision, n_steps, eff[group[0]].threads, &L);
         if (rc != TTCF_OK) return rc;
         if (list_scratch_bytes(L) > 0) {
             rc = ensure_nl_scratch(c, list_scratch_bytes(L));
@@ -2271,7 +2277,7 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
     std::vector<DaughterDesc> hd(nd);
     std::vector<double*> hdst(nd);
     std::vector<int32_t> hints(3 * (size_t)nd + n_states + 1);
-    std::vector<char> nl_of(nd, 0);
+    std::vector<char> form_of(nd, 0);
     for (GraphPart& P : parts) {
         const ttcf_graph_desc* gd = P.gd;
         const Mother& m = c->mothers[gd->mother];
@@ -2300,7 +2306,8 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
                 bool nl = false;
                 rc = apply_shape(c, P.shape, precision, &ds, &nl);
                 if (rc != TTCF_OK) return bail(rc, c->err);
-                nl_of[d] = nl ? 1 : 0;
+                form_of[d] = nl ? (pair_job_apt(P.n) == pair_small_apt() ? kFormPairs : kFormPairsLarge)
+                                : (!c->shape_explicit && takes_lists64(c, m, ds) ? kFormLists64 : kFormCells);
                 hdst[d] = ds.state;
                 hints[nd + d] = st;                   // state_of (the part's own index)
                 hints[2 * (size_t)nd + d] = P.maps[q];  // map_of
@@ -2309,16 +2316,12 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
         }
     }
     hints[3 * (size_t)nd + n_states] = nd;
-    // launch groups as in ttcf_step: (form, thermostat), form 0 pair lists at four atoms per
-    // thread, 1 cells, 2 pair lists at eight; largest systems first inside each
-    std::vector<int32_t> groups[6];
-    for (int32_t d = 0; d < nd; ++d) {
-        const int form = !nl_of[d] ? 1 : (pair_job_apt(hd[d].sys.n) == pair_small_apt() ? 0 : 2);
-        groups[2 * form + (hd[d].thermo ? 1 : 0)].push_back(d);
-    }
+    // launch groups as in ttcf_step: (form, thermostat), largest systems first inside each
+    std::vector<int32_t> groups[2 * kForms];
+    for (int32_t d = 0; d < nd; ++d) groups[2 * form_of[d] + (hd[d].thermo ? 1 : 0)].push_back(d);
     std::vector<BatchLaunch> launches;
     size_t offset = 0;
-    for (int gi = 0; gi < 6; ++gi) {
+    for (int gi = 0; gi < 2 * kForms; ++gi) {
         std::vector<int32_t>& grp = groups[gi];
         if (grp.empty()) continue;
         std::stable_sort(grp.begin(), grp.end(),
@@ -2328,19 +2331,12 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
             hp.push_back(&hd[d]);
             hints[offset + hp.size() - 1] = d;   // order
         }
-        const int form = gi / 2;
         const StepShape& sh = parts[0].shape;
         int threads_req = sh.threads;
-        bool block_explicit = false;
-        for (const GraphPart& P : parts) {
+        for (const GraphPart& P : parts)
             if (grp[0] >= P.d0 && grp[0] < P.d0 + P.nd) threads_req = P.shape.threads;
-            for (int32_t d : grp)
-                if (d >= P.d0 && d < P.d0 + P.nd)
-                    block_explicit = block_explicit || c->mothers[P.gd->mother].sys.block_threads > 0;
-        }
         BatchLaunch B{};
-        rc = plan_group(c, hp, !c->shape_explicit && !block_explicit, form == 1 ? kVariantCells : kVariantNeighbourList,
-                        precision, n_steps, threads_req, &B);
+        rc = plan_group(c, hp, gi / 2, precision, n_steps, threads_req, &B);
         if (rc != TTCF_OK) return bail(rc, c->err);
         if (list_scratch_bytes(B) > 0) {
             // the graph owns the list scratch its replays use

@@ -1706,17 +1706,17 @@ __global__ void k_spawn_pef(const double* states, int32_t n, const int32_t* stat
 
 }  // namespace
 
-int flow64_list_cap() { return kF64Cap; }
-
 size_t flow64_ext_bytes(int threads, int apt, int grid) {
     return sizeof(uint16_t) * (size_t)kF64Ext * threads * apt * grid;
 }
 
+namespace {
 // Neighbours an atom of a uniform fluid has within the list radius.
-double flow64_neighbours(double density, double rc) {
-    const double rl = rc * (1.0 + kF64Skin);
-    return 4.18879020478639 * rl * rl * rl * density;
+double flow64_neighbours(const SysDev& S) {
+    const double rl = S.rc * (1.0 + kF64Skin);
+    return 4.18879020478639 * rl * rl * rl * (S.n / S.volume);
 }
+}  // namespace
 
 // Shape of a launch. Atoms per thread: the fewest with which every daughter of the batch is on a
 // CU at once (registers: 16 waves of 128, or 8 of 256 with four atoms; and the LDS): the steps
@@ -1744,6 +1744,15 @@ bool flow64_shape(int nmax, int cells, int n_jobs, int num_cu, size_t max_lds, F
         if (fit * num_cu >= n_jobs) break;
     }
     return found;
+}
+
+// Lists wherever a workgroup holds them (the cell form rebuilds its grid and scans 27 cells in FP64
+// every step: N = 2048, 1024 daughters x 50 steps 14.97 ms, lists 3.6) and has room in LDS for half as
+// many neighbours again as the list radius holds on average, so that few atoms of a uniform fluid need
+// the global part. Whatever other daughters share the call.
+bool flow64_takes(const SysDev& S, size_t max_lds) {
+    Flow64Shape f{};
+    return 1.5 * flow64_neighbours(S) <= kF64Cap && flow64_shape(S.n, 1 << 28, 1, 1, max_lds, &f);
 }
 
 // The carried-flow batches taken: a cell grid at r_c fits one workgroup's LDS beside the state
@@ -1807,7 +1816,7 @@ hipError_t launch_flow64(const PefLaunch& L, hipStream_t s) {
 // threads beyond, which doubles the registers (two on 1024 threads spilled 80 of them).
 bool mother_lists(const SysDev& S, size_t max_lds, MotherLaunch* L) {
     L->list_lds = 0;
-    if (S.n > kMotherAtoms || 1.5 * flow64_neighbours((double)S.n / S.volume, S.rc) > kF64Cap) return false;
+    if (S.n > kMotherAtoms || 1.5 * flow64_neighbours(S) > kF64Cap) return false;
     for (int a = 0; a < 3; ++a)
         if (S.nc[a] < 3 || S.nc[a] > 63 || !(S.w[a] > S.rc * (1.0 + 2e-6))) return false;
     const int cells = pef_max_cells(S.volume, S.rc);

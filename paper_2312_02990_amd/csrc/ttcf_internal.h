@@ -394,9 +394,9 @@ hipError_t launch_response(const ResponseLaunch& r, hipStream_t s);
 // shape of a launch over n_jobs daughters of up to nmax atoms and `cells` r_c cells; false when
 // no workgroup holds the largest
 bool flow64_shape(int nmax, int cells, int n_jobs, int num_cu, size_t max_lds, Flow64Shape* out);
-int flow64_list_cap();  // neighbours a list holds in LDS
+// whether shear daughters of a system run over FP64 lists
+bool flow64_takes(const SysDev& S, size_t max_lds);
 size_t flow64_ext_bytes(int threads, int apt, int grid);  // global scratch for longer lists
-double flow64_neighbours(double density, double rc);
 int pef_max_cells(double volume, double rc);
 size_t pef_grid_bytes(int nmax, int cmax);
 hipError_t launch_flow64(const PefLaunch& L, hipStream_t s);
