@@ -432,8 +432,9 @@ int32_t ttcf_set_step_shape(ttcf_ctx* ctx, int32_t variant, int32_t threads, dou
  * `mother` (0: all; all four mappings, shear rate gamma_dot; the set repeated until there
  * are four daughters per compute unit, so that throughput is measured), over a short untimed
  * warm-up and probe_steps timed steps (they should span several list rebuilds, e.g. the
- * daughter length, or the pick favours short lists), for each candidate shape: the cell form
- * at 256, 512 and 1024 threads, and (FP32 forces) the neighbour-list form at those sizes and
+ * daughter length, or the pick favours short lists), for each candidate shape: where FP64
+ * forces take neighbour lists (see ttcf_set_step_shape), the automatic shape alone; else the
+ * cell form at 256, 512 and 1024 threads, and (FP32 forces) the pair-list form
  * at the skins that fill list cells one coarser, equal to and one finer than the automatic
  * grid, its list capacity raised while the probe overflows. Probe daughters are discarded
  * (never accumulated) and live daughters are not advanced. The fastest shape (list capacity
@@ -441,14 +442,14 @@ int32_t ttcf_set_step_shape(ttcf_ctx* ctx, int32_t variant, int32_t threads, dou
  * architecture, N, round(1000 N/V), round(10000 r_cut), precision), replacing an older entry,
  * and written to *out (may be NULL). While no explicit shape is set (ttcf_set_step_shape(ctx,
  * 0, 0, 0, 0), the default), ttcf_step uses the cached shape of each daughter's system, the
- * list grid of its skin and, per launch, the workgroup size of the largest system; with FP64
- * forces a cached shape holds where the system runs in the cell form (see
- * ttcf_set_step_shape). Synchronises
+ * list grid of its skin and, per launch, the workgroup size of the largest system; a shape of
+ * the cell form cached for FP64 forces (by an earlier version) holds only where no lists are
+ * taken. Synchronises
  * the context's stream. Errors: TTCF_EINVAL (no stored states, bad arguments, no shape fits),
  * TTCF_EDEVICE (probe daughters unhealthy other than by list overflow, or a HIP error). */
 typedef struct ttcf_shape {
-    int32_t variant;       /* 1 cell form, 2 neighbour-list form                              */
-    int32_t threads;       /* workgroup size                                                  */
+    int32_t variant;       /* 0 automatic (FP64 lists), 1 cell form, 2 pair-list form         */
+    int32_t threads;       /* workgroup size (0: automatic)                                   */
     int32_t kmax;          /* neighbour-list capacity per atom (list form)                    */
     double skin;           /* list skin, sigma (list form)                                    */
     double ms_per_step;    /* probe batch, device milliseconds per step                       */

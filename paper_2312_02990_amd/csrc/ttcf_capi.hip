@@ -1109,11 +1109,10 @@ int32_t spawn_impl(ttcf_ctx* c, int32_t mother, int32_t n_states, int64_t steps_
     return TTCF_OK;
 }
 
-// Whether a shear daughter with FP64 forces runs over neighbour lists (ttcf_flow64.hip), unless a
-// step shape is set: a system that fixes its workgroup size asks for the cell form.
-bool takes_lists64(const ttcf_ctx* c, const Mother& m, const DaughterDesc& d) {
-    return m.sys.precision == TTCF_PREC_FP64 && m.sys.block_threads <= 0 && d.field == kFieldShear &&
-           !d.xseries && flow64_takes(d.sys, c->max_lds);
+// Whether a system's shear daughters run over FP64 neighbour lists (ttcf_flow64.hip) unless a step
+// shape is set: a system that fixes its workgroup size asks for the cell form.
+bool takes_lists64(const ttcf_ctx* c, const Mother& m) {
+    return m.sys.precision == TTCF_PREC_FP64 && m.sys.block_threads <= 0 && flow64_takes(m.dev, c->max_lds);
 }
 
 // Launch groups of a step, by kernel form: pair lists at four and (more than 2048 atoms) at eight
@@ -1333,7 +1332,7 @@ int32_t step_impl(ttcf_ctx* c, int32_t n_steps, const std::vector<char>* only,
             return fail(c, TTCF_EINVAL, "colour-field daughters need the neighbour-list form, "
                                         "and this system runs in cells");
         const int form = nl ? (pair_job_apt(d.sys.n) == pair_small_apt() ? kFormPairs : kFormPairsLarge)
-                            : (automatic && takes_lists64(c, m, d) ? kFormLists64 : kFormCells);
+                            : (automatic && takes_lists64(c, m) ? kFormLists64 : kFormCells);
         groups[2 * form + (d.thermo ? 1 : 0)].push_back((int32_t)i);
     }
     auto any = [&](int form) { return !groups[2 * form].empty() || !groups[2 * form + 1].empty(); };
@@ -1502,12 +1501,15 @@ int32_t ttcf_autotune(ttcf_ctx* c, int32_t mother, int32_t n_states, double gamm
     if (n_states == 0 || n_states > m.n_states) n_states = m.n_states;
     const SysDev& d = m.dev;
     const int precision = m.sys.precision;
-    // candidate shapes: the cell form at 256, 512 and 1024 threads; the pair-list form (four
-    // atoms per thread) at the skins that fill list cells one coarser, equal to and one finer
-    // than the automatic grid
+    // candidate shapes: FP64 forces where they take neighbour lists, the automatic shape, which is
+    // the one that a step runs; else the cell form at 256, 512 and 1024 threads, and the pair-list
+    // form (four atoms per thread) at the skins that fill list cells one coarser, equal to and one
+    // finer than the automatic grid
     std::vector<StepShape> cand;
+    const bool lists64 = takes_lists64(c, m);
+    if (lists64) cand.push_back(StepShape{});
     for (int t : {256, 512, 1024}) {
-        if (pick_apt(d.n, t) < 0) continue;
+        if (lists64 || pick_apt(d.n, t) < 0) continue;
         if (lds_bytes_for(d.n, d.nc[0] * d.nc[1] * d.nc[2], t, precision) <= c->max_lds)
             cand.push_back(StepShape{1, t, 0, 0.0});
     }
@@ -1714,8 +1716,11 @@ int32_t ttcf_autotune_import(ttcf_ctx* c, const char* text) {
         t.shape.kmax = (int32_t)v[6];
         t.shape.skin = v[7];
         t.ms_per_step = v[8];
-        if (t.shape.variant < 1 || t.shape.variant > 2 || t.shape.threads % 64 != 0 ||
-            t.shape.threads < 64 || t.shape.threads > kMaxThreads || t.shape.kmax < 0 ||
+        // (variant 0, the automatic shape: FP64 lists)
+        const bool lists64 = t.shape.variant == 0 && t.precision == TTCF_PREC_FP64 &&
+                             t.shape.threads == 0 && t.shape.kmax == 0 && t.shape.skin == 0.0;
+        if ((t.shape.variant < 1 && !lists64) || t.shape.variant > 2 || t.shape.threads % 64 != 0 ||
+            (t.shape.threads < 64 && !lists64) || t.shape.threads > kMaxThreads || t.shape.kmax < 0 ||
             t.shape.kmax > (t.shape.variant == 2 ? kPairMaxCap : 255) || !(t.shape.skin >= 0.0) ||
             t.n < 2)
             return fail(c, TTCF_EINVAL, "autotune cache: shape out of range");
@@ -2307,7 +2312,7 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
                 rc = apply_shape(c, P.shape, precision, &ds, &nl);
                 if (rc != TTCF_OK) return bail(rc, c->err);
                 form_of[d] = nl ? (pair_job_apt(P.n) == pair_small_apt() ? kFormPairs : kFormPairsLarge)
-                                : (!c->shape_explicit && takes_lists64(c, m, ds) ? kFormLists64 : kFormCells);
+                                : (!c->shape_explicit && takes_lists64(c, m) ? kFormLists64 : kFormCells);
                 hdst[d] = ds.state;
                 hints[nd + d] = st;                   // state_of (the part's own index)
                 hints[2 * (size_t)nd + d] = P.maps[q];  // map_of

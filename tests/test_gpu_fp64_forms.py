@@ -69,3 +69,31 @@ def test_two_sizes_and_thermostats_in_one_call(T, orc):
             want = orc.run_daughters(box, sr, sp, one, maps, rate, DT, STEPS, nthreads=4)[0]
         # FP64 on both sides: roundings of 1e-16 grow less than a thousandfold over 30 steps
         assert np.abs(g - want).max() <= 1e-9 * np.std(want)
+
+
+def test_autotune_reports_what_runs(T):
+    """Where FP64 forces take lists there is one shape: tuned, set as returned, imported, default."""
+    print("FP64 autotune", flush=True)
+    n, out = 500, []
+    r, p, edge = state(n)
+    sysd = T.make_system(n, edge, TEMP, DT, precision=T.TTCF_PREC_FP64)
+    text = None
+    for how in ("tuned", "set", "imported", "default"):
+        with T.Context() as ctx:
+            mid = ctx.ttcf_init_mother(sysd, r, p, n_equil=0)
+            ctx.ttcf_import_states(mid, r.reshape(1, -1), p.reshape(1, -1))
+            first = ctx.ttcf_spawn_daughters(mid, 1, 0, 0.3, STEPS)
+            if how == "tuned":
+                shape = ctx.ttcf_autotune(mid, 0, 0.3, 10)
+                text = ctx.ttcf_autotune_export()
+                assert shape["variant"] == 0 and shape["candidates"] == 1 and shape["ms_per_step"] > 0.0
+            elif how == "set":
+                ctx.ttcf_set_step_shape(shape["variant"], shape["threads"], shape["skin"], shape["kmax"])
+            elif how == "imported":
+                ctx.ttcf_autotune_import(text)
+                with pytest.raises(T.TTCFError):
+                    ctx.ttcf_autotune_import(text.replace('"precision": 0', '"precision": 1'))
+            ctx.ttcf_step(STEPS)
+            out.append(ctx.ttcf_export_series(first, 4, STEPS + 1))
+    for series in out[1:]:
+        np.testing.assert_array_equal(series, out[0])
