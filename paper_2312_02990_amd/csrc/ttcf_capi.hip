@@ -1139,7 +1139,7 @@ int32_t plan_group(ttcf_ctx* c, const std::vector<const DaughterDesc*>& group, i
             cells = std::max(cells, pef_max_cells(dp->sys.volume, dp->sys.rc) + 8);
         }
         Flow64Shape f{};
-        if (!flow64_shape(L->nmax, cells, L->n_jobs, c->num_cu, c->max_lds, &f))
+        if (!flow64_shape(0, L->thermo, L->nmax, cells, L->n_jobs, c->num_cu, c->max_lds, &f))
             return fail(c, TTCF_EINVAL, "batch exceeds the LDS of one workgroup");
         L->apt = f.apt;
         L->threads = f.threads;
@@ -1414,7 +1414,7 @@ int32_t step_impl(ttcf_ctx* c, int32_t n_steps, const std::vector<char>* only,
         }
         Flow64Shape f{};
         if (pef_grid_bytes(P.nmax, cells) > c->max_lds ||
-            !flow64_shape(P.nmax, cells, P.n_jobs, c->num_cu, c->max_lds, &f))
+            !flow64_shape(P.flow, P.thermo, P.nmax, cells, P.n_jobs, c->num_cu, c->max_lds, &f))
             return fail(c, TTCF_EINVAL, "planar-elongation batch exceeds the LDS of one workgroup");
         P.threads = f.threads;
         P.apt = f.apt;

@@ -1722,11 +1722,17 @@ double flow64_neighbours(const SysDev& S) {
 // CU at once (registers: 16 waves of 128, or 8 of 256 with four atoms; and the LDS): the steps
 // of a daughter are a latency chain that more waves shorten. A batch that fills the chip either
 // way takes four: every wave repeats the step's scalars, so half the waves do it half as often
-// (N = 2048, 1024 daughters x 50 steps: 4.47 ms with two, 4.31 with four).
-bool flow64_shape(int nmax, int cells, int n_jobs, int num_cu, size_t max_lds, Flow64Shape* out) {
+// (N = 2048, 1024 daughters x 50 steps, two and four: shear 3.99 and 3.69 ms, elongation 4.35 and
+// 3.60, mixed flow 4.88 and 3.81). So does a small batch of more than 1536 atoms, whose two-atom build
+// would keep 13 to 16 waves waiting for its spills (256 daughters x 50 steps, shear, elongation, mixed:
+// N = 2048 1.09, 1.17, 1.31 and 0.99, 0.98, 1.06 ms; N = 1600 1.03, 1.06, 1.21 and 0.99, 0.97, 1.01; but
+// N = 1500 0.90, 0.92, 1.06 and 0.98, 0.98, 1.04), except elongation with Nose-Hoover, whose spills are
+// fewest (N = 1600 0.83 and 0.87 ms, N = 2048 0.88 and 0.89).
+bool flow64_shape(int flow, int thermo, int nmax, int cells, int n_jobs, int num_cu, size_t max_lds,
+                  Flow64Shape* out) {
     if (nmax > kPefMaxAtoms) return false;
     bool found = false;
-    for (int apt = 1; apt <= 4; apt *= 2) {
+    for (int apt = nmax > 1536 && !(flow == kFlowElong && thermo) ? 4 : 1; apt <= 4; apt *= 2) {
         Flow64Shape f{};
         f.apt = apt;
         f.threads = ((nmax + apt - 1) / apt + 63) / 64 * 64;
@@ -1752,7 +1758,7 @@ bool flow64_shape(int nmax, int cells, int n_jobs, int num_cu, size_t max_lds, F
 // the global part. Whatever other daughters share the call.
 bool flow64_takes(const SysDev& S, size_t max_lds) {
     Flow64Shape f{};
-    return 1.5 * flow64_neighbours(S) <= kF64Cap && flow64_shape(S.n, 1 << 28, 1, 1, max_lds, &f);
+    return 1.5 * flow64_neighbours(S) <= kF64Cap && flow64_shape(kFlowShear, 0, S.n, 1 << 28, 1, 1, max_lds, &f);
 }
 
 // The carried-flow batches taken: a cell grid at r_c fits one workgroup's LDS beside the state

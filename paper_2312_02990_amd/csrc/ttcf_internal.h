@@ -393,7 +393,8 @@ hipError_t launch_increment(int32_t* counter, hipStream_t s);
 hipError_t launch_response(const ResponseLaunch& r, hipStream_t s);
 // shape of a launch over n_jobs daughters of up to nmax atoms and `cells` r_c cells; false when
 // no workgroup holds the largest
-bool flow64_shape(int nmax, int cells, int n_jobs, int num_cu, size_t max_lds, Flow64Shape* out);
+bool flow64_shape(int flow, int thermo, int nmax, int cells, int n_jobs, int num_cu, size_t max_lds,
+                  Flow64Shape* out);
 // whether shear daughters of a system run over FP64 lists
 bool flow64_takes(const SysDev& S, size_t max_lds);
 size_t flow64_ext_bytes(int threads, int apt, int grid);  // global scratch for longer lists
