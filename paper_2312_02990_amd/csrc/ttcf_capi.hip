@@ -411,13 +411,12 @@ void mother_shape(const ttcf_ctx* c, const Mother& m, int64_t steps, MotherLaunc
     L->lds_bytes = lds_for(m.dev, m.sys.precision);
     // A system that fixes its workgroup size asks for the cell form, as for daughters. The list form
     // deals the atoms and builds its lists first, which FP32 forces (their lists are sorted, too) make
-    // up for from the second or third step on. A call of one, two and three steps, cell form and lists:
-    // N = 1000 77, 102, 127 and 81, 86, 101 us; N = 1025 91, 123, 154 and 128, 142, 165; N = 2048 110,
-    // 151, 193 and 128, 145, 161; N = 500 and fewer, and FP64, gain at one step.
+    // up for from the second step on. A call of one and two steps, cell form and lists: N = 500 69, 90
+    // and 62, 68 us; N = 1000 78, 103 and 81, 88; N = 1025 91, 122 and 96, 111; N = 1100 104, 141 and
+    // 98, 113; FP64 forces gain at one step.
+    const bool once = steps <= 1 && m.sys.precision == TTCF_PREC_FP32_FORCES && m.dev.n > 512 && m.dev.n <= 1088;
     L->list_lds = 0;
-    const int64_t few =
-        m.sys.precision != TTCF_PREC_FP32_FORCES ? 0 : (m.dev.n > 1024 ? 2 : (m.dev.n > 512 ? 1 : 0));
-    if (m.sys.block_threads <= 0 && steps > few) (void)mother_lists(m.dev, c->max_lds, L);
+    if (m.sys.block_threads <= 0 && !once) (void)mother_lists(m.dev, c->max_lds, L);
 }
 
 // Launches mothers whose launch blocks are on the device, with the context's list scratch.

@@ -1818,8 +1818,11 @@ hipError_t launch_flow64(const PefLaunch& L, hipStream_t s) {
 // Mothers over lists: where an atom's neighbours leave its list room (as for daughters), the lists
 // and a grid fit one workgroup's LDS, and (FP32 form) the stencil is three cells a side and a cell
 // and an index fit one word. Otherwise (long cutoffs, more than 2048 atoms) the cell form. One atom
-// a thread as far as 1024 threads go, as the steps are a latency chain; four on half the
-// threads beyond, which doubles the registers (two on 1024 threads spilled 80 of them).
+// a thread as far as 1024 threads go, as the steps are a latency chain; two beyond, and four with FP64
+// forces of more than 1536 atoms, whose two-atom build spills 57 registers and the four-atom one two
+// (100 steps, two and four: N = 1025 1.19 and 1.49 ms, N = 1500 1.34 and 1.58, N = 1800 1.68 and 1.64,
+// N = 2048 1.64 and 1.61; FP32 forces spill 117 and 111: N = 1025 1.69 and 2.20, N = 1500 1.96 and 2.45,
+// N = 1800 2.35 and 2.46, N = 2048 2.33 and 2.56).
 bool mother_lists(const SysDev& S, size_t max_lds, MotherLaunch* L) {
     L->list_lds = 0;
     if (S.n > kMotherAtoms || 1.5 * flow64_neighbours(S) > kF64Cap) return false;
@@ -1827,7 +1830,7 @@ bool mother_lists(const SysDev& S, size_t max_lds, MotherLaunch* L) {
         if (S.nc[a] < 3 || S.nc[a] > 63 || !(S.w[a] > S.rc * (1.0 + 2e-6))) return false;
     const int cells = pef_max_cells(S.volume, S.rc);
     L->list_cells = 2 * cells < S.n + 64 ? (cells < 27 ? 54 : 2 * cells) : S.n + 64;
-    L->list_apt = S.n <= kMaxThreads ? 1 : 4;
+    L->list_apt = S.n <= kMaxThreads ? 1 : (L->precision == 0 && S.n > 1536 ? 4 : 2);
     L->list_threads = ((S.n + L->list_apt - 1) / L->list_apt + 63) / 64 * 64;
     const size_t lds = f64_plan(S.n, L->list_cells, L->list_threads, L->list_apt).total;
     if (lds + sizeof(SysDev) + 256 > max_lds) return false;
@@ -1852,8 +1855,9 @@ hipError_t launch_mother_lists(const MotherLaunch* dev_ms, int count, const Moth
     switch (m.list_apt * 2 + (m.precision == 0 ? 0 : 1)) {
         case 2: return launch_mother_lists_t<false, 1>(dev_ms, count, m, s);
         case 3: return launch_mother_lists_t<true, 1>(dev_ms, count, m, s);
+        case 4: return launch_mother_lists_t<false, 2>(dev_ms, count, m, s);
+        case 5: return launch_mother_lists_t<true, 2>(dev_ms, count, m, s);
         case 8: return launch_mother_lists_t<false, 4>(dev_ms, count, m, s);
-        case 9: return launch_mother_lists_t<true, 4>(dev_ms, count, m, s);
     }
     return hipErrorInvalidValue;
 }
