@@ -36,8 +36,8 @@ constexpr int kChTail = 32;                          // of the list build, repea
 constexpr uint32_t kChWinXy = 4 * kChWin, kChWinType = 12 * kChWin;
 constexpr size_t kChWinBytes = 13 * (size_t)kChWin;
 
-// LDS by its address. The kernels hold no other LDS than the block that they are launched with,
-// so it starts at 0 and a window place is an address (through the block's symbol every access
+// LDS by its address. The kernels hold no other LDS than the block that they are launched with
+// (ch_window_at_zero), so it starts at 0 and a window place is an address (through the block's symbol every access
 // adds its base, two instructions a pair of the force loop).
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 template <typename V>
@@ -1160,8 +1160,15 @@ __global__ __launch_bounds__(kChThreads) void k_channel_debug_forces(ChannelLaun
 size_t channel_lds_bytes(int nmax, int cmax, bool win) { return ch_plan(nmax, cmax, win).total; }
 size_t channel_scratch_bytes(int nmax, int kmax) { return ch_scratch_bytes(nmax, kmax); }
 
+// The window's addresses start at 0, so the kernel must have no LDS of a fixed size.
+static bool ch_window_at_zero(const void* kernel) {
+    hipFuncAttributes a;
+    return hipFuncGetAttributes(&a, kernel) == hipSuccess && a.sharedSizeBytes == 0;
+}
+
 hipError_t launch_channel(const ChannelLaunch& b, hipStream_t s) {
     const size_t lds = ch_plan(b.sys.n, b.cmax, b.win).total;
+    if (!ch_window_at_zero((const void*)k_channel)) return hipErrorInvalidConfiguration;
     (void)hipFuncSetAttribute((const void*)k_channel, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
     hipLaunchKernelGGL(k_channel, dim3(b.grid), dim3(kChThreads), lds, s, b);
@@ -1170,6 +1177,7 @@ hipError_t launch_channel(const ChannelLaunch& b, hipStream_t s) {
 
 hipError_t launch_channel_debug_forces(const ChannelLaunch& b, double* out, hipStream_t s) {
     const size_t lds = ch_plan(b.sys.n, b.cmax, b.win).total;
+    if (!ch_window_at_zero((const void*)k_channel_debug_forces)) return hipErrorInvalidConfiguration;
     (void)hipFuncSetAttribute((const void*)k_channel_debug_forces,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k_channel_debug_forces, dim3(1), dim3(kChThreads), lds, s, b, out);
