@@ -208,6 +208,12 @@ int32_t ttcf_spawn_mixed(ttcf_ctx* ctx, int32_t mother, int32_t n_states, int64_
  * steps (never past its own N_d) in one persistent kernel launch per kernel form, recording
  * B(t_k) = P_xy (J_x for colour-field daughters, P_xx - P_yy for planar-elongation ones) after
  * every step. Asynchronous on the context's stream.
+ * A call repeated as it was gives the same bits. Where daughters run over FP64 lists (FP64
+ * forces, see ttcf_set_step_shape; planar elongation and mixed flow) the last bits of their
+ * series follow the number of daughters of their launch and its largest system, which choose
+ * its shape, and the list rebuilds, of which every call starts with one, so also how steps are
+ * split over calls: roundings of the sums. A system with block_threads set, or variant 1, runs
+ * shear in the cell form, which depends on neither.
  * TTCF_EINVAL when a daughter needs a kernel form its system cannot run (see
  * ttcf_record_observables, ttcf_spawn_colour and ttcf_set_step_shape). */
 int32_t ttcf_step(ttcf_ctx* ctx, int32_t n_steps);
@@ -282,7 +288,9 @@ const char* ttcf_last_error(const ttcf_ctx* ctx); /* valid until the next call o
 
 /* Alg. LAMMPS SCRIPT, "run N_s timestep, save system state" alone: the mother advances
  * steps_between steps before each of n_states saved states (replacing the stored set);
- * no daughter is spawned. */
+ * no daughter is spawned. Mothers of up to 2048 atoms with short cutoffs run over neighbour
+ * lists, which every call builds anew: how steps are split over calls changes roundings of
+ * their FP64 sums (block_threads > 0: the cell form, where it does not). */
 int32_t ttcf_sample_states(ttcf_ctx* ctx, int32_t mother, int32_t n_states,
                            int64_t steps_between);
 /* Replace the mother's stored start states by host data (n_states * 3n doubles each for
@@ -409,8 +417,9 @@ int32_t ttcf_pair_forces_static(const ttcf_system* sys, double gamma_dot, int64_
 enum { TTCF_STATIC_SCRATCH_BYTES = 1 << 20 };
 
 /* Shape of the daughter step kernel (the knobs a tuner searches). variant: 0 automatic (FP32
- * forces: 2 where it fits, else 1; FP64 forces: neighbour lists kept in LDS over several steps
- * for systems of up to 2048 atoms without a block_threads of their own, else 1),
+ * forces: 2 where it fits, else 1; FP64 forces: neighbour lists kept over several steps for
+ * systems of up to 2048 atoms with short cutoffs and without a block_threads of their own,
+ * else 1; for each daughter by its own system),
  * 1 cell list rebuilt every step (FP64 or FP32 forces), 2 pair list of radius r_cut + skin
  * rebuilt when needed (FP32 forces, at most 4096 atoms: every pair within the radius stored
  * once in per-workgroup global scratch, four atoms per thread, pair forces summed in 32-bit
@@ -420,9 +429,10 @@ enum { TTCF_STATIC_SCRATCH_BYTES = 1 << 20 };
  * grid of a 0.2 sigma skin, with the skin widened to fill those cells); kmax: pair capacity
  * per atom of the pair form, at most 64 (<= 0: 1.5 times half the ideal-gas count within the
  * list radius, plus two); a daughter whose list outgrows it is marked unhealthy (list
- * overflow). Affects the following ttcf_step calls; results do not depend on the skin,
- * capacity or rebuild schedule (integer force sums do not depend on their order, and pairs
- * beyond r_cut contribute nothing). */
+ * overflow). Affects the following ttcf_step calls. Results of the pair form do not depend on
+ * the skin, capacity or rebuild schedule (integer force sums do not depend on their order, and
+ * pairs beyond r_cut contribute nothing); those of the cell form follow the workgroup size of
+ * the launch. Over FP64 lists the order of a daughter's sums follows more (see ttcf_step). */
 int32_t ttcf_set_step_shape(ttcf_ctx* ctx, int32_t variant, int32_t threads, double skin,
                             int32_t kmax);
 

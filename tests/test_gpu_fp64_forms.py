@@ -97,3 +97,30 @@ def test_autotune_reports_what_runs(T):
             out.append(ctx.ttcf_export_series(first, 4, STEPS + 1))
     for series in out[1:]:
         np.testing.assert_array_equal(series, out[0])
+
+
+@pytest.mark.parametrize("n", [300, 1100])
+@pytest.mark.parametrize("flow", ["shear", "elong", "mixed"])
+def test_shapes_and_splits_agree_to_rounding(T, n, flow):
+    """A start state alone (one or two atoms a thread), in a batch that fills the chip (four), and over
+    two step calls: sums in other orders, lists rebuilt on other steps."""
+    print(f"FP64 lists {flow} n={n} in several shapes", flush=True)
+    r, p, edge = state(n)
+    sysd = T.make_system(n, edge, TEMP, DT, precision=T.TTCF_PREC_FP64)
+    out = []
+    for copies, parts in ((1, (STEPS,)), (322, (STEPS,)), (1, (11, STEPS - 11))):
+        with T.Context() as ctx:
+            mid = ctx.ttcf_init_mother(sysd, r, p, n_equil=0)
+            ctx.ttcf_import_states(mid, np.repeat(r.reshape(1, -1), copies, 0), np.repeat(p.reshape(1, -1), copies, 0))
+            if flow == "mixed":
+                first = ctx.ttcf_spawn_mixed(mid, copies, 0, 0.2, 0.3, STEPS)
+            elif flow == "elong":
+                first = ctx.ttcf_spawn_elongational(mid, copies, 0, 0.3, STEPS)
+            else:
+                first = ctx.ttcf_spawn_daughters(mid, copies, 0, 0.3, STEPS)
+            for k in parts:
+                ctx.ttcf_step(k)
+            out.append(ctx.ttcf_export_series(first, 4, STEPS + 1))
+    for series in out[1:]:
+        # roundings of 1e-16 grow less than a thousandfold over 30 steps
+        assert np.abs(series - out[0]).max() <= 1e-12 * np.abs(out[0]).max()
