@@ -422,7 +422,7 @@ void mother_shape(const ttcf_ctx* c, const Mother& m, int64_t steps, MotherLaunc
 // Launches mothers whose launch blocks are on the device, with the context's list scratch.
 int32_t run_mothers(ttcf_ctx* c, int32_t count, MotherLaunch& shape) {
     if (shape.list_lds > 0) {
-        const int32_t rc = ensure_nl_scratch(c, flow64_ext_bytes(shape.list_threads, shape.list_apt, count));
+        const int32_t rc = ensure_nl_scratch(c, mother_ext_bytes(shape, count));
         if (rc != TTCF_OK) return rc;
         shape.ext = (uint16_t*)c->nl_scratch;
     }
@@ -2262,8 +2262,7 @@ int32_t graph_create_impl(ttcf_ctx* c, const ttcf_graph_desc* gds, int32_t n_des
         for (auto& L : P.ml)
             mother_shape(c, m, (int64_t)gd->states_per_replica * gd->steps_between, &L);
         if (P.ml[0].list_lds > 0) {  // the graph owns the scratch its replays use
-            P.ml[0].ext = (uint16_t*)g->get(
-                flow64_ext_bytes(P.ml[0].list_threads, P.ml[0].list_apt, P.n_copies));
+            P.ml[0].ext = (uint16_t*)g->get(mother_ext_bytes(P.ml[0], P.n_copies));
             if (!P.ml[0].ext) return bail(TTCF_ENOMEM, "list scratch allocation failed");
         }
         for (int r = 0; r < P.n_copies; ++r) {

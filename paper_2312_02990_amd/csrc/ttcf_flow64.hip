@@ -1839,16 +1839,34 @@ bool mother_lists(const SysDev& S, size_t max_lds, MotherLaunch* L) {
 }
 
 namespace {
+// Mothers of a launch: as many whole rounds of the chip's CUs as have their list scratch in 512 MB
+// (1024 of N = 2048); more follow in further launches over the same scratch.
+int mothers_at_once(const MotherLaunch& m) {
+    const size_t most = ((size_t)512 << 20) / flow64_ext_bytes(m.list_threads, m.list_apt, 1);
+    return (int)(most / 256 * 256);
+}
+
 template <bool F32, int APT>
 hipError_t launch_mother_lists_t(const MotherLaunch* dev_ms, int count, const MotherLaunch& m,
                                  hipStream_t s) {
     (void)hipFuncSetAttribute((const void*)k_mother_lists<F32, APT>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)m.list_lds);
-    hipLaunchKernelGGL((k_mother_lists<F32, APT>), dim3(count), dim3(m.list_threads), m.list_lds, s, dev_ms,
-                       m.ext, m.sys.n, m.list_cells);
-    return hipGetLastError();
+    const int held = mothers_at_once(m);
+    for (int b = 0; b < count; b += held) {
+        const int part = count - b < held ? count - b : held;
+        hipLaunchKernelGGL((k_mother_lists<F32, APT>), dim3(part), dim3(m.list_threads), m.list_lds, s,
+                           dev_ms + b, m.ext, m.sys.n, m.list_cells);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 }  // namespace
+
+size_t mother_ext_bytes(const MotherLaunch& m, int count) {
+    const int held = mothers_at_once(m);
+    return flow64_ext_bytes(m.list_threads, m.list_apt, count < held ? count : held);
+}
 
 hipError_t launch_mother_lists(const MotherLaunch* dev_ms, int count, const MotherLaunch& m,
                                hipStream_t s) {

@@ -172,7 +172,7 @@ struct MotherLaunch {
     int32_t threads, apt, precision;
     int32_t list_cells, list_threads, list_apt;  // mother_lists
     size_t list_lds;       // its LDS, or 0: the cell form
-    uint16_t* ext;         // (launch shape) flow64_ext_bytes of the launch
+    uint16_t* ext;         // (launch shape) mother_ext_bytes of the launch
     size_t lds_bytes;      // the cell form's
 };
 
@@ -343,6 +343,7 @@ hipError_t copy_rows(RowStage& stage, void* host, void* dev, size_t pitch, size_
 hipError_t launch_zero_int(int32_t* p, hipStream_t s);
 hipError_t launch_daughters(const BatchLaunch& b, hipStream_t s);
 bool mother_lists(const SysDev& S, size_t max_lds, MotherLaunch* L);
+size_t mother_ext_bytes(const MotherLaunch& m, int count);
 hipError_t launch_mother_lists(const MotherLaunch* dev_ms, int count, const MotherLaunch& m,
                                hipStream_t s);
 hipError_t launch_mothers(const MotherLaunch* dev_ms, int count, const MotherLaunch& shape,
