@@ -636,8 +636,7 @@ __device__ void ch_rebuild(const ChannelDev& S, const ChScratch& G, const ChLds&
         ch_rebuild_scan<false>(S, G, L);
 }
 
-// 1 / x, correctly rounded: the hardware estimate and one Newton step give the bits of the IEEE
-// division for every normal x (all 2^23 mantissas checked on gfx950).
+// 1 / x for normal x, to a rounding: the hardware estimate (an ulp) and one Newton step.
 __device__ __forceinline__ float ch_recip(float x) {
     const float r = __builtin_amdgcn_rcpf(x);
     return __builtin_fmaf(r, __builtin_fmaf(-x, r, 1.0f), r);

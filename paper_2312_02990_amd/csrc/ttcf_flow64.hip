@@ -38,8 +38,8 @@
 // step spends most of its lanes on candidates out of range; a list of about 8 entries per atom of
 // which 5 are in range leaves the pair arithmetic (32 FP64 instructions a pair). Measured on one
 // MI355X against the kernels that scanned the stencil every step: 1024 daughters of N = 2048 over
-// 50 steps, shear 14.97 ms -> 3.80 (2.8e10 atom-steps/s), elongation 15.09 -> 3.64; 256 mixed-flow
-// Nose-Hoover daughters of N = 864 over 100 steps 4.91 -> 1.05. Of a step's time about half is
+// 50 steps, shear 13.4 ms -> 3.74 (2.8e10 atom-steps/s), elongation 13.6 -> 3.61; 256 mixed-flow
+// Nose-Hoover daughters of N = 864 over 100 steps 4.41 -> 1.09. Of a step's time about half is
 // the force pass, a fifth the list builds, the rest the step's scalars and the two barriers.
 
 #include <math.h>
@@ -1232,7 +1232,7 @@ __global__ void __launch_bounds__(APT == 4 ? 512 : 1024, APT == 4 ? 2 : 4) k_flo
 // What bounds a step is a CU's vector issue in the pair sums, of which the longest list of a wave
 // sets the number of trips (13 for a mean of 8), then the builds (a fifth) and the waves that wait
 // for one with several lanes out of turn. Measured on one MI355X, a step of one mother, cell form
-// -> lists: N = 2048 45.8 -> 27.1 us (FP64 61.7 -> 16.9), N = 1000 24.3 -> 14.6 (32.3 -> 9.0); 256
+// -> lists: N = 2048 43.8 -> 23.1 us (FP64 59.7 -> 15.6), N = 1000 22.3 -> 12.8 (30.3 -> 7.6); 256
 // copies of N = 500 sampled over 150 steps 9.6 -> 2.0 ms with their export.
 
 constexpr int kSort32 = 16;  // longest list that is sorted in registers
@@ -1753,7 +1753,7 @@ bool flow64_shape(int flow, int thermo, int nmax, int cells, int n_jobs, int num
 }
 
 // Lists wherever a workgroup holds them (the cell form rebuilds its grid and scans 27 cells in FP64
-// every step: N = 2048, 1024 daughters x 50 steps 14.97 ms, lists 3.6) and has room in LDS for half as
+// every step: N = 2048, 1024 daughters x 50 steps 13.4 ms, lists 3.74) and has room in LDS for half as
 // many neighbours again as the list radius holds on average, so that few atoms of a uniform fluid need
 // the global part. Whatever other daughters share the call.
 bool flow64_takes(const SysDev& S, size_t max_lds) {
@@ -1761,8 +1761,8 @@ bool flow64_takes(const SysDev& S, size_t max_lds) {
     return 1.5 * flow64_neighbours(S) <= kF64Cap && flow64_shape(kFlowShear, 0, S.n, 1 << 28, 1, 1, max_lds, &f);
 }
 
-// The carried-flow batches taken: a cell grid at r_c fits one workgroup's LDS beside the state
-// (sparser systems are refused).
+// The carried-flow batches taken: a cell grid at r_c fits one workgroup's LDS beside the state. Sparser
+// systems are refused, as they always were (k_flow64 itself would hold them).
 size_t pef_grid_bytes(int nmax, int cmax) {
     return 3 * f64_align(sizeof(double) * (size_t)nmax) + f64_align(sizeof(int32_t) * ((size_t)cmax + 1)) +
            f64_align(sizeof(int32_t) * (size_t)cmax) + f64_align(sizeof(uint16_t) * (size_t)nmax) +

@@ -11,7 +11,7 @@ constexpr int kMaxWaves = kMaxThreads / 64;
 constexpr int kRedSlots = 12;       // doubles reduced per block reduction
 constexpr int kMaxCells1D = 1023;   // packed cell coordinates use 10 bits each
 constexpr int kMaxAtoms = 65535;    // sorted atom ids are stored as uint16
-constexpr int kPefMaxAtoms = 2048;  // FP64 list form (ttcf_flow64.hip): two atoms per thread
+constexpr int kPefMaxAtoms = 2048;  // FP64 list form (ttcf_flow64.hip): up to four atoms per thread
 
 // Constants of one simulated system, uniform inside a workgroup.
 struct SysDev {
