@@ -296,8 +296,8 @@ __device__ __forceinline__ Row64 f64_row(const uint16_t* start, int nx, int ny, 
 // Counting sort of the atoms into the grid's cells, members of a cell in index order (an atom's
 // place is the number of smaller indexes in its cell, so the order does not depend on the
 // placement atomics). place[j]: the sorted slot of atom t + j T; cell[j] its cell (-1: no atom);
-// cart: its position in the tilted cell. Begins with nothing of the previous list in use; ends without a barrier
-// (S.start and S.sid are complete).
+// cart: its position in the tilted cell. Begins with nothing of the previous list in use; ends without
+// a barrier (S.start and S.sid are complete).
 template <int F, int APT>
 __device__ __forceinline__ void f64_sort(const F64Lds& S, const Cell64& H, const Grid64& g, int n,
                                          const double (&x)[APT], const double (&y)[APT],
@@ -348,8 +348,9 @@ __device__ __forceinline__ void f64_sort(const F64Lds& S, const Cell64& H, const
 
 // Builds the lists of the positions x, y, z (wrapped into the cell here) and publishes them in
 // S.xy, S.z; without STATE they are taken as they are (in the cell) and not published. nh: the own
-// atoms' list lengths (kF64Over + cell: longer than any list); returns the wave's longest. The scan runs in FP32 over nine rows of five half cells, kScan candidates per lane per
-// trip; the FP32 test has a margin for its own rounding, so a list misses no pair of its radius.
+// atoms' list lengths (kF64Over + cell: longer than any list); returns the wave's longest. The scan
+// runs in FP32 over nine rows of five half cells, kScan candidates per lane per trip; the FP32 test
+// has a margin for its own rounding, so a list misses no pair of its radius.
 template <int F, int APT, bool STATE = true>
 __device__ __forceinline__ int f64_build(const F64Lds& S, const Cell64& H, int n, int cmax, double rc,
                          double (&x)[APT], double (&y)[APT], double (&z)[APT], List64& L,
@@ -521,8 +522,8 @@ __device__ __forceinline__ void f64_more(const F64Lds& S, const List64& L, int n
 // seen from both sides, so each side adds half. The thread's atoms run side by side (up to four
 // independent chains), the next list word and positions loaded a trip ahead.
 template <int F, int APT>
-__device__ __forceinline__ void f64_forces(const F64Lds& S, const Cell64& H, const List64& L, int n, double rc2,
-                                           double ca, const int (&nh)[APT], int longest,
+__device__ __forceinline__ void f64_forces(const F64Lds& S, const Cell64& H, const List64& L,
+                                           int n, double rc2, double ca, const int (&nh)[APT], int longest,
                                            double (&fx)[APT], double (&fy)[APT],
                                            double (&fz)[APT], double& w0, double& w1) {
     const int T = blockDim.x, t = threadIdx.x;
@@ -618,7 +619,8 @@ __device__ __forceinline__ void f64_forces(const F64Lds& S, const Cell64& H, con
             fz[q + j] = gz[j];
         }
     }
-    if (__builtin_expect(longest > kF64Cap, 0)) {  // entries beyond LDS, an atom at a time (most waves have none)
+    // entries beyond LDS, an atom at a time (most waves have none)
+    if (__builtin_expect(longest > kF64Cap, 0)) {
 #pragma unroll 1
         for (int j = 0; j < APT; ++j) {
             int count = nh[0];
